@@ -214,20 +214,66 @@ struct StepArgs {
     const double *dyn;
 };
 
-// Total field of Eq. 4 at (x, y, z), radial part projected by Eq. 3.
-template <class P, class Tab>
-__device__ __forceinline__ void efield(const StepArgs<P, Tab> &a, typename P::T x, typename P::T y,
+// Total field of Eq. 4 at (x, y, z), radial part projected by Eq. 3
+// (gather: the E record interpolated in a cell).
+template <class P, class Tab, class Gather>
+__device__ __forceinline__ void efield(const StepArgs<P, Tab> &a, Gather &&gather, typename P::T x, typename P::T y,
                                        typename P::T z, typename P::T c, typename P::T &ex, typename P::T &ey,
                                        typename P::T &ez) {
     using T = typename P::T;
     const T r = P::sqrt_(x * x + y * y);
     const Cell<T> cl = locate<T>(r, z, (T)a.inv_dr, (T)a.inv_dz, a.nr, a.nz);
-    const Q4<T> q = gather4<T>(a.etab, a.esc, cl, a.nr);
+    const Q4<T> q = gather(cl);
     const T er = q.a + c * q.c;
     ez = q.b + c * q.d;
     const T s = r > (T)0 ? P::div(er, r) : (T)0;
     ex = s * x;
     ey = s * y;
+}
+
+// A pack's position (high and low parts; low zero in the FP64 form) and
+// velocity.
+template <class T>
+struct Motion {
+    T x, y, z, xl, yl, zl, vx, vy, vz;
+};
+
+// Classical RK4 on (x, v) over the step; stages at t, t + dt/2, t + dt/2,
+// t + dt.
+template <class P, class Tab, class Gather>
+__device__ __forceinline__ void push_rk4(const StepArgs<P, Tab> &a, Gather &&gather, typename P::T qm,
+                                         Motion<typename P::T> &p) {
+    using T = typename P::T;
+    const T dt = (T)a.dt, hd = (T)0.5 * dt;
+    const T x0 = p.x, y0 = p.y, z0 = p.z, xl = p.xl, yl = p.yl, zl = p.zl, vx0 = p.vx, vy0 = p.vy, vz0 = p.vz;
+    T ex, ey, ez;
+    efield(a, gather, x0, y0, z0, (T)a.c0, ex, ey, ez);
+    T ax = qm * ex, ay = qm * ey, az = qm * ez;
+    T sxx = vx0, sxy = vy0, sxz = vz0, svx = ax, svy = ay, svz = az;
+    T kx = vx0 + hd * ax, ky = vy0 + hd * ay, kz = vz0 + hd * az;
+    efield(a, gather, x0 + (xl + hd * vx0), y0 + (yl + hd * vy0), z0 + (zl + hd * vz0), (T)a.ch, ex, ey, ez);
+    ax = qm * ex; ay = qm * ey; az = qm * ez;
+    sxx += (T)2 * kx; sxy += (T)2 * ky; sxz += (T)2 * kz;
+    svx += (T)2 * ax; svy += (T)2 * ay; svz += (T)2 * az;
+    const T k2x = kx, k2y = ky, k2z = kz;
+    kx = vx0 + hd * ax; ky = vy0 + hd * ay; kz = vz0 + hd * az;
+    efield(a, gather, x0 + (xl + hd * k2x), y0 + (yl + hd * k2y), z0 + (zl + hd * k2z), (T)a.ch, ex, ey, ez);
+    ax = qm * ex; ay = qm * ey; az = qm * ez;
+    sxx += (T)2 * kx; sxy += (T)2 * ky; sxz += (T)2 * kz;
+    svx += (T)2 * ax; svy += (T)2 * ay; svz += (T)2 * az;
+    const T k3x = kx, k3y = ky, k3z = kz;
+    kx = vx0 + dt * ax; ky = vy0 + dt * ay; kz = vz0 + dt * az;
+    efield(a, gather, x0 + (xl + dt * k3x), y0 + (yl + dt * k3y), z0 + (zl + dt * k3z), (T)a.c1, ex, ey, ez);
+    ax = qm * ex; ay = qm * ey; az = qm * ez;
+    sxx += kx; sxy += ky; sxz += kz;
+    svx += ax; svy += ay; svz += az;
+    const T d6 = dt / (T)6;
+    acc2(p.x, p.xl, d6 * sxx);
+    acc2(p.y, p.yl, d6 * sxy);
+    acc2(p.z, p.zl, d6 * sxz);
+    p.vx = vx0 + d6 * svx;
+    p.vy = vy0 + d6 * svy;
+    p.vz = vz0 + d6 * svz;
 }
 
 // Terminal event: int64 tallies (class weights, Eq. 8 exit-current bins,
@@ -295,14 +341,15 @@ struct GasAt {
     bool gas;
 };
 
-template <class P, class Tab>
-__device__ __forceinline__ GasAt<typename P::T> gas_at(const StepArgs<P, Tab> &a, const Species &sp,
+// (gather: the gas record interpolated in a cell)
+template <class P, class Tab, class Gather>
+__device__ __forceinline__ GasAt<typename P::T> gas_at(const StepArgs<P, Tab> &a, const Species &sp, Gather &&gather,
                                                        typename P::T rr, typename P::T x1, typename P::T y1,
                                                        typename P::T z1) {
     using T = typename P::T;
     const T m = (T)sp.m, ccs = (T)sp.ccs;
     const Cell<T> cl = locate<T>(rr, z1, (T)a.inv_dr, (T)a.inv_dz, a.nr, a.nz);
-    const Q4<T> g = gather4<T>(a.gtab, a.gsc, cl, a.nr);
+    const Q4<T> g = gather(cl);
     const T sr = rr > (T)0 ? P::div(g.a, rr) : (T)0;
     GasAt<T> o;
     o.ux = sr * x1;
@@ -505,57 +552,29 @@ __device__ __forceinline__ void step_one(const StepArgs<P, Tab> &a, int64_t s, S
         // collision loop (at five waves in the FP32 form and three in the FP64
         // form they would spill)
         const Species &sp = a.sp[kOneSpecies ? 0 : tag];
-        const T dt = (T)a.dt, qm = (T)sp.qm, hd = (T)0.5 * dt;
-        const T xl0 = xl, yl0 = yl, zl0 = zl;
-
-        // ---- classical RK4 on (x, v); stages at t, t + dt/2, t + dt/2, t + dt ----
-        T ex, ey, ez;
-        efield(a, x0, y0, z0, (T)a.c0, ex, ey, ez);
-        T ax = qm * ex, ay = qm * ey, az = qm * ez;
-        T sxx = vx0, sxy = vy0, sxz = vz0, svx = ax, svy = ay, svz = az;
-        T kx = vx0 + hd * ax, ky = vy0 + hd * ay, kz = vz0 + hd * az;
-        efield(a, x0 + (xl + hd * vx0), y0 + (yl + hd * vy0), z0 + (zl + hd * vz0), (T)a.ch, ex, ey, ez);
-        ax = qm * ex; ay = qm * ey; az = qm * ez;
-        sxx += (T)2 * kx; sxy += (T)2 * ky; sxz += (T)2 * kz;
-        svx += (T)2 * ax; svy += (T)2 * ay; svz += (T)2 * az;
-        const T k2x = kx, k2y = ky, k2z = kz;
-        kx = vx0 + hd * ax; ky = vy0 + hd * ay; kz = vz0 + hd * az;
-        efield(a, x0 + (xl + hd * k2x), y0 + (yl + hd * k2y), z0 + (zl + hd * k2z), (T)a.ch, ex, ey, ez);
-        ax = qm * ex; ay = qm * ey; az = qm * ez;
-        sxx += (T)2 * kx; sxy += (T)2 * ky; sxz += (T)2 * kz;
-        svx += (T)2 * ax; svy += (T)2 * ay; svz += (T)2 * az;
-        const T k3x = kx, k3y = ky, k3z = kz;
-        kx = vx0 + dt * ax; ky = vy0 + dt * ay; kz = vz0 + dt * az;
-        efield(a, x0 + (xl + dt * k3x), y0 + (yl + dt * k3y), z0 + (zl + dt * k3z), (T)a.c1, ex, ey, ez);
-        ax = qm * ex; ay = qm * ey; az = qm * ez;
-        sxx += kx; sxy += ky; sxz += kz;
-        svx += ax; svy += ay; svz += az;
-        const T d6 = dt / (T)6;
-        T x1 = x0, y1 = y0, z1 = z0;
-        acc2(x1, xl, d6 * sxx);
-        acc2(y1, yl, d6 * sxy);
-        acc2(z1, zl, d6 * sxz);
-        T vx = vx0 + d6 * svx, vy = vy0 + d6 * svy, vz = vz0 + d6 * svz;
+        Motion<T> m{x0, y0, z0, xl, yl, zl, vx0, vy0, vz0};
+        push_rk4(a, [&](const Cell<T> &c) { return gather4<T>(a.etab, a.esc, c, a.nr); }, (T)sp.qm, m);
+        const T x1 = m.x, y1 = m.y, z1 = m.z;
+        T vx = m.vx, vy = m.vy, vz = m.vz;
 
         // ---- terminal classification at the new position ----
-        // (the FP64 form performs exactly the IEEE operations of its reference;
-        // the two-float form classifies its full-precision position in FP64)
-        const double X1 = (double)x1 + (double)xl, Y1 = (double)y1 + (double)yl, Z1 = (double)z1 + (double)zl;
+        const double X1 = (double)x1 + (double)m.xl, Y1 = (double)y1 + (double)m.yl, Z1 = (double)z1 + (double)m.zl;
         double r1;
         {
 #pragma clang fp contract(off)
-        r1 = sqrt(X1 * X1 + Y1 * Y1);
+            r1 = sqrt(X1 * X1 + Y1 * Y1);
         }
         // the gas at the new position, gathered before the hit test so that
         // the two reads overlap (a pack that turns out terminal discards it;
         // the gather's cell is clamped, so any position reads in bounds)
         GasAt<T> g{};
-        if (a.collisions_on) g = gas_at(a, sp, (T)r1, x1, y1, z1);
+        if (a.collisions_on)
+            g = gas_at(a, sp, [&](const Cell<T> &c) { return gather4<T>(a.gtab, a.gsc, c, a.nr); }, (T)r1, x1, y1, z1);
         int32_t cls = ST_ACTIVE, in = -1, jn = -1;
         double tcross = 0.0, rcross = 0.0;
         {
 #pragma clang fp contract(off)
-        const double X0 = (double)x0 + (double)xl0, Y0 = (double)y0 + (double)yl0, Zo = (double)z0 + (double)zl0;
+        const double X0 = (double)x0 + (double)xl, Y0 = (double)y0 + (double)yl, Zo = (double)z0 + (double)zl;
         const bool finite = isfinite(X1) && isfinite(Y1) && isfinite(Z1) && isfinite((double)vx) &&
                             isfinite((double)vy) && isfinite((double)vz);
         if (!finite) {
@@ -598,9 +617,9 @@ __device__ __forceinline__ void step_one(const StepArgs<P, Tab> &a, int64_t s, S
         a.p.y[s] = y1;
         a.p.z[s] = z1;
         if constexpr (P::kTwo) {
-            a.p.xl[s] = xl;
-            a.p.yl[s] = yl;
-            a.p.zl[s] = zl;
+            a.p.xl[s] = m.xl;
+            a.p.yl[s] = m.yl;
+            a.p.zl[s] = m.zl;
         }
         bool lang = false;
         if (cls == ST_ACTIVE && a.collisions_on) {
@@ -636,8 +655,8 @@ __device__ __forceinline__ void step_one(const StepArgs<P, Tab> &a, int64_t s, S
             }
         } else {
             read_e();
-            record_exit(a, s, cls, in, jn, X1, Y1, Z1, (double)vx, (double)vy, (double)vz, tcross, rcross,
-                        (double)e + (double)el, (double)a.p.h[s], sp);
+            record_exit(a, s, cls, in, jn, X1, Y1, Z1, (double)vx, (double)vy, (double)vz, tcross,
+                        rcross, (double)e + (double)el, (double)a.p.h[s], sp);
             a.p.status[s] = cls;
         }
         a.p.vx[s] = vx;
@@ -748,7 +767,8 @@ __global__ __launch_bounds__(256) void k_dt_limits(StepArgs<P, Tab> a, unsigned 
         const T vn = P::sqrt_(vx * vx + vy * vy + vz * vz);
         if (vn > (T)0) lim = fmin(lim, (double)((T)0.5 * P::div(h, vn)));
         T ex, ey, ez;
-        efield(a, x, y, z, (T)(a.dyn ? a.dyn[6] : a.c0), ex, ey, ez);
+        efield(a, [&](const Cell<T> &c) { return gather4<T>(a.etab, a.esc, c, a.nr); }, x, y, z,
+               (T)(a.dyn ? a.dyn[6] : a.c0), ex, ey, ez);
         const T an = (T)fabs(sp.qm) * P::sqrt_(ex * ex + ey * ey + ez * ez);
         const T rr = P::sqrt_(x * x + y * y);
         const Cell<T> cl = locate<T>(rr, z, (T)a.inv_dr, (T)a.inv_dz, a.nr, a.nz);

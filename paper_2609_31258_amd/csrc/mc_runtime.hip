@@ -19,6 +19,7 @@
 #include "mc_kernels.hpp"
 #include "mc_poisson.hpp"
 #include "mc_sort.hpp"
+#include "mc_stretch.hpp"
 
 using namespace mc;
 
@@ -38,6 +39,7 @@ constexpr int64_t kAggBlocks = 1024;
 struct EvPair {
     hipEvent_t a, b;
     int kind;
+    int64_t count;  // launches that the pair stands for: a stretch's launch counts as its steps
 };
 
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -55,6 +57,7 @@ struct mc_ctx {
     bool has_fields = false, has_op = false;
     int32_t nr = 0, nz = 0;
     double dr = 0, dz = 0, inv_dr = 0, inv_dz = 0, R = 0;
+    double gas_n_max = 0, gas_t_max = 0;  // largest number density and temperature of the gas table
 
     double2 *e_dc = nullptr, *e_off = nullptr, *e_rf = nullptr, *e_sc = nullptr;
     StepTables *tables = nullptr;  // the FP64 step's logarithm and turn tables
@@ -209,8 +212,9 @@ static hipEvent_t ev_get(mc_ctx *ctx) {
 struct Timer {
     mc_ctx *ctx;
     int kind;
+    int64_t count;
     hipEvent_t a = nullptr;
-    Timer(mc_ctx *c, int k) : ctx(c), kind(k) {
+    Timer(mc_ctx *c, int k, int64_t n = 1) : ctx(c), kind(k), count(n) {
         if (ctx->opt.timing) {
             a = ev_get(ctx);
             if (a) (void)hipEventRecord(a, ctx->stream);
@@ -221,7 +225,7 @@ struct Timer {
             hipEvent_t b = ev_get(ctx);
             if (!b) return;
             (void)hipEventRecord(b, ctx->stream);
-            ctx->ev_used.push_back(EvPair{a, b, kind});
+            ctx->ev_used.push_back(EvPair{a, b, kind, count});
         }
     }
 };
@@ -231,7 +235,7 @@ static void resolve_timing(mc_ctx *ctx) {
         float ms = 0.f;
         (void)hipEventSynchronize(p.b);
         if (hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) ctx->t_ms[p.kind] += ms;
-        ctx->t_launch[p.kind]++;
+        ctx->t_launch[p.kind] += p.count;
         ctx->ev_pool.push_back(p.a);
         ctx->ev_pool.push_back(p.b);
     }
@@ -326,8 +330,8 @@ static int32_t bake_fold(mc_ctx *ctx, unsigned long long *clear) {
 }
 
 template <class P, class Tab>
-static int32_t launch_emit(mc_ctx *ctx, int si, int64_t count, PackPtrs<typename P::T> p) {
-    Src &S = ctx->srcs[si];
+static EmitArgs<P, Tab> emit_args(mc_ctx *ctx, int si, int64_t count, PackPtrs<typename P::T> p) {
+    const Src &S = ctx->srcs[si];
     EmitArgs<P, Tab> a{};
     a.p = p;
     a.gtab = gtab_as<Tab>(ctx);
@@ -349,6 +353,12 @@ static int32_t launch_emit(mc_ctx *ctx, int si, int64_t count, PackPtrs<typename
     a.ion = S.in.ion;
     a.k0 = (uint32_t)ctx->opt.seed;
     a.k1 = (uint32_t)(ctx->opt.seed >> 32);
+    return a;
+}
+
+template <class P, class Tab>
+static int32_t launch_emit(mc_ctx *ctx, int si, int64_t count, PackPtrs<typename P::T> p) {
+    const EmitArgs<P, Tab> a = emit_args<P, Tab>(ctx, si, count, p);
     Timer t(ctx, MC_K_EMIT);
     k_emit<P, Tab><<<grid_for(count), kBlock, 0, ctx->stream>>>(a);
     LAUNCHCHK();
@@ -433,10 +443,109 @@ static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, do
     return MC_OK;
 }
 
+// Lanes per pack of the stretch kernel for a launch of `steps` steps over n
+// slots, or 0 where k_step is the faster kernel.
+//
+// Lanes: the most, up to 16, that leave one wavefront per SIMD (65536 lanes);
+// the FP32 form's candidates cost less of what the lanes share out than of
+// what each repeats, and two wavefronts per SIMD still gain (FP64 form at
+// 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form at 3.2e4 packs: 4 lanes
+// 25 us, 2 lanes 27 us).  On the Langevin branch there is nothing to share.
+//
+// One lane per pack, several steps: wherever the collision loop does not
+// dominate -- the Langevin branch, or gas so thin that a step draws few
+// candidates (kThinGas) -- and up to the populations where k_step's larger
+// occupancy (three wavefronts per SIMD in the FP64 form, five in the FP32
+// form) outweighs the end of its launches: FP64 3e5 packs 380 against 380 us
+// and 6e5 packs 716 against 669, FP32 6e5 packs 301 against 305 us and 1e6
+// 479 against 468.
+constexpr int64_t kStretchLanes = 65536;
+constexpr int64_t kStretchPacks64 = 300000, kStretchPacks32 = 700000;
+constexpr double kThinGas = 16.0;
+
+// Largest candidate count per step that the gas, the ions and the step allow
+// a pack moving slowly in the gas.
+static double densest_step(const mc_ctx *ctx) {
+    double ccs = 0.0;
+    for (const mc_ion &i : ctx->ions) ccs = std::max(ccs, i.ccs_m2);
+    const double abar = std::sqrt(8.0 * kB * ctx->gas_t_max / (kPi * ctx->op.gas_mass_da * kDa));
+    return ctx->op.collisions_on ? ctx->gas_n_max * ccs * abar * ctx->op.dt : 0.0;
+}
+
+static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
+    if (n <= 0) return 0;
+    const int64_t lanes = ctx->fp32() && !ctx->op.langevin_on ? 2 * kStretchLanes : kStretchLanes;
+    int g = 16;
+    while (g > 1 && n * g > lanes) g >>= 1;
+    if (g > 1) return g;
+    if (steps < 2) return 0;
+    return ctx->op.langevin_on || n <= (ctx->fp32() ? kStretchPacks32 : kStretchPacks64) ||
+                   densest_step(ctx) < kThinGas
+               ? 1
+               : 0;
+}
+
+template <class P, class Tab>
+static int32_t launch_stretch(mc_ctx *ctx, PackPtrs<typename P::T> p, int lanes, const StretchSteps &st, double dt,
+                              const double *dyn) {
+    StretchArgs<P, Tab> a{step_args<P, Tab>(ctx, p, st.t0[0], dt), st};
+    a.a.dyn = dyn;
+    Timer t(ctx, MC_K_STEP, st.n);
+    const int64_t per = 64 / lanes, n = st.n_slots[st.n - 1];
+    const unsigned nb = (unsigned)((n + per - 1) / per);
+    switch (lanes) {
+    case 1: k_stretch<P, Tab, 1><<<nb, 64, 0, ctx->stream>>>(a); break;
+    case 2: k_stretch<P, Tab, 2><<<nb, 64, 0, ctx->stream>>>(a); break;
+    case 4: k_stretch<P, Tab, 4><<<nb, 64, 0, ctx->stream>>>(a); break;
+    case 8: k_stretch<P, Tab, 8><<<nb, 64, 0, ctx->stream>>>(a); break;
+    default: k_stretch<P, Tab, 16><<<nb, 64, 0, ctx->stream>>>(a); break;
+    }
+    LAUNCHCHK();
+    return MC_OK;
+}
+
+static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, double dt, const double *dyn = nullptr) {
+    if (!ctx->fp32()) return launch_stretch<P64, double4>(ctx, ctx->p64, lanes, st, dt, dyn);
+    if (ctx->bf16()) return launch_stretch<P32, bf16x4>(ctx, ctx->p32, lanes, st, dt, dyn);
+    return launch_stretch<P32, float4>(ctx, ctx->p32, lanes, st, dt, dyn);
+}
+
+// Entry j of a stretch: a step of length dt from t0 over n_slots slots.
+static void stretch_step(const mc_ctx *ctx, StretchSteps &st, int j, double t0, double dt, int64_t n_slots) {
+    double c[3];
+    rf_stages_at(ctx->op, t0, dt, c);
+    st.t0[j] = t0;
+    st.c0[j] = c[0];
+    st.ch[j] = c[1];
+    st.c1[j] = c[2];
+    st.n_slots[j] = n_slots;
+}
+
+// One step (dyn: its record on the device, of an adaptive run).
 static int32_t step_once(mc_ctx *ctx, double t0, double dt, const double *dyn = nullptr) {
+    const int lanes = stretch_lanes(ctx, ctx->n_slots, 1);
+    if (lanes > 0) {
+        StretchSteps st;
+        st.n = 1;
+        stretch_step(ctx, st, 0, t0, dt, ctx->n_slots);
+        return step_stretch(ctx, lanes, st, dt, dyn);
+    }
     if (!ctx->fp32()) return launch_step<P64, double4>(ctx, ctx->p64, t0, dt, dyn);
     if (ctx->bf16()) return launch_step<P32, bf16x4>(ctx, ctx->p32, t0, dt, dyn);
     return launch_step<P32, float4>(ctx, ctx->p32, t0, dt, dyn);
+}
+
+// A source's emission over a stretch of steps.
+template <class P, class Tab>
+static int32_t emit_stretch_t(mc_ctx *ctx, int si, const EmitSteps &em, PackPtrs<typename P::T> p) {
+    const int64_t total = em.first[em.n];
+    int64_t emitting = 0;
+    for (int j = 0; j < em.n; ++j) emitting += em.first[j + 1] > em.first[j];
+    const EmitArgs<P, Tab> a = emit_args<P, Tab>(ctx, si, total, p);
+    Timer t(ctx, MC_K_EMIT, emitting);
+    k_emit_stretch<P, Tab><<<grid_for(total), kBlock, 0, ctx->stream>>>(a, em);
+    LAUNCHCHK();
+    return MC_OK;
 }
 
 // Eq. 1 limits over the active packs at t0: returns the smallest per-pack
@@ -986,6 +1095,11 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
                                                                  tmp + 2 * nn, tmp + 3 * nn, nn, 1, 1, 1, 1);
     LAUNCHCHK();
     if (!ctx->bf16()) std::fill(ctx->gsc, ctx->gsc + 4, 1.0f);
+    ctx->gas_n_max = ctx->gas_t_max = 0.0;
+    for (int64_t k = 0; k < nn; ++k) {
+        if (t->gas_t[k] > 0.0) ctx->gas_n_max = std::max(ctx->gas_n_max, t->gas_p[k] / (kB * t->gas_t[k]));
+        ctx->gas_t_max = std::max(ctx->gas_t_max, t->gas_t[k]);
+    }
     if (t->mask) HIPCHK(hipMemcpyAsync(ctx->mask, t->mask, nn, hipMemcpyHostToDevice, ctx->stream));
     else HIPCHK(hipMemsetAsync(ctx->mask, 0, nn, ctx->stream));
     k_sine_table<<<grid_for(2 * (g->nz - 1)), kBlock, 0, ctx->stream>>>(ctx->sine, g->nz);
@@ -1220,6 +1334,69 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     return MC_OK;
 }
 
+// The fixed steps from this one on that one launch can take: as many as end
+// before the next space-charge update, sort or snapshot, each source's packs
+// emitted at their steps' starts.  *done receives the steps taken; none where
+// the step kernel is the better one, or where the next step's emission does
+// not fit (the single step then reports it).
+static int32_t fixed_stretch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
+    *done = 0;
+    const mc_operating &op = ctx->op;
+    int64_t k = std::min<int64_t>(max_steps, kStretchMax);
+    const auto until = [&](int32_t every) {
+        if (every > 0) k = std::min<int64_t>(k, every - ctx->step % every);
+    };
+    if (op.sc_on) until(op.sc_every);
+    until(op.sort_every);
+    if (op.sample_stride > 0) until(op.sample_every);
+    // the sources' packs per step, on copies until the steps are settled
+    const size_t ns = ctx->srcs.size();
+    std::vector<Src> srcs = ctx->srcs, next = srcs;
+    std::vector<EmitSteps> em(ns);
+    for (EmitSteps &e : em) e.first[0] = 0;
+    StretchSteps st;
+    int64_t n = ctx->n_slots;
+    int32_t j = 0;
+    for (; j < k; ++j) {
+        int64_t at = n;
+        for (size_t si = 0; si < ns; ++si) {
+            const int64_t c = std::max<int64_t>(0, due(next[si], ctx->step + j));
+            em[si].slot0[j] = at;
+            em[si].first[j + 1] = em[si].first[j] + c;
+            next[si].emitted += c;
+            at += c;
+        }
+        if (at > ctx->cap) break;
+        n = at;
+        srcs = next;
+        stretch_step(ctx, st, j, (double)(ctx->step + j) * op.dt, op.dt, n);
+    }
+    const int lanes = stretch_lanes(ctx, n, j);
+    if (j == 0 || lanes == 0) return MC_OK;
+    st.n = j;
+    for (size_t si = 0; si < ns; ++si) {
+        em[si].n = j;
+        const int64_t total = em[si].first[j];
+        if (total == 0) continue;
+        int32_t rc;
+        if (!ctx->fp32()) rc = emit_stretch_t<P64, double4>(ctx, (int)si, em[si], ctx->p64);
+        else if (ctx->bf16()) rc = emit_stretch_t<P32, bf16x4>(ctx, (int)si, em[si], ctx->p32);
+        else rc = emit_stretch_t<P32, float4>(ctx, (int)si, em[si], ctx->p32);
+        if (rc) return rc;
+        ctx->emitted_n += total;
+        ctx->emitted_w += total * srcs[si].w_fx;
+    }
+    ctx->srcs = srcs;
+    ctx->n_slots = n;
+    const int32_t rc = step_stretch(ctx, lanes, st, op.dt);
+    if (rc) return rc;
+    ctx->last_dt = op.dt;
+    ctx->step += j;
+    ctx->t = (double)ctx->step * op.dt;
+    *done = j;
+    return MC_OK;
+}
+
 int32_t mc_step(mc_ctx *ctx, int64_t n_steps) {
     if (!ctx) return MC_EINVAL;
     if (!ctx->has_fields || !ctx->has_op) return fail(ctx, MC_ESTATE, "fields and operating point required");
@@ -1255,6 +1432,13 @@ int32_t mc_step(mc_ctx *ctx, int64_t n_steps) {
         } else if (ctx->op.sc_on && ctx->step % ctx->op.sc_every == 0) {
             rc = pic_update(ctx);
             if (rc) return rc;
+        }
+        if (!ctx->op.adaptive) {
+            int64_t done = 0;
+            rc = fixed_stretch(ctx, n_steps - it, &done);
+            if (rc) return rc;
+            it += done;
+            if (done > 0) continue;
         }
         for (size_t si = 0; si < ctx->srcs.size(); ++si) {
             rc = emit(ctx, (int)si, due(ctx->srcs[si], ctx->step));
