@@ -199,8 +199,7 @@ typedef struct mc_source {
  * only the FP64 sums over the active population (sum_w_*_active) may change
  * in their last bits, being reduced in slot order.  Sorting groups packs of
  * like collision rate and place, for the step's wavefronts, the field
- * gathers and the deposit (which then adds straight into the grid instead of
- * grid copies).  0 = never; needs pack_capacity <= 2^28 and at most 2^32 - 2
+ * gathers and the deposit.  0 = never; needs pack_capacity <= 2^28 and at most 2^32 - 2
  * (species x nodes) keys (MC_EINVAL from mc_step otherwise).  The serving
  * runtime ignores it. */
 typedef struct mc_operating {
@@ -453,23 +452,16 @@ typedef struct mc_cic_packs {
  * to the grid).  q_out: device int64 array of grid->nz * grid->nr, row-major
  * [nz][nr], overwritten with the deposited charge (2^-32 e); the result does
  * not depend on the order of the packs.  Enqueued on `stream` (a
- * hipStream_t; NULL = the default stream); the call allocates its scratch
- * (copies of the grid for the blocks' flushes) with hipMalloc, waits for
- * the stream and frees it.  Errors: MC_EINVAL (NULL pointers, grid < 3 x 3
- * or non-positive spacing, n < 0), MC_ENOMEM, MC_EDEVICE. */
+ * hipStream_t; NULL = the default stream); the call waits for the stream.
+ * Errors: MC_EINVAL (NULL pointers, grid < 3 x 3 or non-positive spacing,
+ * n < 0), MC_EDEVICE. */
 int32_t mc_deposit_cic(const mc_cic_packs *packs, const mc_grid *grid, int64_t *q_out, void *stream);
 
-/* The deposit of mc_deposit_cic for callers that cannot allocate device
- * memory -- code being recorded into a HIP graph, tight serving loops,
- * harnesses that forbid hipMalloc: no allocation and no host
- * synchronisation (asynchronous on `stream`).  Its scratch is a fixed
- * library-owned device array of 8 MiB + 16 B per GPU, held until the
- * process ends, so the grid may hold at most 1 048 576 nodes (MC_EINVAL
- * beyond; 16 grid copies up to 65 536 nodes, fewer above).  Every call on a
- * GPU uses that GPU's one array and leaves it cleared for the next:
- * concurrent calls on one GPU (overlapping on different streams) race and
- * must be serialised by the caller.  Results are bit-identical to
- * mc_deposit_cic.  Errors: MC_EINVAL, MC_EDEVICE. */
+/* The deposit of mc_deposit_cic for callers that cannot wait -- code being
+ * recorded into a HIP graph, tight serving loops: no allocation, no scratch
+ * memory and no host synchronisation (asynchronous on `stream`).  The grid may
+ * hold at most 1 048 576 nodes (MC_EINVAL beyond).  Results are bit-identical
+ * to mc_deposit_cic.  Errors: MC_EINVAL, MC_EDEVICE. */
 int32_t mc_deposit_cic_noalloc(const mc_cic_packs *packs, const mc_grid *grid, int64_t *q_out, void *stream);
 
 /* ------------------------------------------------------------------------- */

@@ -907,52 +907,48 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_multi(cons
 template <class T>
 struct DepositArgs {
     PackPtrs<T> p;
-    unsigned long long *q;     // the grid (when qrep is null: the blocks' sums go here)
-    unsigned long long *qrep;  // nrep zeroed copies of the grid, or null
-    int32_t *range;            // lowest and highest node written (with qrep)
-    int64_t n_slots, nn;
-    int64_t chunk;             // slots per sub-range (a multiple of the block size; see k_deposit)
+    unsigned long long *q;  // the zeroed grid, which the blocks' sums are added to
+    int64_t n_slots;
+    int64_t chunk;          // slots per block (a multiple of the block size; see k_deposit)
     double inv_dr, inv_dz;
-    int32_t nr, nz, nrep;
+    int32_t nr, nz;
 };
 
 // Block-local aggregation: each block sums its packs' contributions in an
-// LDS hash table (open addressing) keyed by the CIC cell, i.e. the cell's
-// lower-left node: one compare-and-swap per insertion, the four quanta added
-// to the entry's four slots (lower-left, upper-left, lower-right,
-// upper-right), and one device atomic per nonzero slot at the flush.
+// LDS hash table keyed by the CIC cell, i.e. the cell's lower-left node: one
+// compare-and-swap per insertion and the four quanta added to the entry's four
+// values (lower-left, upper-left, lower-right, upper-right).  The flush adds
+// the table up by node and puts one device atomic per node onto the grid:
+// what bounds the deposit of a population in few cells is the chain of
+// atomics that all blocks send to the same addresses, about 50 ns each (one
+// per cell corner and block, four per node, took 64 us at 1e6 packs in 42
+// cells, and 16 copies of the grid, added up by a second kernel, 23 us).
 //
 // Each block takes one contiguous range of `chunk` slots (a multiple of the
 // block size), so that sorted slots give each block a few cells that few
 // other blocks share (when the ranges were dealt out in several pieces per
 // block, the flushes of more blocks met on each cell and the deposit of
-// sorted packs ran at half the speed).  A thread sums the quanta
-// of its consecutive packs while they stay in one cell and inserts the sums
-// when the cell changes; at the end, where the runs of a wavefront's 64
-// lanes all lie in one cell, their sums are added across the wavefront in
-// registers (DPP row shifts and row broadcasts, no LDS traffic) and one
-// lane inserts them.  Once the slots are sorted by cell -- a cell then
-// holds thousands of consecutive packs -- a block makes a handful of
-// insertions; unsorted, about one per pack.  Packs of the source region concentrate
-// in a few cells, so when the slots are not sorted the blocks' flushes meet
-// on the same few hundred addresses: the caller may then give nrep zeroed
-// copies of the grid, block b flushing into copy b mod nrep, and
-// k_deposit_sum adds the copies over the node range the blocks wrote (and
-// clears them for the next update).  Integer sums make the result
-// independent of the order.
-constexpr int kDepHash = 2048;
-// Grid of the deposit: one block of 16 wavefronts per CU, each thread
-// reading two packs per pass with their loads issued together.
+// sorted packs ran at half the speed).  A thread sums the quanta of its
+// consecutive packs while they stay in one cell and inserts the sums when the
+// cell changes; at the end, where the runs of a wavefront's 64 lanes all lie
+// in one cell, their sums are added across the wavefront in registers (DPP
+// row shifts and row broadcasts, no LDS traffic) and one lane inserts them.
+// Once the slots are sorted by cell -- a cell then holds thousands of
+// consecutive packs -- a block makes a handful of insertions; unsorted, about
+// one per pack.  Integer sums make the result independent of the order.
+//
+// Measured at 1e6 packs on the 256x1024 grid (before, with the copies and
+// their sum where the slots were not sorted): unsorted in the source region
+// 29 us (32), FP32 form 30 us (35), over the whole grid 147 us (180, bound by
+// the 4e6 atomics of packs that share no cell); sorted 18.3 us (18.0).  At 3e4
+// unsorted packs 7.1 us (8.0 and 4.8).
+constexpr int kDepHashBits = 11, kDepHash = 1 << kDepHashBits;
+// One block of 16 wavefronts per CU, each thread reading two packs per pass
+// with their loads issued together.  (128 blocks, which halve the chains of
+// the flush, measured 25 us in the source region, 174 us over the whole grid
+// and 31 us in the FP32 form's sorted slots.)
 constexpr int64_t kDepositBlocks = 256;
 constexpr int kDepositThreads = 1024, kDepositUnroll = 2;
-// Copies of the grid for the flush: 16, fewer on grids where 16 copies would
-// pass 64 MiB.
-constexpr int64_t kDepositRepBytes = 64ll << 20;
-constexpr int32_t kDepositMaxCopies = 16;
-inline int32_t deposit_copies(int64_t nn) {
-    const int64_t r = kDepositRepBytes / (8 * nn);
-    return (int32_t)(r >= kDepositMaxCopies ? kDepositMaxCopies : r < 1 ? 1 : r);
-}
 // Launch shape for n slots: blocks, and the slots of each block's range (a
 // multiple of the block size).
 inline void deposit_shape(int64_t n, unsigned *nb, int64_t *chunk) {
@@ -991,19 +987,34 @@ __device__ __forceinline__ void dep_split(double X, double Y, double Z, int64_t 
     k = (int32_t)fj * nr + (int32_t)fi;
 }
 
+// The block's table: open addressing, keyed by cell, probed at most
+// kDepProbes slots on; a cell's four quanta (lower-left, upper-left,
+// lower-right, upper-right node) in four arrays.
+constexpr int kDepProbes = 8;
+
+struct DepTable {
+    int32_t keys[kDepHash];
+    unsigned long long vals[4][kDepHash];
+    int32_t used[kDepHash], n_used;  // the slots taken, in any order
+};
+
+__device__ __forceinline__ uint32_t dep_hash(int32_t k) {
+    return ((uint32_t)k * 2654435761u) >> (32 - kDepHashBits);
+}
+
 // Quanta of cell k into the block's table (or, when its probes find no
-// room, straight into the grid or its copy).
-__device__ __forceinline__ void dep_insert(int32_t *keys, unsigned long long *vals, unsigned long long *grid,
-                                           int32_t k, int32_t nr, int64_t a0, int64_t a1, int64_t b0, int64_t b1) {
-    uint32_t h = ((uint32_t)k * 2654435761u) >> (32 - 11);
-    for (int probe = 0; probe < 8; ++probe) {
-        const int32_t old = atomicCAS(&keys[h], -1, k);
+// room, straight into the grid).
+__device__ __forceinline__ void dep_insert(DepTable &t, unsigned long long *grid, int32_t k, int32_t nr, int64_t a0, int64_t a1,
+                                           int64_t b0, int64_t b1) {
+    uint32_t h = dep_hash(k);
+    for (int probe = 0; probe < kDepProbes; ++probe) {
+        const int32_t old = atomicCAS(&t.keys[h], -1, k);
+        if (old == -1) t.used[atomicAdd(&t.n_used, 1)] = (int32_t)h;
         if (old == -1 || old == k) {
-            unsigned long long *v = vals + 4 * h;
-            if (a0) atomicAdd(&v[0], (unsigned long long)a0);
-            if (a1) atomicAdd(&v[1], (unsigned long long)a1);
-            if (b0) atomicAdd(&v[2], (unsigned long long)b0);
-            if (b1) atomicAdd(&v[3], (unsigned long long)b1);
+            if (a0) atomicAdd(&t.vals[0][h], (unsigned long long)a0);
+            if (a1) atomicAdd(&t.vals[1][h], (unsigned long long)a1);
+            if (b0) atomicAdd(&t.vals[2][h], (unsigned long long)b0);
+            if (b1) atomicAdd(&t.vals[3][h], (unsigned long long)b1);
             return;
         }
         h = (h + 1) & (kDepHash - 1);
@@ -1012,6 +1023,19 @@ __device__ __forceinline__ void dep_insert(int32_t *keys, unsigned long long *va
     if (a1) atom_add(&grid[k + nr], a1);
     if (b0) atom_add(&grid[k + 1], b0);
     if (b1) atom_add(&grid[k + nr + 1], b1);
+}
+
+// Slot of cell k in the finished table, or -1.
+__device__ __forceinline__ int dep_find(const DepTable &t, int32_t k) {
+    if (k < 0) return -1;
+    uint32_t h = dep_hash(k);
+    for (int probe = 0; probe < kDepProbes; ++probe) {
+        const int32_t have = t.keys[h];
+        if (have == k) return (int)h;
+        if (have == -1) return -1;
+        h = (h + 1) & (kDepHash - 1);
+    }
+    return -1;
 }
 
 // 64-bit DPP move of v (row_mask selects the rows that take the moved value;
@@ -1042,21 +1066,15 @@ __device__ __forceinline__ uint64_t wave_total_u64(uint64_t v) {
 template <class P>
 __global__ __launch_bounds__(kDepositThreads) void k_deposit(DepositArgs<typename P::T> a) {
     using T = typename P::T;
-    __shared__ int32_t keys[kDepHash];
-    __shared__ unsigned long long vals[4 * kDepHash];
-    __shared__ int32_t blo, bhi;
+    __shared__ DepTable tab;
     for (int k = threadIdx.x; k < kDepHash; k += blockDim.x) {
-        keys[k] = -1;
-        vals[4 * k] = vals[4 * k + 1] = vals[4 * k + 2] = vals[4 * k + 3] = 0ull;
+        tab.keys[k] = -1;
+        tab.vals[0][k] = tab.vals[1][k] = tab.vals[2][k] = tab.vals[3][k] = 0ull;
     }
-    if (threadIdx.x == 0) {
-        blo = INT32_MAX;
-        bhi = -1;
-    }
+    if (threadIdx.x == 0) tab.n_used = 0;
     __syncthreads();
-    unsigned long long *dst = a.qrep ? a.qrep + (int64_t)(blockIdx.x % (unsigned)a.nrep) * a.nn : a.q;
+    unsigned long long *dst = a.q;
     const int lane = threadIdx.x & 63;
-    int32_t lo = INT32_MAX, hi = -1;
     // the block's range in rows of blockDim.x slots; every wavefront of the
     // block runs the same passes (its lanes stay together for the wavefront
     // sums at the end)
@@ -1106,10 +1124,8 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit(DepositArgs<typenam
             int64_t a0, a1, c0, c1;
             dep_split(X, Y, Z, q[u], a.inv_dr, a.inv_dz, a.nr, a.nz, k, a0, a1, c0, c1);
             if (k < 0) continue;
-            lo = min(lo, k);
-            hi = max(hi, k + a.nr + 1);
             if (k != rk) {
-                if (rk >= 0) dep_insert(keys, vals, dst, rk, a.nr, r0, r1, r2, r3);
+                if (rk >= 0) dep_insert(tab, dst, rk, a.nr, r0, r1, r2, r3);
                 rk = k;
                 r0 = r1 = r2 = r3 = 0;
             }
@@ -1130,80 +1146,38 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit(DepositArgs<typenam
                 const uint64_t s00 = wave_total_u64((uint64_t)r0), s01 = wave_total_u64((uint64_t)r1),
                                s10 = wave_total_u64((uint64_t)r2), s11 = wave_total_u64((uint64_t)r3);
                 if (lane == lead)
-                    dep_insert(keys, vals, dst, kl, a.nr, (int64_t)s00, (int64_t)s01, (int64_t)s10, (int64_t)s11);
+                    dep_insert(tab, dst, kl, a.nr, (int64_t)s00, (int64_t)s01, (int64_t)s10, (int64_t)s11);
             } else if (rk >= 0) {
-                dep_insert(keys, vals, dst, rk, a.nr, r0, r1, r2, r3);
+                dep_insert(tab, dst, rk, a.nr, r0, r1, r2, r3);
             }
         }
     }
-    if (a.range) {
-        // lowest and highest node over the wavefront first: one LDS atomic per
-        // wavefront instead of one per thread on the same two words
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            lo = min(lo, __shfl_xor(lo, o, 64));
-            hi = max(hi, __shfl_xor(hi, o, 64));
-        }
-        if (lane == 0 && hi >= 0) {
-            atomicMin(&blo, lo);
-            atomicMax(&bhi, hi);
-        }
-    }
     __syncthreads();
-    for (int k = threadIdx.x; k < kDepHash; k += blockDim.x)
-        if (keys[k] >= 0) {
-            const int64_t c = keys[k], off[4] = {0, a.nr, 1, a.nr + 1};
+    // The flush: one device atomic per node that the block's cells touch.  A
+    // node belongs to up to four cells; the first of them in the table (in the
+    // order of the cell's corners) adds what all of them hold for it.  The
+    // blocks start at different places, so that those with the same cells do
+    // not meet on one address after the other.
+    const int items = 4 * tab.n_used;
+    const int rot = items ? (int)(blockIdx.x * 521u % (unsigned)items) : 0;
+    for (int i = threadIdx.x; i < items; i += blockDim.x) {
+        const int k = i + rot < items ? i + rot : i + rot - items;
+        const int h = tab.used[k >> 2], j = k & 3;
+        const int32_t up = j & 1, right = j >> 1;  // the corner's place in its cell
+        const int32_t c = tab.keys[h], node = c + right + up * a.nr;
+        unsigned long long sum = tab.vals[j][h];
+        bool first = true;
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-                if (vals[4 * k + j] != 0ull) atomicAdd(&dst[c + off[j]], vals[4 * k + j]);
+        for (int b = 0; b < 4; ++b) {
+            if (b == j) continue;
+            const int o = dep_find(tab, node - ((b >> 1) + (b & 1) * a.nr));
+            if (o < 0) continue;
+            if (b < j) first = false;
+            sum += tab.vals[b][o];
         }
-    if (a.range && threadIdx.x == 0 && bhi >= 0) {
-        atomicMin(&a.range[0], blo);
-        atomicMax(&a.range[1], bhi);
+        if (first && sum != 0ull) atomicAdd(&dst[node], sum);
     }
 }
-
-// The grid from the copies: q[n] = the sum of the copies' values at n for n
-// in the range this deposit wrote (range; the copies are cleared there, after
-// all of the thread's loads have been issued; nrep <= kDepositMaxCopies), 0
-// elsewhere.  Only the nodes in the span of this range and of the previous
-// deposit's (prev) are written -- the grid is zero outside the previous
-// range already -- or every node when prev is null.  Grid-stride; the first
-// thread also resets the range slot `next` for the deposit after this one.
-static __global__ __launch_bounds__(256) void k_deposit_sum(unsigned long long *q, unsigned long long *qrep,
-                                                            int32_t nrep, int64_t nn, const int32_t *range,
-                                                            const int32_t *prev, int32_t *next) {
-    int64_t n0 = 0, n1 = nn - 1;
-    if (prev) {
-        n0 = min((int64_t)range[0], (int64_t)prev[0]);
-        n1 = max((int64_t)range[1], (int64_t)prev[1]);
-        n1 = min(n1, nn - 1);
-    }
-    const int32_t lo = range[0], hi = range[1];
-    for (int64_t n = n0 + (int64_t)blockIdx.x * blockDim.x + threadIdx.x; n <= n1;
-         n += (int64_t)gridDim.x * blockDim.x) {
-        unsigned long long v = 0ull;
-        if (n >= lo && n <= hi) {
-            unsigned long long w[kDepositMaxCopies];
-#pragma unroll
-            for (int32_t c = 0; c < kDepositMaxCopies; ++c) w[c] = c < nrep ? qrep[(int64_t)c * nn + n] : 0ull;
-#pragma unroll
-            for (int32_t c = 0; c < kDepositMaxCopies; ++c) v += w[c];
-#pragma unroll
-            for (int32_t c = 0; c < kDepositMaxCopies; ++c)
-                if (c < nrep) qrep[(int64_t)c * nn + n] = 0ull;
-        }
-        q[n] = v;
-    }
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        next[0] = INT32_MAX;
-        next[1] = -1;
-    }
-}
-
-// Blocks of the sum kernel: enough to cover a 1M-node grid in one sweep of
-// 256-thread blocks, grid-stride beyond.
-constexpr int64_t kDepositSumBlocks = 4096;
 
 // E = -grad(phi) on nodes: central differences, one-sided at the outer
 // edges, E_r = 0 on the axis.  clear (nullable): a charge grid zeroed on

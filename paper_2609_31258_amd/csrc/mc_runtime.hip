@@ -66,14 +66,9 @@ struct mc_ctx {
     float esc[4] = {1, 1, 1, 1}, gsc[4] = {1, 1, 1, 1};
     uint8_t *mask = nullptr, *hit = nullptr;
 
-    unsigned long long *qgrid = nullptr;
-    unsigned long long *qrep = nullptr;  // the deposit's copies of the grid (nrep of them, kept zeroed)
-    // with sorted slots the deposit flushes straight into a zeroed grid: the
-    // other of two grids, cleared by the field bake of the update after it
-    unsigned long long *qnext = nullptr;
-    int32_t nrep = 1, dep_slot = 0;
-    int32_t *dep_range = nullptr;        // three (lowest, highest) node slots, rotating by update
-    bool dep_full = true;                // the next sum writes every node (the grid may hold charge anywhere)
+    // the charge grid, and the zeroed grid the next deposit adds into: the two
+    // swap, and the field bake of an update clears the one that it retired
+    unsigned long long *qgrid = nullptr, *qnext = nullptr;
     double *sine = nullptr, *tcp = nullptr, *tinv = nullptr;
     void *bh = nullptr;
     Bluestein blu;
@@ -311,7 +306,7 @@ static int32_t fold(mc_ctx *ctx) {
 }
 
 // The field of the new space-charge potential and the step's table from it,
-// in one kernel (clear: the other charge grid of a direct deposit, or null).
+// in one kernel (clear: the charge grid that the next deposit adds into).
 template <class Tab>
 static int32_t bake_fold_table(mc_ctx *ctx, unsigned long long *clear) {
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
@@ -726,33 +721,16 @@ static int32_t sort_if_due(mc_ctx *ctx) {
     return ctx->fp32() ? sort_packs_t(ctx, ctx->p32, ctx->p32b) : sort_packs_t(ctx, ctx->p64, ctx->p64b);
 }
 
-// Grid buffer the deposit adds into directly (sorted slots): allocated and
-// zeroed once, and from then on cleared by the field bake of the update
-// after the deposit that used it.
-static int32_t direct_grid(mc_ctx *ctx) {
-    if (ctx->qnext) return MC_OK;
-    const int64_t nn = (int64_t)ctx->nr * ctx->nz;
-    int32_t rc = dalloc_t(ctx, &ctx->qnext, nn);
-    if (rc) return rc;
-    HIPCHK(hipMemsetAsync(ctx->qnext, 0, nn * sizeof(unsigned long long), ctx->stream));
-    return MC_OK;
-}
-
 template <class P, class D>
 static int32_t pic_update_t(mc_ctx *ctx, PackPtrs<typename P::T> p) {
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
-    // sorted slots: one deposit kernel adding straight into the zeroed grid
-    const bool direct = ctx->op.sort_every > 0;
-    if (direct) {
-        int32_t rc = direct_grid(ctx);
-        if (rc) return rc;
+    {
         Timer t(ctx, MC_K_DEPOSIT);
         if (ctx->n_slots > 0) {
             DepositArgs<typename P::T> a{};
             a.p = p;
             a.q = ctx->qnext;
             a.n_slots = ctx->n_slots;
-            a.nn = nn;
             a.inv_dr = ctx->inv_dr;
             a.inv_dz = ctx->inv_dz;
             a.nr = ctx->nr;
@@ -763,42 +741,13 @@ static int32_t pic_update_t(mc_ctx *ctx, PackPtrs<typename P::T> p) {
             LAUNCHCHK();
         }
         std::swap(ctx->qgrid, ctx->qnext);  // qnext now holds the previous deposit: cleared below
-        ctx->dep_full = true;               // a later sum over copies must write every node
-    } else {
-        Timer t(ctx, MC_K_DEPOSIT);
-        // slots: this deposit's range, the previous deposit's, and the next one's
-        int32_t *range = ctx->dep_range + 2 * ctx->dep_slot, *prev = ctx->dep_range + 2 * ((ctx->dep_slot + 2) % 3),
-                *next = ctx->dep_range + 2 * ((ctx->dep_slot + 1) % 3);
-        if (ctx->n_slots > 0) {
-            DepositArgs<typename P::T> a{};
-            a.p = p;
-            a.q = ctx->qgrid;
-            a.qrep = ctx->qrep;
-            a.range = range;
-            a.n_slots = ctx->n_slots;
-            a.nn = nn;
-            a.inv_dr = ctx->inv_dr;
-            a.inv_dz = ctx->inv_dz;
-            a.nr = ctx->nr;
-            a.nz = ctx->nz;
-            a.nrep = ctx->nrep;
-            unsigned nb;
-            deposit_shape(ctx->n_slots, &nb, &a.chunk);
-            k_deposit<P><<<nb, kDepositThreads, 0, ctx->stream>>>(a);
-            LAUNCHCHK();
-        }
-        // the grid from the copies: the nodes of this deposit's range and the
-        // previous one's are written, the rest of the grid is zero already
-        const unsigned sb = (unsigned)std::min<int64_t>(grid_for(nn), kDepositSumBlocks);
-        k_deposit_sum<<<sb, kBlock, 0, ctx->stream>>>(ctx->qgrid, ctx->qrep, ctx->nrep, nn, range,
-                                                      ctx->dep_full ? nullptr : prev, next);
-        LAUNCHCHK();
-        ctx->dep_slot = (ctx->dep_slot + 1) % 3;
-        ctx->dep_full = false;
     }
     if (ctx->op.sc_mask && !ctx->mcap.ready) {
         const int32_t rc = mask_setup(ctx);
-        if (rc) return rc;
+        if (rc) {
+            k_zero_u64<<<grid_for(nn), kBlock, 0, ctx->stream>>>(ctx->qnext, nn);
+            return rc;
+        }
     }
     {
         Timer t(ctx, MC_K_POISSON);
@@ -808,7 +757,7 @@ static int32_t pic_update_t(mc_ctx *ctx, PackPtrs<typename P::T> p) {
     }
     {
         Timer t(ctx, MC_K_FIELD);
-        const int32_t rc = bake_fold(ctx, direct ? ctx->qnext : nullptr);
+        const int32_t rc = bake_fold(ctx, ctx->qnext);
         if (rc) return rc;
     }
     return MC_OK;
@@ -1041,9 +990,7 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     if (!rc) rc = dalloc_t(ctx, &ctx->mask, nn);
     if (!rc) rc = dalloc_t(ctx, &ctx->hit, nn);
     if (!rc) rc = dalloc_t(ctx, &ctx->qgrid, nn);
-    ctx->nrep = deposit_copies(nn);
-    if (!rc) rc = dalloc_t(ctx, &ctx->qrep, (size_t)ctx->nrep * nn);
-    if (!rc) rc = dalloc_t(ctx, &ctx->dep_range, 6);
+    if (!rc) rc = dalloc_t(ctx, &ctx->qnext, nn);
     if (!rc) rc = dalloc_t(ctx, &ctx->sine, 2 * (int64_t)(g->nz - 1));
     if (!rc) rc = dalloc_t(ctx, &ctx->tcp, (int64_t)nu * m);
     if (!rc) rc = dalloc_t(ctx, &ctx->tinv, (int64_t)nu * m);
@@ -1059,13 +1006,7 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     HIPCHK(hipMemsetAsync(ctx->e_off, 0, nn * sizeof(double2), ctx->stream));
     HIPCHK(hipMemsetAsync(ctx->e_rf, 0, nn * sizeof(double2), ctx->stream));
     HIPCHK(hipMemsetAsync(ctx->qgrid, 0, nn * sizeof(unsigned long long), ctx->stream));
-    HIPCHK(hipMemsetAsync(ctx->qrep, 0, (size_t)ctx->nrep * nn * sizeof(unsigned long long), ctx->stream));
-    {
-        static const int32_t empty[6] = {INT32_MAX, -1, INT32_MAX, -1, INT32_MAX, -1};
-        HIPCHK(hipMemcpyAsync(ctx->dep_range, empty, sizeof(empty), hipMemcpyHostToDevice, ctx->stream));
-        ctx->dep_slot = 0;
-        ctx->dep_full = true;
-    }
+    HIPCHK(hipMemsetAsync(ctx->qnext, 0, nn * sizeof(unsigned long long), ctx->stream));
     // bake E = -grad(phi) for the three potentials
     const double *phis[3] = {t->phi_dc, t->phi_off, t->phi_rf};
     double2 *outs[3] = {ctx->e_dc, ctx->e_off, ctx->e_rf};
@@ -1738,7 +1679,6 @@ int32_t mc_load_state(mc_ctx *ctx, const char *path) {
     if (!ctx || !path) return MC_EINVAL;
     if (!ctx->has_fields || !ctx->has_op) return fail(ctx, MC_ESTATE, "fields and operating point required");
     HIPCHK(hipSetDevice(ctx->opt.device));
-    ctx->dep_full = true;  // the restored charge grid may hold charge anywhere
     ctx->dt_rec_valid = false;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     FILE *f = std::fopen(path, "rb");

@@ -318,6 +318,7 @@ static int32_t admit_query(mc_server *S, Query &Q) {
     if (Q.q.op.sc_on) {
         k_zero_u64<<<blocks_for(2 * nn), kBlk, 0, S->stream>>>((unsigned long long *)Q.e_sc, 2 * nn);
         k_zero_u64<<<blocks_for(nn), kBlk, 0, S->stream>>>((unsigned long long *)Q.phi, nn);
+        k_zero_u64<<<blocks_for(nn), kBlk, 0, S->stream>>>(Q.qgrid, nn);
         if (Q.rhs) k_zero_u64<<<blocks_for(nn), kBlk, 0, S->stream>>>((unsigned long long *)Q.rhs, nn);
         SCHK(hipGetLastError());
     }
@@ -332,8 +333,7 @@ static int32_t admit_query(mc_server *S, Query &Q) {
 template <class P, class Tab, class D>
 static int32_t pic_query(mc_server *S, Query &Q, PackPtrs<typename P::T> p) {
     const int64_t nn = (int64_t)S->nr * S->nz;
-    k_zero_u64<<<blocks_for(nn), kBlk, 0, S->stream>>>(Q.qgrid, nn);
-    if (Q.n_slots > 0) {
+    if (Q.n_slots > 0) {  // into the grid that admission or the last update zeroed
         DepositArgs<typename P::T> a{};
         a.p = p;
         a.q = Q.qgrid;
@@ -381,8 +381,9 @@ static int32_t pic_query(mc_server *S, Query &Q, PackPtrs<typename P::T> p) {
         }
         SCHK(mask_correct<D>(S->pg, S->cap, bh, Q.rhs, Q.phi, S->stream));
     }
-    // the field of the new potential folded into the query's table in one pass
-    k_bake_fold<Tab><<<blocks_for(nn), kBlk, 0, S->stream>>>(Q.phi, Q.e_sc, S->nr, S->nz, S->dr, S->dz, nullptr,
+    // the field of the new potential folded into the query's table in one
+    // pass, which clears the charge for the next update
+    k_bake_fold<Tab><<<blocks_for(nn), kBlk, 0, S->stream>>>(Q.phi, Q.e_sc, S->nr, S->nz, S->dr, S->dz, Q.qgrid,
                                                              static_cast<Tab *>(Q.etab), S->e_dc, S->e_off, S->e_rf,
                                                              Q.q.op.v_off, S->esc[0], S->esc[1], S->esc[2], S->esc[3]);
     SCHK(hipGetLastError());
