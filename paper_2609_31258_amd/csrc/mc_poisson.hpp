@@ -9,10 +9,12 @@
 //                    chirp z-transform: power-of-two FFTs held in LDS
 //   k_dst_rows, k_idst_rows  the same transforms as direct sums (used when
 //                    the FFT length does not fit in a workgroup's LDS)
-//   k_pcr            per-mode tridiagonal solve in r by parallel cyclic
-//                    reduction, one wavefront per mode, FP64 always
+//   k_tri_table, k_tri  per-mode tridiagonal solve in r by scans, one
+//                    wavefront per mode (FP64 form)
+//   k_pcr            the same solve by parallel cyclic reduction, one
+//                    wavefront per mode, FP64 arithmetic (FP32 form)
 //   k_thomas_coef, k_thomas  the same solve by Thomas sweeps (one thread per
-//                    mode), for grids taller than k_pcr takes
+//                    mode), for grids taller than these take
 //   k_mask_*         the metal-mask Dirichlet condition by a capacitance-
 //                    matrix correction (induced charges on the mask nodes)
 //
@@ -28,6 +30,17 @@
 #include <vector>
 
 namespace mc {
+
+// The n places of a launch dealt out so that neighbours meet in one L2: the
+// blocks go round the chip's eight dies (XCDs) in turn, so block b takes place
+// (b mod 8) ceil(n/8) + b / 8.  Launched with xcd_blocks(n) blocks; the excess
+// ones get a place >= n.  (The transforms read and write the columns of a
+// row-major grid, 8 bytes of a line each: 15.6 -> 13.1 us on 256x1024 and 30
+// -> 24 us on 512x2048 where neighbouring rows share an L2.)
+inline unsigned xcd_blocks(int32_t n) { return 8u * (unsigned)((n + 7) / 8); }
+__device__ __forceinline__ int32_t xcd_place(int32_t n) {
+    return (int32_t)(blockIdx.x & 7) * ((n + 7) / 8) + (int32_t)(blockIdx.x >> 3);
+}
 
 static __global__ __launch_bounds__(256) void k_sine_table(double *s, int32_t nz) {
     const int32_t n2 = 2 * (nz - 1);
@@ -189,7 +202,13 @@ __global__ __launch_bounds__(256) void k_thomas(D *bh, const double *cp, const d
 // -4/dr^2 + lambda_k, 4/dr^2; x = 0 beyond the last row): strictly
 // diagonally dominant since lambda_k < 0, where cyclic reduction is stable.
 // 1022 modes of 255 rows are 1022 wavefronts across the chip instead of
-// 1022 threads stepping through 255 dependent rows.
+// 1022 threads stepping through 255 dependent rows.  The rows of the block's
+// W modes are read and written together, W neighbours at a time.
+//
+// The FP32 form keeps this solve beside the faster scans (below): it rounds
+// the modes to FP32, and its transforms carry the last bit of a mode into the
+// seventh digit of the potential, so a run of it (from a saved state, or with
+// the capacitance matrix of its mask) stays what it was bit for bit.
 template <class D, int R, int W>
 __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, double dr, double dz) {
     constexpr int N = 64 * R;
@@ -197,7 +216,15 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
     __shared__ double s_abcd[2][4][W][N];
     const int32_t m = nz - 2, nu = nr - 1;
     const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    const int32_t k = blockIdx.x * W + w + 1;  // mode 1..m (uniform per wavefront)
+    const int32_t k0 = xcd_place((m + W - 1) / W) * W;  // first mode (less one) of the block
+    if (k0 >= m) return;
+    const int32_t k = k0 + w + 1;  // mode 1..m (uniform per wavefront)
+    const int wi = threadIdx.x % W, i0 = threadIdx.x / W;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int32_t i = i0 + 64 * q;
+        s_abcd[0][3][wi][i] = i < nu && k0 + wi < m ? (double)bh[(int64_t)i * m + k0 + wi] : 0.0;
+    }
     const bool live = k <= m;
     double lam = 0.0;
     if (live) {
@@ -207,7 +234,7 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
 #pragma unroll
     for (int q = 0; q < R; ++q) {
         const int32_t i = lane + 64 * q;
-        double a = 0.0, b = 1.0, c = 0.0, d = 0.0;
+        double a = 0.0, b = 1.0, c = 0.0;
         if (live && i < nu) {
             if (i == 0) {
                 b = -4.0 / (dr * dr) + lam;
@@ -219,12 +246,10 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
                 b = -(a + c) + lam;
             }
             if (i == nu - 1) c = 0.0;  // Phi = 0 at r = R
-            d = (double)bh[(int64_t)i * m + (k - 1)];
         }
         s_abcd[0][0][w][i] = a;
         s_abcd[0][1][w][i] = b;
         s_abcd[0][2][w][i] = c;
-        s_abcd[0][3][w][i] = d;
     }
     __syncthreads();
     int src = 0;
@@ -250,8 +275,160 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        const int32_t i = lane + 64 * q;
-        if (live && i < nu) bh[(int64_t)i * m + (k - 1)] = (D)(s_abcd[src][3][w][i] / s_abcd[src][1][w][i]);
+        const int32_t i = i0 + 64 * q;
+        if (i < nu && k0 + wi < m) bh[(int64_t)i * m + k0 + wi] = (D)(s_abcd[src][3][wi][i] / s_abcd[src][1][wi][i]);
+    }
+}
+
+// The same systems by scans (FP64 form, up to 1024 rows): one wavefront per mode, R
+// consecutive rows per lane (64 R >= nu).  The forward sweep is the linear
+// recurrence d_i = f_i d_{i-1} + inv_i b_i with f_i = -lo_i inv_i, the back
+// substitution x_i = d_i - cp_i x_{i+1} with cp_i = up_i inv_i; a lane runs
+// each over its own rows from zero, a scan over the lanes (DPP moves) gives
+// what comes in from the rows before, and the products of the lane's
+// coefficients carry it through.  Strictly diagonally dominant rows (lambda_k
+// < 0) keep |f|, |cp| < 1.  Only inv depends on the mode: it is read from a
+// table made once per grid (k_tri_table), lo and up follow from the row.
+// FP64 throughout.  What bounds it is the trip to memory and back: the rows
+// of W modes are read together, W neighbours at a time, and turned in LDS.
+// 255 rows of 1022 modes: 15.3 us by cyclic reduction (two divisions per row
+// and level), 4.9 us so; 511 rows of 2046 modes 62 -> 8.3 us; 1023 rows of
+// 2046 modes, the whole solve 371 -> 146 us.
+constexpr int kTriMaxRows = 1024;
+inline int tri_rows_per_lane(int32_t nu) { return nu <= 128 ? 2 : nu <= 256 ? 4 : nu <= 512 ? 8 : 16; }
+
+// inv_i of every mode, [mode][np] with np = 64 R rows (zero beyond nu), and
+// after them lo_i and up_i, [np] each, which no mode changes.
+static __global__ __launch_bounds__(64) void k_tri_table(double *inv, int32_t nr, int32_t nz, double dr, double dz,
+                                                         int32_t np) {
+    const int32_t m = nz - 2, nu = nr - 1;
+    const int32_t k = 1 + blockIdx.x * blockDim.x + threadIdx.x;
+    if (k > m) return;
+    const double sk = sin(kPi * (double)k / (2.0 * (double)(nz - 1)));
+    const double lam = -(4.0 / (dz * dz)) * sk * sk;
+    double *row = inv + (int64_t)(k - 1) * np, *ends = inv + (int64_t)m * np;
+    double cprev = 0.0;
+    for (int32_t i = 0; i < np; ++i) {
+        double lo = 0.0, up = 0.0, v = 0.0;
+        if (i < nu) {
+            up = 4.0 / (dr * dr);
+            if (i > 0) {
+                const double ri = (double)i * dr;
+                lo = (ri - 0.5 * dr) / (ri * dr * dr);
+                up = (ri + 0.5 * dr) / (ri * dr * dr);
+            }
+            const double di = -(lo + up) + lam;
+            v = 1.0 / (di - lo * cprev);
+            cprev = up * v;
+        }
+        row[i] = v;
+        if (k == 1) {
+            ends[i] = lo;
+            ends[np + i] = up;
+        }
+    }
+}
+
+// 64-bit DPP move; lanes without a source keep `old`.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ double dpp_f64(double old, double v) {
+    const uint64_t o = (uint64_t)__double_as_longlong(old), x = (uint64_t)__double_as_longlong(v);
+    const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)o, (int)(uint32_t)x, kCtrl, kRowMask, 0xf,
+                                                              false);
+    const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(o >> 32), (int)(uint32_t)(x >> 32), kCtrl,
+                                                              kRowMask, 0xf, false);
+    return __longlong_as_double((long long)(((uint64_t)hi << 32) | lo));
+}
+
+// Inclusive scan over the lanes of the maps y -> f y + d (lower lanes first):
+// d becomes the value after this lane's map, from zero before lane 0.
+template <int kCtrl, int kRowMask>
+__device__ __forceinline__ void scan_step(double &f, double &d) {
+    const double fp = dpp_f64<kCtrl, kRowMask>(1.0, f), dp = dpp_f64<kCtrl, kRowMask>(0.0, d);
+    d = __builtin_fma(f, dp, d);
+    f *= fp;
+}
+__device__ __forceinline__ void scan_maps(double f, double &d) {
+    scan_step<0x111, 0xf>(f, d);  // row_shr:1
+    scan_step<0x112, 0xf>(f, d);  // row_shr:2
+    scan_step<0x114, 0xf>(f, d);  // row_shr:4
+    scan_step<0x118, 0xf>(f, d);  // row_shr:8
+    scan_step<0x142, 0xa>(f, d);  // row_bcast:15 into rows 1 and 3
+    scan_step<0x143, 0xc>(f, d);  // row_bcast:31 into rows 2 and 3
+}
+
+template <class D, int R, int W>
+__global__ __launch_bounds__(64 * W) void k_tri(D *bh, const double *inv, int32_t nr, int32_t nz) {
+    constexpr int N = 64 * R;
+    __shared__ double rows[W][N + 2];  // (two spare: the modes' rows start on different banks)
+    const int32_t m = nz - 2, nu = nr - 1;
+    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    // first mode (less one) of the block; beyond the last with the grid's excess blocks
+    const int32_t k0 = xcd_place((m + W - 1) / W) * W;
+    if (k0 >= m) return;
+    const int32_t k = k0 + w;
+    double v[R], lo[R], up[R];
+    {
+        // the lane's rows of the tables, read while the modes' rows come in
+        const double *t = inv + (int64_t)(k < m ? k : m - 1) * N + lane * R, *e = inv + (int64_t)m * N + lane * R;
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            v[q] = t[q];
+            lo[q] = e[q];
+            up[q] = e[N + q];
+        }
+    }
+    {
+        const int wi = threadIdx.x % W, i0 = threadIdx.x / W;
+        D b[R];
+#pragma unroll
+        for (int q = 0; q < R; ++q) {
+            const int32_t i = i0 + 64 * q;
+            b[q] = i < nu && k0 + wi < m ? bh[(int64_t)i * m + k0 + wi] : (D)0;
+        }
+#pragma unroll
+        for (int q = 0; q < R; ++q) rows[wi][i0 + 64 * q] = (double)b[q];
+    }
+    __syncthreads();
+    double x[R], p[R];
+    double f = 1.0, d = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const double fi = -lo[q] * v[q];
+        d = __builtin_fma(fi, d, v[q] * rows[w][lane * R + q]);
+        f *= fi;
+        x[q] = d;
+        p[q] = f;
+    }
+    scan_maps(f, d);
+    double in = __shfl_up(d, 1, 64);
+    if (lane == 0) in = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) x[q] = __builtin_fma(p[q], in, x[q]);
+    f = 1.0;
+    d = 0.0;
+#pragma unroll
+    for (int q = R - 1; q >= 0; --q) {
+        const double ci = -up[q] * v[q];
+        d = __builtin_fma(ci, d, x[q]);
+        f *= ci;
+        x[q] = d;
+        p[q] = f;
+    }
+    // the scan from the last lane down: lanes turned round
+    f = __shfl(f, 63 - lane, 64);
+    d = __shfl(d, 63 - lane, 64);
+    scan_maps(f, d);
+    in = __shfl(d, 62 - lane, 64);  // the value after lane + 1, which sits in lane 62 - lane
+    if (lane == 63) in = 0.0;
+#pragma unroll
+    for (int q = 0; q < R; ++q) rows[w][lane * R + q] = __builtin_fma(p[q], in, x[q]);
+    __syncthreads();
+    const int wi = threadIdx.x % W, i0 = threadIdx.x / W;
+#pragma unroll
+    for (int q = 0; q < R; ++q) {
+        const int32_t i = i0 + 64 * q;
+        if (i < nu && k0 + wi < m) bh[(int64_t)i * m + k0 + wi] = (D)rows[wi][i];
     }
 }
 
@@ -457,23 +634,157 @@ __global__ __launch_bounds__(1024) void k_bluestein_filter(Cx<D> *fb, const Cx<D
     for (int32_t n = threadIdx.x; n < L; n += blockDim.x) fb[n] = a[cslot(n)];
 }
 
+// The twiddle factors of G consecutive stages for one group, in the order of
+// the forward stages (the inverse stages of the same group take them from the
+// back).
+template <class D, int G>
+struct Twiddles {
+    Cx<D> w[(1 << G) - 1];
+
+    __device__ __forceinline__ void load(int32_t o, int32_t sub, int32_t len, int32_t L, const Cx<D> *tw) {
+        int n = 0;
+#pragma unroll
+        for (int t = 0; t < G; ++t)
+#pragma unroll
+            for (int j = 0; j < (1 << (G - 1 - t)); ++j) w[n++] = tw[(o + j * sub) * (L / (len >> t))];
+    }
+    // first factor of the stage whose partner distance within the group is h
+    static constexpr int at(int h) { return (1 << G) - 2 * h; }
+
+    __device__ __forceinline__ void forward(Cx<D> (&v)[1 << G]) const {
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+            const int h = 1 << (G - 1 - t);
+#pragma unroll
+            for (int j = 0; j < (1 << G); ++j) {
+                if (j & h) continue;
+                const Cx<D> u = v[j], x = v[j + h];
+                v[j] = Cx<D>{u.re + x.re, u.im + x.im};
+                v[j + h] = cmul(Cx<D>{u.re - x.re, u.im - x.im}, w[at(h) + (j & (h - 1))]);
+            }
+        }
+    }
+    __device__ __forceinline__ void inverse(Cx<D> (&v)[1 << G]) const {
+#pragma unroll
+        for (int t = 0; t < G; ++t) {
+            const int h = 1 << t;
+#pragma unroll
+            for (int j = 0; j < (1 << G); ++j) {
+                if (j & h) continue;
+                const Cx<D> x = w[at(h) + (j & (h - 1))];
+                const Cx<D> tt = cmul(v[j + h], Cx<D>{x.re, -x.im});
+                const Cx<D> u = v[j];
+                v[j] = Cx<D>{u.re + tt.re, u.im + tt.im};
+                v[j + h] = Cx<D>{u.re - tt.re, u.im - tt.im};
+            }
+        }
+    }
+};
+
+// The convolution of a row in LDS (forward FFT, product with the filter
+// spectrum, inverse FFT), L = 2^S, by L/8 threads: one group of 8 values per
+// thread and pass, so that a thread meets the same twiddle factors on the way
+// back as on the way out.  load() reads all of them and the thread's filter
+// values ahead, beside the row's own values; read from memory pass by pass
+// they took a third of a pass (7 passes of 2048 points: 8.2 us in FP64 and 6.2
+// us in FP32, 5.8 and 3.9 us so; the row's way in and out takes 6 us more).
+// The arithmetic is that of the passes above.
+template <class D, int S>
+struct RowConvolution {
+    static constexpr int L = 1 << S, kRest = S % 3, kPasses = (S - kRest - 3) / 3;
+    static constexpr int kRestGroups = kRest ? 8 >> kRest : 1, kG = kRest ? kRest : 1;
+    Twiddles<D, kG> rest[kRestGroups];
+    Twiddles<D, 3> pass[kPasses], mid;
+    Cx<D> filter[8];
+
+    __device__ __forceinline__ void load(const Cx<D> *tw, const Cx<D> *fb) {
+        const int32_t g = threadIdx.x;
+        if constexpr (kRest > 0) {
+#pragma unroll
+            for (int q = 0; q < kRestGroups; ++q) rest[q].load(g + q * (L >> 3), L >> kRest, L, L, tw);
+        }
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            const int32_t len = L >> (kRest + 3 * p), sub = len >> 3;
+            pass[p].load(g & (sub - 1), sub, len, L, tw);
+        }
+        mid.load(0, 1, 8, L, tw);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) filter[j] = fb[8 * g + j];
+    }
+
+    // groups of 2^G values sub apart from base on
+    template <int G, class F>
+    static __device__ __forceinline__ void group(Cx<D> *a, int32_t base, int32_t sub, F &&f) {
+        Cx<D> v[1 << G];
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) v[j] = a[cslot(base + j * sub)];
+        f(v);
+#pragma unroll
+        for (int j = 0; j < (1 << G); ++j) a[cslot(base + j * sub)] = v[j];
+    }
+    static __device__ __forceinline__ int32_t base_of(int p) {
+        const int32_t sub = L >> (kRest + 3 * p + 3), o = threadIdx.x & (sub - 1);
+        return ((int32_t)threadIdx.x - o) << 3 | o;
+    }
+
+    __device__ __forceinline__ void run(Cx<D> *a) const {
+        const int32_t g = threadIdx.x;
+        if constexpr (kRest > 0) {
+#pragma unroll
+            for (int q = 0; q < kRestGroups; ++q)
+                group<kRest>(a, g + q * (L >> 3), L >> kRest, [&](Cx<D> (&v)[1 << kG]) { rest[q].forward(v); });
+            __syncthreads();
+        }
+#pragma unroll
+        for (int p = 0; p < kPasses; ++p) {
+            group<3>(a, base_of(p), L >> (kRest + 3 * p + 3), [&](Cx<D> (&v)[8]) { pass[p].forward(v); });
+            __syncthreads();
+        }
+        group<3>(a, 8 * g, 1, [&](Cx<D> (&v)[8]) {
+            mid.forward(v);
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v[j] = cmul(v[j], filter[j]);
+            mid.inverse(v);
+        });
+        __syncthreads();
+#pragma unroll
+        for (int p = kPasses - 1; p >= 0; --p) {
+            group<3>(a, base_of(p), L >> (kRest + 3 * p + 3), [&](Cx<D> (&v)[8]) { pass[p].inverse(v); });
+            __syncthreads();
+        }
+        if constexpr (kRest > 0) {
+#pragma unroll
+            for (int q = 0; q < kRestGroups; ++q)
+                group<kRest>(a, g + q * (L >> 3), L >> kRest, [&](Cx<D> (&v)[1 << kG]) { rest[q].inverse(v); });
+            __syncthreads();
+        }
+    }
+};
+
 // One radial row per block of dst_threads(L) threads (one group of 8 values
 // per thread and pass, 64 to 1024 threads: long rows, whose LDS allows one
 // block per CU, get the most).  kForward: input -rho/eps0 of column i from
 // the int64 charge grid, output bh[i][:] scaled by 2/N.  Inverse: input
-// bh[i][:], output Phi[1..m][i].
+// bh[i][:], output Phi[1..m][i].  S: log2 L where the row's factors stay in
+// registers, 0 for the passes above.
 inline int dst_threads(int32_t L) { return std::min(1024, std::max(64, L / 8)); }
+constexpr int dst_most_threads(int S) { return S ? 1 << (S - 3) : 1024; }
 
-template <class D, bool kForward>
-__global__ __launch_bounds__(1024) void k_dst_bluestein(const unsigned long long *q, const double *rhs, D *bh,
-                                                               double *phi, int32_t accumulate, const Cx<D> *chirp,
-                                                               const Cx<D> *fb, const Cx<D> *tw, int32_t nr,
-                                                               int32_t nz, int32_t L, double dr, double dz) {
+template <class D, bool kForward, int S>
+__global__ __launch_bounds__(dst_most_threads(S)) void k_dst_bluestein(const unsigned long long *q, const double *rhs,
+                                                                       D *bh, double *phi, int32_t accumulate,
+                                                                       const Cx<D> *chirp, const Cx<D> *fb,
+                                                                       const Cx<D> *tw, int32_t nr, int32_t nz,
+                                                                       int32_t L, double dr, double dz) {
     extern __shared__ unsigned char smem_raw[];
     Cx<D> *a = reinterpret_cast<Cx<D> *>(smem_raw);
-    const int32_t i = blockIdx.x, m = nz - 2, S = __builtin_ctz((uint32_t)L);
+    const int32_t m = nz - 2;
+    const int32_t i = xcd_place(nr - 1);  // the radial row
+    if (i >= nr - 1) return;
     const double vol = control_volume(i, dr, dz);
     const double scale = -kQe * 0x1p-32 / (vol * kEps0);
+    if constexpr (S > 0) L = 1 << S;
 #pragma unroll 4
     for (int32_t n = threadIdx.x; n < L; n += blockDim.x) {
         Cx<D> v{(D)0, (D)0};
@@ -485,25 +796,33 @@ __global__ __launch_bounds__(1024) void k_dst_bluestein(const unsigned long long
         }
         a[cslot(n)] = v;
     }
-    __syncthreads();
-    fft_forward_head<D>(a, L, S, tw);
-    // the last three forward stages, the product with the filter spectrum
-    // (both in bit-reversed order) and the first three inverse stages all act
-    // on the same 8 consecutive values: one pass
-    for (int32_t gi = threadIdx.x; gi < (L >> 3); gi += blockDim.x) {
-        const int32_t base = gi << 3;
-        Cx<D> v[8];
+    if constexpr (S > 0) {
+        RowConvolution<D, S> row;
+        row.load(tw, fb);
+        __syncthreads();
+        row.run(a);
+    } else {
+        __syncthreads();
+        const int32_t s = __builtin_ctz((uint32_t)L);
+        fft_forward_head<D>(a, L, s, tw);
+        // the last three forward stages, the product with the filter spectrum
+        // (both in bit-reversed order) and the first three inverse stages all act
+        // on the same 8 consecutive values: one pass
+        for (int32_t gi = threadIdx.x; gi < (L >> 3); gi += blockDim.x) {
+            const int32_t base = gi << 3;
+            Cx<D> v[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = a[cslot(base + j)];
-        dif_stages<D, 3>(v, 0, 1, 8, L, tw);
+            for (int j = 0; j < 8; ++j) v[j] = a[cslot(base + j)];
+            dif_stages<D, 3>(v, 0, 1, 8, L, tw);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = cmul(v[j], fb[base + j]);
-        dit_stages<D, 3>(v, 0, 1, 2, L, tw);
+            for (int j = 0; j < 8; ++j) v[j] = cmul(v[j], fb[base + j]);
+            dit_stages<D, 3>(v, 0, 1, 2, L, tw);
 #pragma unroll
-        for (int j = 0; j < 8; ++j) a[cslot(base + j)] = v[j];
+            for (int j = 0; j < 8; ++j) a[cslot(base + j)] = v[j];
+        }
+        __syncthreads();
+        fft_inverse_tail<D>(a, L, s, tw);
     }
-    __syncthreads();
-    fft_inverse_tail<D>(a, L, S, tw);
     // the inverse transform's 1/L folded into the output scale (a power of two)
     const D norm = (D)((kForward ? 2.0 / (double)(nz - 1) : 1.0) / (double)L);
 #pragma unroll 4
@@ -527,12 +846,6 @@ struct Bluestein {
 
 constexpr size_t kLdsLimit = 160 * 1024;  // LDS per workgroup on gfx950
 
-// Modes from which systems of more than 256 rows take Thomas sweeps: on the
-// 1024 x 8192 grid (8190 modes of 1023 rows) the sweeps took 0.21 ms and
-// cyclic reduction 0.80 ms; on the 256 x 1024 grid (1022 modes of 255 rows)
-// the sweeps took 0.056 ms and cyclic reduction 0.015 ms.
-constexpr int32_t kPcrMaxModes = 4096;
-
 // LDS a workgroup may take on the current device (the smaller of the
 // architectural limit and what the runtime reports).
 inline size_t lds_per_block() {
@@ -555,8 +868,28 @@ inline int32_t bluestein_length(int32_t m) {
 // spare slot per 8 (cslot).
 inline size_t bluestein_lds(int32_t L, size_t cx) { return ((size_t)L + (size_t)(L >> 3)) * cx; }
 
+// The transform kernel for n rows of FFT length L: with the factors in
+// registers where a block's L/8 threads have room for them (1024 threads have
+// 128 registers each, enough in FP32).  In FP64 the 4096-point kernel leaves
+// room for one block per CU, the general one for two: it is the better one
+// only while every CU has at most one row (255 rows of 4096 points: the solve
+// 45.9 against 50.9 us; 511 rows: 83.7 against 79.1).
+template <class D, bool kForward>
+inline const void *dst_kernel(int32_t L, int32_t n) {
+    if (sizeof(D) == 8 && L == 1 << 12 && n > 256) L = 0;
+    if constexpr (sizeof(D) == 4)
+        if (L == 1 << 13) return (const void *)&k_dst_bluestein<D, kForward, 13>;
+    switch (L) {
+    case 1 << 9: return (const void *)&k_dst_bluestein<D, kForward, 9>;
+    case 1 << 10: return (const void *)&k_dst_bluestein<D, kForward, 10>;
+    case 1 << 11: return (const void *)&k_dst_bluestein<D, kForward, 11>;
+    case 1 << 12: return (const void *)&k_dst_bluestein<D, kForward, 12>;
+    default: return (const void *)&k_dst_bluestein<D, kForward, 0>;
+    }
+}
+
 template <class D>
-inline hipError_t bluestein_prepare(Bluestein &B, int32_t m, hipStream_t st) {
+inline hipError_t bluestein_prepare(Bluestein &B, int32_t m, int32_t rows, hipStream_t st) {
     const int32_t n = std::max(m, B.L >> 1);
     k_bluestein_tables<D><<<(n + 255) / 256, 256, 0, st>>>((Cx<D> *)B.chirp, (Cx<D> *)B.tw, m, B.L);
     hipError_t e = hipGetLastError();
@@ -565,11 +898,9 @@ inline hipError_t bluestein_prepare(Bluestein &B, int32_t m, hipStream_t st) {
         e = hipFuncSetAttribute((const void *)&k_bluestein_filter<D>, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 (int)B.lds);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)&k_dst_bluestein<D, true>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
+            e = hipFuncSetAttribute(dst_kernel<D, true>(B.L, rows), hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
         if (e == hipSuccess)
-            e = hipFuncSetAttribute((const void *)&k_dst_bluestein<D, false>,
-                                    hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
+            e = hipFuncSetAttribute(dst_kernel<D, false>(B.L, rows), hipFuncAttributeMaxDynamicSharedMemorySize, (int)B.lds);
         if (e != hipSuccess) return e;
     }
     k_bluestein_filter<D><<<1, 1024, B.lds, st>>>((Cx<D> *)B.fb, (const Cx<D> *)B.tw, m, B.L);
@@ -584,9 +915,39 @@ inline hipError_t bluestein_prepare(Bluestein &B, int32_t m, hipStream_t st) {
 struct PoissonGrid {
     int32_t nr = 0, nz = 0;
     double dr = 0, dz = 0;
-    const double *sine = nullptr, *tcp = nullptr, *tinv = nullptr;
+    const double *sine = nullptr;
+    double *tri = nullptr, *tcp = nullptr, *tinv = nullptr;  // tables of the tridiagonal solve, of one kind
     const Bluestein *blu = nullptr;
 };
+
+// Which tridiagonal solve a context takes.  FP64 form: the scans up to 1024
+// rows, Thomas sweeps beyond.  FP32 form: cyclic reduction up to 256 rows, and
+// up to 1024 rows while the modes are too few to fill the GPU with Thomas
+// sweeps (one thread per mode), Thomas sweeps otherwise: on the 1024 x 8192
+// grid (8190 modes of 1023 rows) the sweeps took 0.21 ms and cyclic reduction
+// 0.80 ms; on the 256 x 1024 grid (1022 modes of 255 rows) the sweeps took
+// 0.056 ms and cyclic reduction 0.015 ms.
+constexpr int32_t kPcrMaxModes = 4096;
+inline bool takes_scans(bool fp32, int32_t nu) { return !fp32 && nu <= kTriMaxRows; }
+inline bool takes_thomas(int32_t nu, int32_t m) { return !(nu <= 256 || (nu <= 1024 && m < kPcrMaxModes)); }
+
+// Doubles of its tables: tri of the scans, tcp and tinv of the sweeps.
+inline size_t tri_len(bool fp32, int32_t nr, int32_t nz) {
+    return takes_scans(fp32, nr - 1) ? (size_t)64 * tri_rows_per_lane(nr - 1) * nz : 0;
+}
+inline size_t thomas_len(bool fp32, int32_t nr, int32_t nz) {
+    return !takes_scans(fp32, nr - 1) && takes_thomas(nr - 1, nz - 2) ? (size_t)(nr - 1) * (nz - 2) : 0;
+}
+
+// Fills the tables of the solve that g has buffers for.
+inline hipError_t tri_prepare(const PoissonGrid &g, hipStream_t st) {
+    const int32_t m = g.nz - 2, nu = g.nr - 1;
+    if (g.tri)
+        k_tri_table<<<(m + 63) / 64, 64, 0, st>>>(g.tri, g.nr, g.nz, g.dr, g.dz, 64 * tri_rows_per_lane(nu));
+    else if (g.tcp)
+        k_thomas_coef<<<(m + 255) / 256, 256, 0, st>>>(g.tcp, g.tinv, g.nr, g.nz, g.dr, g.dz);
+    return hipGetLastError();
+}
 
 template <class D>
 inline hipError_t poisson_solve(const PoissonGrid &g, const unsigned long long *q, const double *rhs, D *bh,
@@ -594,31 +955,41 @@ inline hipError_t poisson_solve(const PoissonGrid &g, const unsigned long long *
     const int32_t m = g.nz - 2, nu = g.nr - 1;
     const Bluestein &B = *g.blu;
     const Cx<D> *chirp = (const Cx<D> *)B.chirp, *fb = (const Cx<D> *)B.fb, *tw = (const Cx<D> *)B.tw;
+    hipError_t e = hipSuccess;
+    int32_t nr = g.nr, nz = g.nz, L = B.L, add = accumulate ? 1 : 0;
+    double dr = g.dr, dz = g.dz;
+    void *args[] = {&q, &rhs, &bh, &phi, &add, &chirp, &fb, &tw, &nr, &nz, &L, &dr, &dz};
+    const dim3 rows(xcd_blocks(nu)), threads(B.L > 0 ? dst_threads(B.L) : 0);
     if (B.L > 0)
-        k_dst_bluestein<D, true><<<nu, dst_threads(B.L), B.lds, st>>>(q, rhs, bh, nullptr, 0, chirp, fb, tw, g.nr, g.nz, B.L,
-                                                           g.dr, g.dz);
+        e = hipLaunchKernel(dst_kernel<D, true>(B.L, nu), rows, threads, args, B.lds, st);
     else
         k_dst_rows<D><<<nu, 256, m * sizeof(D), st>>>(q, rhs, g.sine, bh, g.nr, g.nz, g.dr, g.dz);
-    hipError_t e = hipGetLastError();
+    if (e == hipSuccess) e = hipGetLastError();
     if (e != hipSuccess) return e;
-    // tridiagonal solves: cyclic reduction up to 256 rows, and up to 1024
-    // rows while the modes are too few to fill the GPU with Thomas sweeps
-    // (one thread per mode); Thomas sweeps otherwise
-    if (nu <= 256)
-        k_pcr<D, 4, 4><<<(m + 3) / 4, 256, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
-    else if (nu <= 512 && m < kPcrMaxModes)
-        k_pcr<D, 8, 2><<<(m + 1) / 2, 128, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
-    else if (nu <= 1024 && m < kPcrMaxModes)
-        k_pcr<D, 16, 1><<<m, 64, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
-    else
+    if (g.tri) {
+        constexpr int W = 4;
+        const unsigned nb = xcd_blocks((m + W - 1) / W);
+        switch (tri_rows_per_lane(nu)) {
+        case 2: k_tri<D, 2, W><<<nb, 64 * W, 0, st>>>(bh, g.tri, g.nr, g.nz); break;
+        case 4: k_tri<D, 4, W><<<nb, 64 * W, 0, st>>>(bh, g.tri, g.nr, g.nz); break;
+        case 8: k_tri<D, 8, W><<<nb, 64 * W, 0, st>>>(bh, g.tri, g.nr, g.nz); break;
+        default: k_tri<D, 16, W><<<nb, 64 * W, 0, st>>>(bh, g.tri, g.nr, g.nz); break;
+        }
+    } else if (takes_thomas(nu, m)) {
         k_thomas<D><<<(m + 255) / 256, 256, 0, st>>>(bh, g.tcp, g.tinv, g.nr, g.nz, g.dr);
+    } else if (nu <= 256) {
+        k_pcr<D, 4, 4><<<xcd_blocks((m + 3) / 4), 256, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+    } else if (nu <= 512) {
+        k_pcr<D, 8, 2><<<xcd_blocks((m + 1) / 2), 128, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+    } else {
+        k_pcr<D, 16, 1><<<xcd_blocks(m), 64, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+    }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (B.L > 0)
-        k_dst_bluestein<D, false><<<nu, dst_threads(B.L), B.lds, st>>>(nullptr, nullptr, bh, phi, accumulate ? 1 : 0, chirp, fb,
-                                                            tw, g.nr, g.nz, B.L, g.dr, g.dz);
+        e = hipLaunchKernel(dst_kernel<D, false>(B.L, nu), rows, threads, args, B.lds, st);
     else
         k_idst_rows<D><<<nu, 256, m * sizeof(D), st>>>(bh, g.sine, phi, g.nr, g.nz, accumulate ? 1 : 0);
-    return hipGetLastError();
+    return e != hipSuccess ? e : hipGetLastError();
 }
 
 // ---------------------------------------------------------------------------

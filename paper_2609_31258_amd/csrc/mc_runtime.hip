@@ -69,7 +69,7 @@ struct mc_ctx {
     // the charge grid, and the zeroed grid the next deposit adds into: the two
     // swap, and the field bake of an update clears the one that it retired
     unsigned long long *qgrid = nullptr, *qnext = nullptr;
-    double *sine = nullptr, *tcp = nullptr, *tinv = nullptr;
+    double *sine = nullptr;
     void *bh = nullptr;
     Bluestein blu;
     PoissonGrid pg;
@@ -637,7 +637,7 @@ static int32_t mask_setup(mc_ctx *ctx) {
             rc = dalloc(ctx, &b64.chirp, (size_t)m * cx);
             if (!rc) rc = dalloc(ctx, &b64.tw, (size_t)std::max(L / 2, 1) * cx);
             if (!rc) rc = dalloc(ctx, &b64.fb, (size_t)L * cx);
-            if (!rc && bluestein_prepare<double>(b64, m, ctx->stream) != hipSuccess) b64.L = 0;
+            if (!rc && bluestein_prepare<double>(b64, m, nu, ctx->stream) != hipSuccess) b64.L = 0;
         }
         if (rc) return rc;
         g64.blu = &b64;
@@ -992,8 +992,10 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     if (!rc) rc = dalloc_t(ctx, &ctx->qgrid, nn);
     if (!rc) rc = dalloc_t(ctx, &ctx->qnext, nn);
     if (!rc) rc = dalloc_t(ctx, &ctx->sine, 2 * (int64_t)(g->nz - 1));
-    if (!rc) rc = dalloc_t(ctx, &ctx->tcp, (int64_t)nu * m);
-    if (!rc) rc = dalloc_t(ctx, &ctx->tinv, (int64_t)nu * m);
+    const size_t n_tri = tri_len(ctx->fp32(), g->nr, g->nz), n_thomas = thomas_len(ctx->fp32(), g->nr, g->nz);
+    if (!rc && n_tri) rc = dalloc_t(ctx, &ctx->pg.tri, n_tri);
+    if (!rc && n_thomas) rc = dalloc_t(ctx, &ctx->pg.tcp, n_thomas);
+    if (!rc && n_thomas) rc = dalloc_t(ctx, &ctx->pg.tinv, n_thomas);
     if (!rc) rc = dalloc(ctx, &ctx->bh, (size_t)nu * m * (ctx->fp32() ? sizeof(float) : sizeof(double)));
     const size_t node_bytes = !ctx->fp32() ? sizeof(double4) : (ctx->bf16() ? sizeof(bf16x4) : sizeof(float4));
     if (!rc) rc = dalloc(ctx, &ctx->etab, nn * node_bytes);
@@ -1045,8 +1047,6 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     else HIPCHK(hipMemsetAsync(ctx->mask, 0, nn, ctx->stream));
     k_sine_table<<<grid_for(2 * (g->nz - 1)), kBlock, 0, ctx->stream>>>(ctx->sine, g->nz);
     LAUNCHCHK();
-    k_thomas_coef<<<grid_for(m), kBlock, 0, ctx->stream>>>(ctx->tcp, ctx->tinv, g->nr, g->nz, g->dr, g->dz);
-    LAUNCHCHK();
     // chirp z sine transform tables when the FFT length fits in LDS
     {
         Bluestein &B = ctx->blu;
@@ -1059,8 +1059,8 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
             if (!rc2) rc2 = dalloc(ctx, &B.tw, (size_t)std::max(L / 2, 1) * cx);
             if (!rc2) rc2 = dalloc(ctx, &B.fb, (size_t)L * cx);
             if (rc2) return rc2;
-            const hipError_t e = ctx->fp32() ? bluestein_prepare<float>(B, m, ctx->stream)
-                                             : bluestein_prepare<double>(B, m, ctx->stream);
+            const hipError_t e = ctx->fp32() ? bluestein_prepare<float>(B, m, nu, ctx->stream)
+                                             : bluestein_prepare<double>(B, m, nu, ctx->stream);
             if (e != hipSuccess) B.L = 0;  // fall back to the direct sine sums
         }
     }
@@ -1069,9 +1069,8 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     ctx->pg.dr = g->dr;
     ctx->pg.dz = g->dz;
     ctx->pg.sine = ctx->sine;
-    ctx->pg.tcp = ctx->tcp;
-    ctx->pg.tinv = ctx->tinv;
     ctx->pg.blu = &ctx->blu;
+    HIPCHK(tri_prepare(ctx->pg, ctx->stream));
     ctx->mask_nodes = mask_unknowns(t->mask, g->nr, g->nz);
     HIPCHK(hipStreamSynchronize(ctx->stream));
     // the staging buffer is returned at once

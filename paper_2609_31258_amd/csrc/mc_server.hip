@@ -86,7 +86,7 @@ struct mc_server {
     float gsc[4] = {1, 1, 1, 1}, esc[4] = {1, 1, 1, 1};
     uint8_t *hit = nullptr;
     StepTables *tables = nullptr;  // the FP64 step's logarithm and turn tables
-    double *sine = nullptr, *tcp = nullptr, *tinv = nullptr;
+    double *sine = nullptr;
     Bluestein blu;
     PoissonGrid pg;
     std::vector<int32_t> mask_nodes;  // metal-mask nodes among the Poisson unknowns
@@ -371,7 +371,7 @@ static int32_t pic_query(mc_server *S, Query &Q, PackPtrs<typename P::T> p) {
                     if (salloc(S, &b64.chirp, (size_t)m * cx) || salloc(S, &b64.tw, (size_t)std::max(L / 2, 1) * cx) ||
                         salloc(S, &b64.fb, (size_t)L * cx))
                         return MC_ENOMEM;
-                    if (bluestein_prepare<double>(b64, m, S->stream) != hipSuccess) b64.L = 0;
+                    if (bluestein_prepare<double>(b64, m, nu, S->stream) != hipSuccess) b64.L = 0;
                 }
                 g64.blu = &b64;
             }
@@ -845,8 +845,10 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
     if (!rc) rc = salloc_t(S, &S->hit, nn);
     if (!rc) rc = salloc_t(S, &mask, nn);
     if (!rc) rc = salloc_t(S, &S->sine, 2 * (int64_t)(g->nz - 1));
-    if (!rc) rc = salloc_t(S, &S->tcp, (int64_t)nu * m);
-    if (!rc) rc = salloc_t(S, &S->tinv, (int64_t)nu * m);
+    const size_t n_tri = tri_len(S->fp32(), g->nr, g->nz), n_thomas = thomas_len(S->fp32(), g->nr, g->nz);
+    if (!rc && n_tri) rc = salloc_t(S, &S->pg.tri, n_tri);
+    if (!rc && n_thomas) rc = salloc_t(S, &S->pg.tcp, n_thomas);
+    if (!rc && n_thomas) rc = salloc_t(S, &S->pg.tinv, n_thomas);
     if (!rc) rc = salloc_t(S, &tmp, 4 * nn);
     if (!rc) rc = salloc_t(S, &S->tables, 1);
     if (rc) return bail(rc);
@@ -889,7 +891,6 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
     k_hit<<<blocks_for(nn), kBlk, 0, S->stream>>>(mask, S->hit, g->nr, g->nz, g->dr, g->dz, reach,
                                                  (int32_t)std::ceil(reach / g->dr), (int32_t)std::ceil(reach / g->dz));
     k_sine_table<<<blocks_for(2 * (g->nz - 1)), kBlk, 0, S->stream>>>(S->sine, g->nz);
-    k_thomas_coef<<<blocks_for(m), kBlk, 0, S->stream>>>(S->tcp, S->tinv, g->nr, g->nz, g->dr, g->dz);
     SC2(hipGetLastError());
     {
         Bluestein &B = S->blu;
@@ -901,8 +902,8 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
             if (salloc(S, &B.chirp, (size_t)m * cx) || salloc(S, &B.tw, (size_t)std::max(L / 2, 1) * cx) ||
                 salloc(S, &B.fb, (size_t)L * cx))
                 return bail(MC_ENOMEM);
-            const hipError_t e = S->fp32() ? bluestein_prepare<float>(B, m, S->stream)
-                                           : bluestein_prepare<double>(B, m, S->stream);
+            const hipError_t e = S->fp32() ? bluestein_prepare<float>(B, m, nu, S->stream)
+                                           : bluestein_prepare<double>(B, m, nu, S->stream);
             if (e != hipSuccess) B.L = 0;
         }
     }
@@ -911,9 +912,8 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
     S->pg.dr = g->dr;
     S->pg.dz = g->dz;
     S->pg.sine = S->sine;
-    S->pg.tcp = S->tcp;
-    S->pg.tinv = S->tinv;
     S->pg.blu = &S->blu;
+    SC2(tri_prepare(S->pg, S->stream));
     S->mask_nodes = mask_unknowns(t->mask, g->nr, g->nz);
     SC2(hipStreamSynchronize(S->stream));
     if (S->bf16()) {
