@@ -1281,17 +1281,6 @@ static __global__ __launch_bounds__(256) void k_hit(const uint8_t *mask, uint8_t
     hit[n] = h;
 }
 
-// Snapshot pack initialisation after a host write: charge from the ion
-// charge and weight, status active.
-template <class T>
-__global__ __launch_bounds__(256) void k_init_written(PackPtrs<T> p, const Species *sp, const int32_t *charge,
-                                                      int64_t n) {
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-    if (s >= n) return;
-    p.q[s] = fx32((double)charge[p.tag[s]] * p.w[s]);
-    p.status[s] = ST_ACTIVE;
-}
-
 // ---------------------------------------------------------------------------
 // Read-time tallies: active count/weight and histograms (int64 atomics), and
 // FP64 sums reduced per block in a fixed order (deterministic).

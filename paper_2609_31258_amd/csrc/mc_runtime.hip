@@ -16,6 +16,7 @@
 #include <vector>
 
 #include "mc_host.hpp"
+#include "mc_io.hpp"
 #include "mc_kernels.hpp"
 #include "mc_poisson.hpp"
 #include "mc_sort.hpp"
@@ -117,6 +118,8 @@ struct mc_ctx {
     int64_t emitted_n = 0, emitted_w = 0;
     int64_t step = 0;
 
+    hipEvent_t stage_ev[2] = {nullptr, nullptr};  // of the staging memory's halves (staged)
+
     std::vector<EvPair> ev_used;
     std::vector<hipEvent_t> ev_pool;
     double t_ms[MC_NKERNEL] = {0};
@@ -183,6 +186,48 @@ static void dfree_all(mc_ctx *ctx) {
     }
     ctx->allocs.clear();
     ctx->device_bytes = 0;
+}
+
+// Staging memory for the length of a call (mc_io.hpp).
+struct Stage {
+    char *base = nullptr;
+    Stage() : base(stage_pool().take()) {}
+    ~Stage() {
+        if (base) stage_pool().put(base);
+    }
+    Stage(const Stage &) = delete;
+    Stage &operator=(const Stage &) = delete;
+};
+
+// n items of `item` bytes through the staging halves: fill(half, first, count)
+// is called in turn for consecutive pieces and enqueues the device's part,
+// done(half, first, count) follows when the device has finished with it.
+// Filling one half overlaps the other's device part.
+template <class Fill, class Done>
+static int32_t staged(mc_ctx *ctx, int64_t n, size_t item, Fill &&fill, Done &&done) {
+    Stage stage;
+    if (!stage.base) return fail(ctx, MC_ENOMEM, "pinned staging memory");
+    const int64_t per = (int64_t)(kStageHalf / item) & ~(int64_t)255, pieces = (n + per - 1) / per;
+    const auto count = [&](int64_t k) { return std::min(per, n - k * per); };
+    const auto run = [&]() -> int32_t {
+        for (hipEvent_t &e : ctx->stage_ev)
+            if (!e) HIPCHK(hipEventCreateWithFlags(&e, hipEventDisableTiming));
+        for (int64_t k = 0; k <= pieces; ++k) {
+            if (k < pieces) {
+                const int32_t rc = fill(stage.base + (k & 1) * kStageHalf, k * per, count(k));
+                if (rc) return rc;
+                HIPCHK(hipEventRecord(ctx->stage_ev[k & 1], ctx->stream));
+            }
+            if (k > 0) {
+                HIPCHK(hipEventSynchronize(ctx->stage_ev[(k - 1) & 1]));
+                done(stage.base + ((k - 1) & 1) * kStageHalf, (k - 1) * per, count(k - 1));
+            }
+        }
+        return MC_OK;
+    };
+    const int32_t rc = run();
+    if (rc) (void)hipStreamSynchronize(ctx->stream);  // the memory goes back with nothing under way
+    return rc;
 }
 
 // Timing events come from a pool that is refilled in batches (creating an
@@ -893,11 +938,13 @@ int32_t mc_create(const mc_options *o, mc_ctx **out) {
         delete ctx;
         return MC_EDEVICE;
     }
+    stage_pool().join();
     if (o->stream) {
         ctx->stream = static_cast<hipStream_t>(o->stream);
     } else {
         e = hipStreamCreateWithFlags(&ctx->stream, hipStreamNonBlocking);
         if (e != hipSuccess) {
+            stage_pool().leave();
             delete ctx;
             return MC_EDEVICE;
         }
@@ -945,6 +992,9 @@ void mc_destroy(mc_ctx *ctx) {
     if (!ctx) return;
     (void)hipSetDevice(ctx->opt.device);
     dfree_all(ctx);
+    for (hipEvent_t e : ctx->stage_ev)
+        if (e) (void)hipEventDestroy(e);
+    stage_pool().leave();
     for (auto &p : ctx->ev_used) {
         (void)hipEventDestroy(p.a);
         (void)hipEventDestroy(p.b);
@@ -1460,14 +1510,38 @@ int32_t mc_read_tallies(mc_ctx *ctx, mc_tallies *out) {
     HIPCHK(hipSetDevice(ctx->opt.device));
     int32_t rc = ctx->fp32() ? snapshot_t<float>(ctx, ctx->p32) : snapshot_t<double>(ctx, ctx->p64);
     if (rc) return rc;
-    HIPCHK(hipStreamSynchronize(ctx->stream));
-    std::vector<unsigned long long> cnt(TC_N), hot(kHotLen), snap(2 + MC_HIST_KE + MC_HIST_TEFF);
+    // everything but the loss map in one gather: counters and exit bins, the
+    // three histograms, the replicated counters, the active population's
+    const int64_t n_snap = 2 + MC_HIST_KE + MC_HIST_TEFF, n_cnt = TC_N + ctx->op.n_exit_bins,
+                  n_hist = MC_HIST_KE + MC_HIST_TEFF + MC_HIST_R, words = n_cnt + n_hist + kHotLen + n_snap + 3;
+    std::vector<unsigned long long> all(words);
+    {
+        Stage stage;
+        if (!stage.base) return fail(ctx, MC_ENOMEM, "pinned staging memory");
+        Gather g{};
+        const unsigned long long *from[] = {ctx->tp.cnt, ctx->tp.hist_ke, ctx->tp.hot, ctx->snap,
+                                            (const unsigned long long *)ctx->sums};
+        const int64_t len[] = {n_cnt, n_hist, kHotLen, n_snap, 3};
+        for (int a = 0; a < 5; ++a) {
+            g.from[a] = from[a];
+            g.len[a] = len[a];
+        }
+        if ((size_t)words * 8 <= 2 * kStageHalf) {
+            k_gather_words<<<16, kBlock, 0, ctx->stream>>>(g, (unsigned long long *)stage.base);
+            LAUNCHCHK();
+            HIPCHK(hipStreamSynchronize(ctx->stream));
+            std::memcpy(all.data(), stage.base, words * 8);
+        } else {  // more exit bins than the staging memory holds
+            HIPCHK(hipStreamSynchronize(ctx->stream));
+            unsigned long long *to = all.data();
+            for (int a = 0; a < 5; to += len[a], ++a) HIPCHK(hipMemcpy(to, from[a], len[a] * 8, hipMemcpyDeviceToHost));
+        }
+    }
+    unsigned long long *cnt = all.data();
+    const unsigned long long *hist = cnt + n_cnt, *hot = hist + n_hist, *snap = hot + kHotLen;
     double sums[3];
-    HIPCHK(hipMemcpy(cnt.data(), ctx->tp.cnt, TC_N * sizeof(unsigned long long), hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(hot.data(), ctx->tp.hot, kHotLen * sizeof(unsigned long long), hipMemcpyDeviceToHost));
-    fold_hot(hot.data(), cnt.data());
-    HIPCHK(hipMemcpy(snap.data(), ctx->snap, snap.size() * sizeof(unsigned long long), hipMemcpyDeviceToHost));
-    HIPCHK(hipMemcpy(sums, ctx->sums, 3 * sizeof(double), hipMemcpyDeviceToHost));
+    std::memcpy(sums, snap + n_snap, sizeof(sums));
+    fold_hot(hot, cnt);
     out->emitted_n = ctx->emitted_n;
     out->emitted_w = ctx->emitted_w;
     for (int c = 0; c < MC_NCLASS; ++c) {
@@ -1489,14 +1563,13 @@ int32_t mc_read_tallies(mc_ctx *ctx, mc_tallies *out) {
     out->sum_w_eint_active = sums[1];
     out->sum_w_dissoc_terminal = sums[2];
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
-    if (out->exit_bins)
-        HIPCHK(hipMemcpy(out->exit_bins, ctx->tp.exit_bins, ctx->op.n_exit_bins * sizeof(int64_t), hipMemcpyDeviceToHost));
+    if (out->exit_bins) std::memcpy(out->exit_bins, cnt + TC_N, ctx->op.n_exit_bins * sizeof(int64_t));
     if (out->loss_map) HIPCHK(hipMemcpy(out->loss_map, ctx->tp.loss_map, nn * sizeof(int64_t), hipMemcpyDeviceToHost));
-    if (out->hist_ke) HIPCHK(hipMemcpy(out->hist_ke, ctx->tp.hist_ke, MC_HIST_KE * 8, hipMemcpyDeviceToHost));
-    if (out->hist_teff) HIPCHK(hipMemcpy(out->hist_teff, ctx->tp.hist_teff, MC_HIST_TEFF * 8, hipMemcpyDeviceToHost));
-    if (out->hist_r) HIPCHK(hipMemcpy(out->hist_r, ctx->tp.hist_r, MC_HIST_R * 8, hipMemcpyDeviceToHost));
-    if (out->act_hist_ke) std::memcpy(out->act_hist_ke, snap.data() + 2, MC_HIST_KE * 8);
-    if (out->act_hist_teff) std::memcpy(out->act_hist_teff, snap.data() + 2 + MC_HIST_KE, MC_HIST_TEFF * 8);
+    if (out->hist_ke) std::memcpy(out->hist_ke, hist, MC_HIST_KE * 8);
+    if (out->hist_teff) std::memcpy(out->hist_teff, hist + MC_HIST_KE, MC_HIST_TEFF * 8);
+    if (out->hist_r) std::memcpy(out->hist_r, hist + MC_HIST_KE + MC_HIST_TEFF, MC_HIST_R * 8);
+    if (out->act_hist_ke) std::memcpy(out->act_hist_ke, snap + 2, MC_HIST_KE * 8);
+    if (out->act_hist_teff) std::memcpy(out->act_hist_teff, snap + 2 + MC_HIST_KE, MC_HIST_TEFF * 8);
     return MC_OK;
 }
 
@@ -1535,6 +1608,20 @@ int32_t mc_read_exits(mc_ctx *ctx, mc_exit_rec *buf, int64_t cap, int64_t *n) {
     return MC_OK;
 }
 
+// The staged arrays of n slots in a half of the staging memory (want: which of
+// them the caller has).
+static StagedPacks staged_packs(char *half, const bool (&want)[kPackArrays], int64_t first, int64_t n) {
+    StagedPacks p{};
+    p.first = first;
+    p.n = n;
+    for (int a = 0; a < kPackArrays; ++a) {
+        if (!want[a]) continue;
+        p.base[a] = half;
+        half += n * pack_array_bytes(a);
+    }
+    return p;
+}
+
 int32_t mc_read_packs(mc_ctx *ctx, mc_packs *o) {
     if (!ctx || !o) return MC_EINVAL;
     if (o->n < ctx->n_slots) return fail(ctx, MC_EINVAL, "buffer shorter than the slot count");
@@ -1543,43 +1630,39 @@ int32_t mc_read_packs(mc_ctx *ctx, mc_packs *o) {
     const int64_t n = ctx->n_slots;
     o->n = n;
     if (n == 0) return MC_OK;
-    auto cp = [&](void *dst, const void *src, size_t b) -> hipError_t {
-        return dst ? hipMemcpy(dst, src, b, hipMemcpyDeviceToHost) : hipSuccess;
-    };
-    if (!ctx->fp32()) {
-        const PackPtrs<double> &p = ctx->p64;
-        double *dsts[] = {o->x, o->y, o->z, o->vx, o->vy, o->vz, o->e_int, o->h, o->w};
-        double *srcs[] = {p.x, p.y, p.z, p.vx, p.vy, p.vz, p.e, p.h, p.w};
-        for (int k = 0; k < 9; ++k) HIPCHK(cp(dsts[k], srcs[k], n * sizeof(double)));
-        HIPCHK(cp(o->id, p.id, n * 8));
-        HIPCHK(cp(o->q, p.q, n * 8));
-        HIPCHK(cp(o->tag, p.tag, n * 4));
-        HIPCHK(cp(o->status, p.status, n * 4));
-    } else {
-        const PackPtrs<float> &p = ctx->p32;
-        std::vector<float> hi(n), lo(n);
-        double *dsts[] = {o->x, o->y, o->z, o->e_int};
-        float *shi[] = {p.x, p.y, p.z, p.e}, *slo[] = {p.xl, p.yl, p.zl, p.el};
-        for (int k = 0; k < 4; ++k) {
-            if (!dsts[k]) continue;
-            HIPCHK(hipMemcpy(hi.data(), shi[k], n * 4, hipMemcpyDeviceToHost));
-            HIPCHK(hipMemcpy(lo.data(), slo[k], n * 4, hipMemcpyDeviceToHost));
-            for (int64_t i = 0; i < n; ++i) dsts[k][i] = (double)hi[i] + (double)lo[i];
-        }
-        double *d1[] = {o->vx, o->vy, o->vz, o->h};
-        float *s1[] = {p.vx, p.vy, p.vz, p.h};
-        for (int k = 0; k < 4; ++k) {
-            if (!d1[k]) continue;
-            HIPCHK(hipMemcpy(hi.data(), s1[k], n * 4, hipMemcpyDeviceToHost));
-            for (int64_t i = 0; i < n; ++i) d1[k][i] = (double)hi[i];
-        }
-        HIPCHK(cp(o->w, p.w, n * 8));
-        HIPCHK(cp(o->id, p.id, n * 8));
-        HIPCHK(cp(o->q, p.q, n * 8));
-        HIPCHK(cp(o->tag, p.tag, n * 4));
-        HIPCHK(cp(o->status, p.status, n * 4));
+    void *dst[kPackArrays] = {o->x,     o->y, o->z,  o->vx, o->vy,  o->vz,    o->e_int,
+                              o->h,     o->w, o->id, o->q,  o->tag, o->status};
+    bool want[kPackArrays];
+    for (int a = 0; a < kPackArrays; ++a) want[a] = dst[a] != nullptr;
+    return staged(
+        ctx, n, 96,
+        [&](char *half, int64_t first, int64_t count) -> int32_t {
+            const StagedPacks p = staged_packs(half, want, first, count);
+            if (ctx->fp32())
+                k_export_packs<float><<<grid_for(count), kBlock, 0, ctx->stream>>>(ctx->p32, p);
+            else
+                k_export_packs<double><<<grid_for(count), kBlock, 0, ctx->stream>>>(ctx->p64, p);
+            LAUNCHCHK();
+            return MC_OK;
+        },
+        [&](char *half, int64_t first, int64_t count) {
+            const StagedPacks p = staged_packs(half, want, first, count);
+            for (int a = 0; a < kPackArrays; ++a)
+                if (want[a])
+                    std::memcpy((char *)dst[a] + first * pack_array_bytes(a), p.base[a], count * pack_array_bytes(a));
+        });
+}
+
+// Whether every value is finite: an exponent of all ones carries into the sign
+// bit (integer arithmetic, which the compiler turns into vector code).
+static bool all_finite(const double *v, int64_t n) {
+    uint64_t any = 0;
+    for (int64_t k = 0; k < n; ++k) {
+        uint64_t b;
+        std::memcpy(&b, v + k, sizeof(b));
+        any |= (b & 0x7FF0000000000000ull) + 0x0010000000000000ull;
     }
-    return MC_OK;
+    return !(any >> 63);
 }
 
 int32_t mc_write_packs(mc_ctx *ctx, const mc_packs *in) {
@@ -1588,56 +1671,40 @@ int32_t mc_write_packs(mc_ctx *ctx, const mc_packs *in) {
     if (!in->x || !in->y || !in->z || !in->vx || !in->vy || !in->vz || !in->e_int || !in->h || !in->w || !in->id ||
         !in->tag)
         return fail(ctx, MC_EINVAL, "snapshot field missing");
-    for (int64_t k = 0; k < in->n; ++k) {
+    const int64_t n = in->n;
+    for (int64_t k = 0; k < n; ++k)
         if (in->tag[k] < 0 || in->tag[k] >= (int32_t)ctx->ions.size()) return fail(ctx, MC_EINVAL, "bad ion tag");
-        if (!std::isfinite(in->x[k]) || !std::isfinite(in->y[k]) || !std::isfinite(in->z[k]) ||
-            !std::isfinite(in->vx[k]) || !std::isfinite(in->vy[k]) || !std::isfinite(in->vz[k]) ||
-            !std::isfinite(in->e_int[k]) || !std::isfinite(in->w[k]) || !std::isfinite(in->h[k]))
-            return fail(ctx, MC_EINVAL, "non-finite snapshot state");
-    }
+    const double *f[kPackF64] = {in->x, in->y, in->z, in->vx, in->vy, in->vz, in->e_int, in->h, in->w};
+    for (const double *v : f)
+        if (!all_finite(v, n)) return fail(ctx, MC_EINVAL, "non-finite snapshot state");
     HIPCHK(hipSetDevice(ctx->opt.device));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    const int64_t n = in->n;
+    const void *src[kPackArrays] = {in->x, in->y, in->z,  in->vx, in->vy,  in->vz, in->e_int,
+                                    in->h, in->w, in->id, nullptr, in->tag, nullptr};
+    bool have[kPackArrays];
+    for (int a = 0; a < kPackArrays; ++a) have[a] = src[a] != nullptr;
     if (n > 0) {
-        if (!ctx->fp32()) {
-            const PackPtrs<double> &p = ctx->p64;
-            const double *s[] = {in->x, in->y, in->z, in->vx, in->vy, in->vz, in->e_int, in->h, in->w};
-            double *d[] = {p.x, p.y, p.z, p.vx, p.vy, p.vz, p.e, p.h, p.w};
-            for (int k = 0; k < 9; ++k) HIPCHK(hipMemcpy(d[k], s[k], n * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy(p.id, in->id, n * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy(p.tag, in->tag, n * 4, hipMemcpyHostToDevice));
-            k_init_written<double><<<grid_for(n), kBlock, 0, ctx->stream>>>(p, ctx->sp_dev, ctx->charge_dev, n);
-        } else {
-            const PackPtrs<float> &p = ctx->p32;
-            std::vector<float> hi(n), lo(n);
-            const double *s2[] = {in->x, in->y, in->z, in->e_int};
-            float *dh[] = {p.x, p.y, p.z, p.e}, *dl[] = {p.xl, p.yl, p.zl, p.el};
-            for (int k = 0; k < 4; ++k) {
-                for (int64_t i = 0; i < n; ++i) {
-                    hi[i] = (float)s2[k][i];
-                    lo[i] = (float)(s2[k][i] - (double)hi[i]);
-                }
-                HIPCHK(hipMemcpy(dh[k], hi.data(), n * 4, hipMemcpyHostToDevice));
-                HIPCHK(hipMemcpy(dl[k], lo.data(), n * 4, hipMemcpyHostToDevice));
-            }
-            const double *s1[] = {in->vx, in->vy, in->vz, in->h};
-            float *d1[] = {p.vx, p.vy, p.vz, p.h};
-            for (int k = 0; k < 4; ++k) {
-                for (int64_t i = 0; i < n; ++i) hi[i] = (float)s1[k][i];
-                HIPCHK(hipMemcpy(d1[k], hi.data(), n * 4, hipMemcpyHostToDevice));
-            }
-            HIPCHK(hipMemcpy(p.w, in->w, n * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy(p.id, in->id, n * 8, hipMemcpyHostToDevice));
-            HIPCHK(hipMemcpy(p.tag, in->tag, n * 4, hipMemcpyHostToDevice));
-            k_init_written<float><<<grid_for(n), kBlock, 0, ctx->stream>>>(p, ctx->sp_dev, ctx->charge_dev, n);
-        }
-        LAUNCHCHK();
+        const int32_t rc = staged(
+            ctx, n, 96,
+            [&](char *half, int64_t first, int64_t count) -> int32_t {
+                const StagedPacks p = staged_packs(half, have, first, count);
+                for (int a = 0; a < kPackArrays; ++a)
+                    if (have[a])
+                        std::memcpy(p.base[a], (const char *)src[a] + first * pack_array_bytes(a),
+                                    count * pack_array_bytes(a));
+                if (ctx->fp32())
+                    k_import_packs<float><<<grid_for(count), kBlock, 0, ctx->stream>>>(ctx->p32, ctx->charge_dev, p);
+                else
+                    k_import_packs<double><<<grid_for(count), kBlock, 0, ctx->stream>>>(ctx->p64, ctx->charge_dev, p);
+                LAUNCHCHK();
+                return MC_OK;
+            },
+            [](char *, int64_t, int64_t) {});
+        if (rc) return rc;
     }
     ctx->n_slots = n;
-    HIPCHK(hipStreamSynchronize(ctx->stream));
     return MC_OK;
 }
-
 
 int32_t mc_save_state(mc_ctx *ctx, const char *path) {
     if (!ctx || !path) return MC_EINVAL;
@@ -1748,14 +1815,21 @@ int32_t mc_read_sc(mc_ctx *ctx, double *phi, double *er, double *ez) {
     HIPCHK(hipStreamSynchronize(ctx->stream));
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
     if (phi) HIPCHK(hipMemcpy(phi, ctx->phi_sc, nn * 8, hipMemcpyDeviceToHost));
-    if (er || ez) {
-        std::vector<double2> e(nn);
-        HIPCHK(hipMemcpy(e.data(), ctx->e_sc, nn * sizeof(double2), hipMemcpyDeviceToHost));
-        for (int64_t k = 0; k < nn; ++k) {
-            if (er) er[k] = e[k].x;
-            if (ez) ez[k] = e[k].y;
-        }
-    }
+    if (er || ez)
+        return staged(
+            ctx, nn, sizeof(double2),
+            [&](char *half, int64_t first, int64_t count) -> int32_t {
+                double *r = (double *)half, *z = r + count;
+                k_export_field<<<grid_for(count), kBlock, 0, ctx->stream>>>(ctx->e_sc + first, er ? r : nullptr,
+                                                                           ez ? z : nullptr, count);
+                LAUNCHCHK();
+                return MC_OK;
+            },
+            [&](char *half, int64_t first, int64_t count) {
+                const double *r = (const double *)half, *z = r + count;
+                if (er) std::memcpy(er + first, r, count * 8);
+                if (ez) std::memcpy(ez + first, z, count * 8);
+            });
     return MC_OK;
 }
 
