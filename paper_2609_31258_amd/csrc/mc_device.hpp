@@ -117,6 +117,16 @@ struct P64 {
         sincos_turn_tab(u, g_tables.turn, s, c);
     }
     static __device__ __forceinline__ double cos2pi_fast(double u) { return cos_turn_tab(u, g_tables.turn); }
+    // of the uniform variates of random words (step kernels): ln u, ln(u v),
+    // 2 u - 1, sine and cosine of u turns; the root of a positive x
+    static __device__ __forceinline__ double ln_word(uint32_t w) { return mc::ln_word(w, g_tables.ln); }
+    static __device__ __forceinline__ double ln_words(uint32_t w, uint32_t v) { return mc::ln_words(w, v, g_tables.ln); }
+    static __device__ __forceinline__ double sym_word(uint32_t w) { return mc::sym_word(w); }
+    static __device__ __forceinline__ void sc2pi_word(uint32_t w, double *s, double *c) {
+        sincos_word(w, g_tables.turn, s, c);
+    }
+    static __device__ __forceinline__ double cos2pi_word(uint32_t w) { return cos_word(w, g_tables.turn); }
+    static __device__ __forceinline__ double sqrt_pos(double x) { return sqrt_seeded_pos(x, __builtin_amdgcn_rsq(x)); }
 };
 
 // FP32 form: the hardware transcendental instructions (v_log_f32 = log2,
@@ -143,6 +153,12 @@ struct P32 {
     static __device__ __forceinline__ float cos2pi(float u) { return __builtin_amdgcn_cosf(u); }
     static __device__ __forceinline__ void sc2pi_fast(float u, float *s, float *c) { sc2pi(u, s, c); }
     static __device__ __forceinline__ float cos2pi_fast(float u) { return cos2pi(u); }
+    static __device__ __forceinline__ float ln_word(uint32_t w) { return ln(u01(w)); }
+    static __device__ __forceinline__ float ln_words(uint32_t w, uint32_t v) { return ln(u01(w) * u01(v)); }
+    static __device__ __forceinline__ float sym_word(uint32_t w) { return 2.0f * u01(w) - 1.0f; }
+    static __device__ __forceinline__ void sc2pi_word(uint32_t w, float *s, float *c) { sc2pi(u01(w), s, c); }
+    static __device__ __forceinline__ float cos2pi_word(uint32_t w) { return cos2pi(u01(w)); }
+    static __device__ __forceinline__ float sqrt_pos(float x) { return sqrt_(x); }
 };
 
 // Error-free sum a + b = s + e (Knuth), for two-float accumulation.

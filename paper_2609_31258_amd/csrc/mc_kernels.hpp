@@ -395,11 +395,11 @@ __device__ __forceinline__ void langevin_relax(const StepArgs<P, Tab> &a, const 
     const T dt = (T)a.dt, m = (T)sp.m, mg = (T)a.mg;
     const T fm = P::div(mg, m + mg);
     const W4 w = draw(id, a.step, kPurposeLangevin, 0u, k0, k1);
-    const T r0 = P::sqrt_((T)-2 * P::ln_fast(P::u01(w.w0)));
-    const T r1 = P::sqrt_((T)-2 * P::ln_fast(P::u01(w.w2)));
+    const T r0 = P::sqrt_pos((T)-2 * P::ln_word(w.w0));
+    const T r1 = P::sqrt_pos((T)-2 * P::ln_word(w.w2));
     T s0, c0;
-    P::sc2pi_fast(P::u01(w.w1), &s0, &c0);
-    const T c1 = P::cos2pi_fast(P::u01(w.w3));
+    P::sc2pi_word(w.w1, &s0, &c0);
+    const T c1 = P::cos2pi_word(w.w3);
     const T ktm = P::div((T)kB * g.tg, m);  // kB T / m (no underflow in FP32)
     const T gam = (T)(16.0 / 3.0) * g.ngs * P::sqrt_(fm * ktm * (T)0.15915494309189535);
     const T f = P::exp_(-gam * dt);
@@ -440,7 +440,7 @@ __device__ __forceinline__ void collide_explicit(const StepArgs<P, Tab> &a, cons
             break;
         }
         const W4 wa = draw(id, a.step, kPurposeCollide, (uint32_t)(3 * c), k0, k1);
-        const T tau = -P::ln_fast(P::u01(wa.w0)) * inv_lam;
+        const T tau = -P::ln_word(wa.w0) * inv_lam;
         if (!(tau < tleft)) break;
         tleft -= tau;
         ++pc.cand;
@@ -448,13 +448,13 @@ __device__ __forceinline__ void collide_explicit(const StepArgs<P, Tab> &a, cons
         // partner thermal velocity: E = |w|^2/(2 a^2) ~ Gamma(3/2) (Maxwellian branch)
         // or Gamma(2) (flux-weighted branch), isotropic direction; no divergent branch
         const bool maxw = P::u01(wa.w1) * (sv + abar) < sv;  // u < s/(s + abar)
-        const T cc = P::cos2pi_fast(P::u01(wb.w0));
-        const T en = -P::ln_fast(P::u01(wa.w2)) - P::ln_fast(P::u01(wa.w3)) * (maxw ? cc * cc : (T)1);
-        const T wn = ag * P::sqrt_((T)2 * en);
-        const T ct = (T)2 * P::u01(wb.w1) - (T)1;
-        const T st = P::sqrt_(fmax((T)0, (T)1 - ct * ct));
+        const T cc = P::cos2pi_word(wb.w0);
+        const T en = -P::ln_word(wa.w2) - P::ln_word(wa.w3) * (maxw ? cc * cc : (T)1);
+        const T wn = ag * P::sqrt_pos((T)2 * en);
+        const T ct = P::sym_word(wb.w1);
+        const T st = P::sqrt_pos((T)1 - ct * ct);
         T sph, cph;
-        P::sc2pi_fast(P::u01(wb.w2), &sph, &cph);
+        P::sc2pi_word(wb.w2, &sph, &cph);
         const T wx = wn * st * cph, wy = wn * st * sph, wz = wn * ct;
         const T gx = rx - wx, gy = ry - wy, gz = rz - wz;
         const T g2 = gx * gx + gy * gy + gz * gz;
@@ -473,7 +473,7 @@ __device__ __forceinline__ void collide_explicit(const StepArgs<P, Tab> &a, cons
         if (lhs2 < alpha2 * g2) {  // residual u (s + |w|)/|g| < alpha
             ++pc.exch;
             const T te = einstein_t<P>(e + el, skt, theta);
-            etp = -(T)kB * te * P::ln_fast(P::u01(wc.w2) * P::u01(wc.w3));
+            etp = -(T)kB * te * P::ln_words(wc.w2, wc.w3);
             const T de = et - etp;
             if (e + el + de < (T)0) {
                 etp = e + el + et;
@@ -484,10 +484,10 @@ __device__ __forceinline__ void collide_explicit(const StepArgs<P, Tab> &a, cons
                 acc2(e, el, de);
             }
         }
-        const T cchi = (T)2 * P::u01(wc.w0) - (T)1;
-        const T schi = P::sqrt_(fmax((T)0, (T)1 - cchi * cchi));
+        const T cchi = P::sym_word(wc.w0);
+        const T schi = P::sqrt_pos((T)1 - cchi * cchi);
         T sps, cps;
-        P::sc2pi_fast(P::u01(wc.w1), &sps, &cps);
+        P::sc2pi_word(wc.w1, &sps, &cps);
         const T f = fm * P::sqrt_(etp * two_mu);
         vx = vcx + f * schi * cps;
         vy = vcy + f * schi * sps;

@@ -112,23 +112,23 @@ __device__ __forceinline__ Draws<typename P::T> draw_candidate(const StepArgs<P,
     const W4 wa = draw(id, a.step, kPurposeCollide, 3 * c, k0, k1);
     const W4 wb = draw(id, a.step, kPurposeCollide, 3 * c + 1, k0, k1);
     const W4 wc = draw(id, a.step, kPurposeCollide, 3 * c + 2, k0, k1);
-    d.v[DR_WAIT] = -P::ln_fast(P::u01(wa.w0));
+    d.v[DR_WAIT] = -P::ln_word(wa.w0);
     d.v[DR_BRANCH] = P::u01(wa.w1);
-    const T cc = P::cos2pi_fast(P::u01(wb.w0));
-    const T la = P::ln_fast(P::u01(wa.w2)), lb = P::ln_fast(P::u01(wa.w3));
+    const T cc = P::cos2pi_word(wb.w0);
+    const T la = P::ln_word(wa.w2), lb = P::ln_word(wa.w3);
     const T ef = -la - lb * (T)1, em = -la - lb * (cc * cc);
-    d.v[DR_WFLUX] = ag * P::sqrt_((T)2 * ef);
-    d.v[DR_WMAXW] = ag * P::sqrt_((T)2 * em);
-    const T ct = (T)2 * P::u01(wb.w1) - (T)1;
-    d.v[DR_ST] = P::sqrt_(fmax((T)0, (T)1 - ct * ct));
+    d.v[DR_WFLUX] = ag * P::sqrt_pos((T)2 * ef);
+    d.v[DR_WMAXW] = ag * P::sqrt_pos((T)2 * em);
+    const T ct = P::sym_word(wb.w1);
+    d.v[DR_ST] = P::sqrt_pos((T)1 - ct * ct);
     d.v[DR_CT] = ct;
-    P::sc2pi_fast(P::u01(wb.w2), &d.v[DR_SPH], &d.v[DR_CPH]);
+    P::sc2pi_word(wb.w2, &d.v[DR_SPH], &d.v[DR_CPH]);
     d.v[DR_ACC] = P::u01(wb.w3);
-    const T cchi = (T)2 * P::u01(wc.w0) - (T)1;
-    d.v[DR_SCHI] = P::sqrt_(fmax((T)0, (T)1 - cchi * cchi));
+    const T cchi = P::sym_word(wc.w0);
+    d.v[DR_SCHI] = P::sqrt_pos((T)1 - cchi * cchi);
     d.v[DR_CCHI] = cchi;
-    P::sc2pi_fast(P::u01(wc.w1), &d.v[DR_SPS], &d.v[DR_CPS]);
-    d.v[DR_LNX] = P::ln_fast(P::u01(wc.w2) * P::u01(wc.w3));
+    P::sc2pi_word(wc.w1, &d.v[DR_SPS], &d.v[DR_CPS]);
+    d.v[DR_LNX] = P::ln_words(wc.w2, wc.w3);
     return d;
 }
 

@@ -142,3 +142,46 @@ def test_restricted_functions_within_two_ulp(tmp_path):
     out = subprocess.run([str(exe)], capture_output=True, text=True, check=True).stdout.strip()
     print(out)
     assert out.startswith("OK"), out
+
+
+WORD_HARNESS = r'''
+#include "mc_math64.hpp"
+#include <cstdint>
+#include <cstdio>
+#include <random>
+int main() {
+    static mc::StepTables t;
+    mc::step_tables_fill(&t);
+    std::mt19937_64 rng(9);
+    long bad[4] = {0, 0, 0, 0};
+    for (long k = 0; k < 4000000; ++k) {
+        // the ends of the range, both sides of every node and bin edge, and at random
+        uint32_t w = (uint32_t)rng();
+        if (k < 100000) w = (uint32_t)k;
+        else if (k < 200000) w = ~(uint32_t)(k - 100000);
+        else if (k < 1000000) w = ((uint32_t)(k - 200000) << 15) + (uint32_t)(rng() % 5) - 2u;
+        const uint32_t v = (uint32_t)rng();
+        const double u = ((double)w + 0.5) * 0x1p-32, uv = ((double)v + 0.5) * 0x1p-32;
+        double s, c, sw, cw;
+        mc::sincos_turn_tab(u, t.turn, &s, &c);
+        mc::sincos_word(w, t.turn, &sw, &cw);
+        bad[0] += mc::ln_word(w, t.ln) != mc::ln_tab(u, t.ln);
+        bad[1] += mc::ln_words(w, v, t.ln) != mc::ln_tab(u * uv, t.ln);
+        bad[2] += s != sw || c != cw || mc::cos_word(w, t.turn) != c;
+        bad[3] += mc::sym_word(w) != 2.0 * u - 1.0;
+    }
+    std::printf("%ld %ld %ld %ld\n", bad[0], bad[1], bad[2], bad[3]);
+    return bad[0] || bad[1] || bad[2] || bad[3];
+}
+'''
+
+
+def test_word_functions_equal_the_functions_of_the_uniform(tmp_path):
+    """The functions of a random word equal the table functions of its uniform variate bit for bit."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    src, exe = tmp_path / "words.cpp", tmp_path / "words"
+    src.write_text(WORD_HARNESS)
+    subprocess.run(["g++", "-O2", "-mfma", "-ffp-contract=off", "-std=c++17", "-I",
+                    os.path.join(root, "paper_2609_31258_amd", "csrc"), "-o", str(exe), str(src)], check=True)
+    r = subprocess.run([str(exe)], capture_output=True, text=True)
+    assert r.returncode == 0, r.stdout
