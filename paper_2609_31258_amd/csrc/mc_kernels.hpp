@@ -180,15 +180,6 @@ __device__ __forceinline__ int block_query(const int32_t *prefix, int32_t nq) {
     return lo;
 }
 
-template <class P, class Tab>
-__global__ __launch_bounds__(256) void k_emit_multi(const EmitArgs<P, Tab> *descs, const int32_t *prefix,
-                                                    int32_t nq) {
-    const int q = block_query(prefix, nq);
-    const EmitArgs<P, Tab> &a = descs[q];
-    const int64_t k = (int64_t)(blockIdx.x - prefix[q]) * blockDim.x + threadIdx.x;
-    if (k < a.count) emit_one(a, k);
-}
-
 // ---------------------------------------------------------------------------
 // Fused step.
 // ---------------------------------------------------------------------------
@@ -882,12 +873,13 @@ static __global__ __launch_bounds__(kHotRep) void k_dt_reset(unsigned long long 
 }
 
 // All resident queries of a server advance one step in one launch; each
-// block belongs to one query (descriptors in device memory).
-template <class P, class Tab>
-__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_multi(const StepArgs<P, Tab> *descs, const int32_t *prefix,
-                                                    int32_t nq) {
+// block belongs to one query (descriptors in device memory, whose member a is
+// the query's).
+template <class P, class Tab, class Desc>
+__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_multi(const Desc *descs, const int32_t *prefix,
+                                                                            int32_t nq) {
     const int q = block_query(prefix, nq);
-    const StepArgs<P, Tab> &a = descs[q];
+    const StepArgs<P, Tab> &a = descs[q].a;
     P::prepare_tables(a.tables);
     StepCount n{0, 0, 0, 0, 0, 0, 0};
     // the random key is the query's, the same for the whole block: scalar.

@@ -483,24 +483,7 @@ static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, do
     return MC_OK;
 }
 
-// Lanes per pack of the stretch kernel for a launch of `steps` steps over n
-// slots, or 0 where k_step is the faster kernel.
-//
-// Lanes: the most, up to 16, that leave one wavefront per SIMD (65536 lanes);
-// the FP32 form's candidates cost less of what the lanes share out than of
-// what each repeats, and two wavefronts per SIMD still gain (FP64 form at
-// 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form at 3.2e4 packs: 4 lanes
-// 25 us, 2 lanes 27 us).  On the Langevin branch there is nothing to share.
-//
-// One lane per pack, several steps: wherever the collision loop does not
-// dominate -- the Langevin branch, or gas so thin that a step draws few
-// candidates (kThinGas) -- and up to the populations where k_step's larger
-// occupancy (three wavefronts per SIMD in the FP64 form, five in the FP32
-// form) outweighs the end of its launches: FP64 3e5 packs 380 against 380 us
-// and 6e5 packs 716 against 669, FP32 6e5 packs 301 against 305 us and 1e6
-// 479 against 468.
-constexpr int64_t kStretchLanes = 65536;
-constexpr int64_t kStretchPacks64 = 300000, kStretchPacks32 = 700000;
+// Candidates per step below which gas counts as thin (lanes_for).
 constexpr double kThinGas = 16.0;
 
 // Largest candidate count per step that the gas, the ions and the step allow
@@ -512,17 +495,11 @@ static double densest_step(const mc_ctx *ctx) {
     return ctx->op.collisions_on ? ctx->gas_n_max * ccs * abar * ctx->op.dt : 0.0;
 }
 
+// Lanes per pack of the stretch kernel for a launch of `steps` steps over n
+// slots, or 0 for k_step (with one lane, a single step is k_step's).
 static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
-    if (n <= 0) return 0;
-    const int64_t lanes = ctx->fp32() && !ctx->op.langevin_on ? 2 * kStretchLanes : kStretchLanes;
-    int g = 16;
-    while (g > 1 && n * g > lanes) g >>= 1;
-    if (g > 1) return g;
-    if (steps < 2) return 0;
-    return ctx->op.langevin_on || n <= (ctx->fp32() ? kStretchPacks32 : kStretchPacks64) ||
-                   densest_step(ctx) < kThinGas
-               ? 1
-               : 0;
+    const int g = lanes_for(ctx->fp32(), ctx->op.langevin_on, densest_step(ctx) < kThinGas, n);
+    return g == 1 && steps < 2 ? 0 : g;
 }
 
 template <class P, class Tab>

@@ -1,10 +1,11 @@
 // mc_server.hip -- serving runtime: continuous batching of design queries.
 //
 // One worker thread per server runs rounds of: admit (FIFO, pool permitting)
-// -> steps_per_sync co-steps -> synchronise -> retire finished queries.  A
-// co-step advances every resident query by one step: per-query space-charge
-// updates where due, one multi-query emission launch, one multi-query step
-// launch.  Launch descriptors go through a ring of pinned host buffers and
+// -> steps_per_sync steps of every resident query -> synchronise -> retire
+// finished queries.  A co-step is one multi-query emission launch and one
+// multi-query step launch, in which each query goes as far as it can on its
+// own: to its next space-charge update or snapshot, whose launches come before
+// the next co-step (adaptive queries: one step).  Launch descriptors go through a ring of pinned host buffers and
 // device buffers, each guarded by an event, so the host never overwrites a
 // descriptor the GPU has not read yet.
 #include <hip/hip_runtime.h>
@@ -24,13 +25,14 @@
 #include "mc_kernels.hpp"
 #include "mc_poisson.hpp"
 #include "mc_pool.hpp"
+#include "mc_stretch.hpp"
 
 using namespace mc;
 
 namespace {
 
 constexpr int kBlk = 256;
-constexpr int kRing = 8;
+constexpr int kRing = 4;
 constexpr int64_t kAggMax = 1024;
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlk - 1) / kBlk); }
@@ -47,6 +49,7 @@ struct Query {
     Species sp{};
     Src src{};
     int64_t n_slots = 0, step = 0, emitted_n = 0, emitted_w = 0, partial_len = 0;
+    int64_t left = 0;  // steps it may still take in this round
     // device views into the query's pool block
     PackPtrs<double> p64{};
     PackPtrs<float> p32{};
@@ -511,9 +514,65 @@ static int32_t adaptive_steps(mc_server *S, std::vector<Query *> &act) {
     return MC_OK;
 }
 
+// A query's part of a co-step: its arguments over the steps from its step on
+// that the co-step takes, as many as `most`, ending before its next
+// space-charge update or snapshot; the packs each of them emits (on a copy of
+// its source).
+template <class P, class Tab>
+static void plan_query(mc_server *S, const Query &Q, int64_t most, StretchArgs<P, Tab> &sd,
+                       EmitStretchArgs<P, Tab> &ed, Src &src) {
+    const mc_operating &op = Q.q.op;
+    int64_t k = std::min<int64_t>(most, op.adaptive ? 1 : kStretchMax);
+    const auto until = [&](int32_t every) {
+        if (every > 0) k = std::min<int64_t>(k, every - Q.step % every);
+    };
+    if (op.sc_on) until(op.sc_every);
+    if (op.sample_stride > 0 && Q.q.sample_capacity > 0) until(op.sample_every);
+    src = Q.src;
+    StretchSteps &st = sd.st;
+    EmitSteps &em = ed.st;
+    st.n = em.n = (int32_t)k;
+    em.first[0] = 0;
+    int64_t n = Q.n_slots;
+    for (int32_t j = 0; j < k; ++j) {
+        int64_t c = src.in.kind == 0 ? (Q.step + j == 0 ? src.in.n_total : 0) : due(src, Q.step + j);
+        c = std::max<int64_t>(0, std::min(c, src.in.n_total - src.emitted));
+        em.slot0[j] = n;
+        em.first[j + 1] = em.first[j] + c;
+        src.emitted += c;
+        n += c;
+        const double t0 = op.adaptive ? Q.t : (double)(Q.step + j) * op.dt;
+        double rf[3];
+        rf_stages_at(op, t0, op.adaptive ? Q.dt_now : op.dt, rf);
+        st.t0[j] = t0;
+        st.c0[j] = rf[0];
+        st.ch[j] = rf[1];
+        st.c1[j] = rf[2];
+        st.n_slots[j] = n;
+    }
+}
+
+// What a step of a query's packs costs, to order the queries of a launch by:
+// the long ones go first, or the launch ends with their wavefronts alone on
+// the chip.  (The queries share the gas, so their collision rates go with the
+// cross section and the step; on the Langevin branch there are no candidates.)
+static double step_cost(const Query &Q) {
+    const mc_operating &op = Q.q.op;
+    return op.langevin_on || !op.collisions_on ? 0.0 : Q.q.ion.ccs_m2 * (op.adaptive ? Q.dt_now : op.dt);
+}
+
+template <class P, class Tab, int G>
+static void launch_multi(mc_server *S, unsigned blocks, const StretchArgs<P, Tab> *d, const int32_t *prefix, int n) {
+    k_stretch_multi<P, Tab, G><<<blocks, 64, 0, S->stream>>>(d, prefix, n);
+}
+
+// One co-step of the queries `act`, each of which may take Q.left more steps
+// this round.
 template <class P, class Tab>
 static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     using D = typename P::T;
+    using Emit = EmitStretchArgs<P, Tab>;
+    using Steps = StretchArgs<P, Tab>;
     const int32_t maxres = S->opt.max_resident;
     // ring slot: wait until the GPU has consumed its previous contents
     const int slot = S->ring_pos;
@@ -523,32 +582,51 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     char *d = S->d_ring + slot * S->ring_slot;
     const size_t pre = (size_t)Pool::round_up(2 * (maxres + 1) * sizeof(int32_t));
     int32_t *pe = (int32_t *)h, *ps = pe + (maxres + 1);
-    EmitArgs<P, Tab> *ed = (EmitArgs<P, Tab> *)(h + pre);
-    StepArgs<P, Tab> *sd = (StepArgs<P, Tab> *)(h + pre + maxres * sizeof(EmitArgs<P, Tab>));
+    Emit *ed = (Emit *)(h + pre);
+    Steps *sd = (Steps *)(h + pre + maxres * sizeof(Emit));
     int ne = 0, ns = 0, be = 0, bs = 0;
     int32_t rc0 = adaptive_steps<P, Tab>(S, act);
     if (rc0) return rc0;
     for (Query *Qp : act) {
         Query &Q = *Qp;
+        if (Q.fail_code || Q.q.op.adaptive) continue;
+        int32_t rc = sample_query<P, Tab>(S, Q);
+        if (rc) return rc;
+        if (Q.q.op.sc_on && Q.step % Q.q.op.sc_every == 0) {
+            rc = pic_query<P, Tab, D>(S, Q, packs_of<P, Tab>(Q));
+            if (rc) return rc;
+        }
+    }
+    std::stable_sort(act.begin(), act.end(),
+                     [](const Query *a, const Query *b) { return step_cost(*a) > step_cost(*b); });
+    // the lanes that all queries' packs together leave to each
+    int64_t total = 0;
+    bool langevin = true;
+    for (const Query *Q : act) {
+        if (Q->fail_code) continue;
+        total += std::min<int64_t>(Q->q.source.n_total,
+                                   Q->n_slots + (Q->src.in.kind == 1 ? Q->src.in.packs_per_step : 0));
+        langevin = langevin && step_cost(*Q) == 0.0;
+    }
+    const int lanes = lanes_for(S->fp32(), langevin, false, total);
+    for (Query *Qp : act) {
+        Query &Q = *Qp;
         if (Q.fail_code) continue;
-        if (!Q.q.op.adaptive) {
-            int32_t rc = sample_query<P, Tab>(S, Q);
-            if (rc) return rc;
-        }
-        if (!Q.q.op.adaptive && Q.q.op.sc_on && Q.step % Q.q.op.sc_every == 0) {
-            int32_t rc = pic_query<P, Tab, D>(S, Q, packs_of<P, Tab>(Q));
-            if (rc) return rc;
-        }
-        int64_t cnt = (Q.src.in.kind == 0) ? (Q.step == 0 ? Q.src.in.n_total : 0) : due(Q.src, Q.step);
-        cnt = std::min(cnt, Q.src.in.n_total - Q.src.emitted);
-        if (cnt > 0) {
-            EmitArgs<P, Tab> a{};
+        Src src;
+        Steps &sa = sd[ns];
+        Emit &ea = ed[ne];
+        plan_query<P, Tab>(S, Q, lanes ? Q.left : 1, sa, ea, src);
+        const int32_t k = sa.st.n;
+        const int64_t emitted = ea.st.first[k], n_end = sa.st.n_slots[k - 1];
+        if (emitted > 0) {
+            EmitArgs<P, Tab> &a = ea.a;
+            a = EmitArgs<P, Tab>{};
             a.p = packs_of<P, Tab>(Q);
             a.gtab = static_cast<const Tab *>(S->gtab);
             std::memcpy(a.gsc, S->gsc, sizeof(a.gsc));
             a.sp = Q.sp_dev;
             a.slot0 = Q.n_slots;
-            a.count = cnt;
+            a.count = emitted;
             a.id0 = Q.src.emitted;
             a.step = Q.step;
             a.sigma_r = Q.src.in.sigma_r;
@@ -563,37 +641,43 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
             a.ion = 0;
             a.k0 = (uint32_t)Q.q.seed;
             a.k1 = (uint32_t)(Q.q.seed >> 32);
-            pe[ne] = be;
-            ed[ne++] = a;
-            be += (int)blocks_for(cnt);
-            Q.n_slots += cnt;
-            Q.src.emitted += cnt;
-            Q.emitted_n += cnt;
-            Q.emitted_w += cnt * Q.src.w_fx;
+            pe[ne++] = be;
+            be += (int)blocks_for(emitted);
+            Q.emitted_n += emitted;
+            Q.emitted_w += emitted * Q.src.w_fx;
         }
-        if (Q.n_slots > 0) {
-            const StepArgs<P, Tab> a = Q.q.op.adaptive ? query_step_args<P, Tab>(S, Q, Q.t, Q.dt_now)
-                                                       : query_step_args<P, Tab>(S, Q, (double)Q.step * Q.q.op.dt,
-                                                                                 Q.q.op.dt);
-            ps[ns] = bs;
-            sd[ns++] = a;
-            bs += (int)((Q.n_slots + kStepBlk - 1) / kStepBlk);
+        Q.n_slots = n_end;
+        Q.src = src;
+        if (n_end > 0) {
+            sa.a = query_step_args<P, Tab>(S, Q, sa.st.t0[0], Q.q.op.adaptive ? Q.dt_now : Q.q.op.dt);
+            ps[ns++] = bs;
+            const int64_t per = 64 / (lanes ? lanes : 1);
+            bs += (int)((n_end + per - 1) / per);
         }
         if (Q.q.op.adaptive) Q.t += Q.dt_now;
-        Q.step++;
+        Q.step += k;
+        Q.left -= k;
     }
     pe[ne] = be;
     ps[ns] = bs;
-    const size_t used = pre + maxres * sizeof(EmitArgs<P, Tab>) + ns * sizeof(StepArgs<P, Tab>);
-    SCHK(hipMemcpyAsync(d, h, used, hipMemcpyHostToDevice, S->stream));
+    SCHK(hipMemcpyAsync(d, h, pre + ne * sizeof(Emit), hipMemcpyHostToDevice, S->stream));
+    const size_t at = pre + maxres * sizeof(Emit);
+    if (ns > 0) SCHK(hipMemcpyAsync(d + at, h + at, ns * sizeof(Steps), hipMemcpyHostToDevice, S->stream));
     const int32_t *dpe = (const int32_t *)d, *dps = dpe + (maxres + 1);
     if (ne > 0) {
-        k_emit_multi<P, Tab><<<be, kBlk, 0, S->stream>>>((const EmitArgs<P, Tab> *)(d + pre), dpe, ne);
+        k_emit_stretch_multi<P, Tab><<<be, kBlk, 0, S->stream>>>((const Emit *)(d + pre), dpe, ne);
         SCHK(hipGetLastError());
     }
     if (ns > 0) {
-        k_step_multi<P, Tab><<<bs, kStepBlk, 0, S->stream>>>(
-            (const StepArgs<P, Tab> *)(d + pre + maxres * sizeof(EmitArgs<P, Tab>)), dps, ns);
+        const Steps *dsd = (const Steps *)(d + at);
+        switch (lanes) {
+        case 0: k_step_multi<P, Tab><<<bs, kStepBlk, 0, S->stream>>>(dsd, dps, ns); break;
+        case 1: launch_multi<P, Tab, 1>(S, bs, dsd, dps, ns); break;
+        case 2: launch_multi<P, Tab, 2>(S, bs, dsd, dps, ns); break;
+        case 4: launch_multi<P, Tab, 4>(S, bs, dsd, dps, ns); break;
+        case 8: launch_multi<P, Tab, 8>(S, bs, dsd, dps, ns); break;
+        default: launch_multi<P, Tab, 16>(S, bs, dsd, dps, ns); break;
+        }
         SCHK(hipGetLastError());
     }
     SCHK(hipEventRecord(S->ring_ev[slot], S->stream));
@@ -727,10 +811,11 @@ static int32_t worker_round(mc_server *S) {
         std::lock_guard<std::mutex> lk(S->mu);
         act = S->resident;
     }
-    for (int k = 0; k < S->opt.steps_per_sync; ++k) {
+    for (Query *Q : act) Q->left = std::min<int64_t>(S->opt.steps_per_sync, Q->q.n_steps - Q->step);
+    for (;;) {
         std::vector<Query *> live;
         for (Query *Q : act)
-            if (Q->step < Q->q.n_steps && !Q->fail_code) live.push_back(Q);
+            if (Q->left > 0 && !Q->fail_code) live.push_back(Q);
         if (live.empty()) break;
         int32_t rc = co_step<P, Tab>(S, live);
         if (rc) return rc;
@@ -926,10 +1011,10 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
         for (int k = 0; k < 4; ++k) S->esc[k] = mx[k] > 0 ? (float)mx[k] : 1.0f;
     }
     // descriptor ring (pinned host + device)
-    const size_t emit_sz = S->fp32() ? (S->bf16() ? sizeof(EmitArgs<P32, bf16x4>) : sizeof(EmitArgs<P32, float4>))
-                                     : sizeof(EmitArgs<P64, double4>);
-    const size_t step_sz = S->fp32() ? (S->bf16() ? sizeof(StepArgs<P32, bf16x4>) : sizeof(StepArgs<P32, float4>))
-                                     : sizeof(StepArgs<P64, double4>);
+    const size_t emit_sz = S->fp32() ? (S->bf16() ? sizeof(EmitStretchArgs<P32, bf16x4>) : sizeof(EmitStretchArgs<P32, float4>))
+                                     : sizeof(EmitStretchArgs<P64, double4>);
+    const size_t step_sz = S->fp32() ? (S->bf16() ? sizeof(StretchArgs<P32, bf16x4>) : sizeof(StretchArgs<P32, float4>))
+                                     : sizeof(StretchArgs<P64, double4>);
     S->ring_slot = (size_t)Pool::round_up((int64_t)(Pool::round_up(2 * (o->max_resident + 1) * sizeof(int32_t)) +
                                                     o->max_resident * (emit_sz + step_sz)));
     if (hipHostMalloc((void **)&S->h_ring, kRing * S->ring_slot, hipHostMallocDefault) != hipSuccess)

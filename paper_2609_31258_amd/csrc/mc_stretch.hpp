@@ -245,23 +245,25 @@ constexpr int stretch_waves() {
     return P::kTwo ? 3 : 2;
 }
 
-// One wavefront per block, 64 / G packs each.  The arguments are read afresh
-// in every step, through a pointer that the compiler cannot see through: left
-// to itself it keeps all of them, and what it makes of them, in registers
-// across the steps (some 130 scalar registers spilled; 40 this way in the
-// FP64 form and 8 in the FP32 form).
+// One wavefront, 64 / G packs: those of place `block` of the launch.  The
+// arguments are read afresh in every step, through a pointer that the compiler
+// cannot see through: left to itself it keeps all of them, and what it makes
+// of them, in registers across the steps (some 130 scalar registers spilled;
+// 40 this way in the FP64 form and 8 in the FP32 form).
+template <class P, class Tab>
+using ConstArgs = const __attribute__((address_space(4))) StretchArgs<P, Tab> *;
+
 template <class P, class Tab, int G>
-__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArgs<P, Tab> args) {
+__device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t block) {
     using T = typename P::T;
-    using Kernarg = const __attribute__((address_space(4))) StretchArgs<P, Tab> *;
     __shared__ T lds[G > 1 ? DR_N : 1][64];
-    Kernarg kernarg = (Kernarg)__builtin_amdgcn_kernarg_segment_ptr();
+    const auto &args = *(const StretchArgs<P, Tab> *)from;
     const double *const dyn = args.a.dyn;  // an adaptive run's single step: its record on the device (k_step)
     if (dyn && !(dyn[1] > 0.0)) return;
     const int32_t n_steps = args.st.n;
     P::prepare_tables(args.a.tables);
     const int lane = threadIdx.x & 63, sub = lane & (G - 1), col = lane & ~(G - 1);
-    const int64_t s = (int64_t)blockIdx.x * (64 / G) + lane / G;
+    const int64_t s = block * (64 / G) + lane / G;
     StepCount n{0, 0, 0, 0, 0, 0, 0};
     int32_t status = -1, tag = 0;
     Motion<T> m{};
@@ -295,8 +297,8 @@ __global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArg
     T te = (T)0;
     if (mine) te = einstein_t<P>(e + el, (T)args.a.sp[tag].skt, (T)args.a.sp[tag].theta);
     for (int32_t j = 0; j < n_steps; ++j) {
-        asm volatile("" : "+s"(kernarg));
-        const auto &now = *(const StretchArgs<P, Tab> *)kernarg;
+        asm volatile("" : "+s"(from));
+        const auto &now = *(const StretchArgs<P, Tab> *)from;
         StepArgs<P, Tab> a = now.a;
         const StretchSteps &st = now.st;
         const uint32_t k0 = a.k0, k1 = a.k1;
@@ -394,7 +396,7 @@ __global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArg
         }
         if (__ballot(n.cand >> 24) != 0ull) flush_stretch(a.t, n);
     }
-    const StepArgs<P, Tab> &a = ((const StretchArgs<P, Tab> *)kernarg)->a;
+    const StepArgs<P, Tab> &a = ((const StretchArgs<P, Tab> *)from)->a;
     if (mine && sub == 0) {
         const PackPtrs<T> &p = a.p;
         p.x[s] = m.x;
@@ -416,6 +418,20 @@ __global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArg
     flush_stretch(a.t, n);
 }
 
+template <class P, class Tab, int G>
+__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArgs<P, Tab>) {
+    stretch_packs<P, Tab, G>((ConstArgs<P, Tab>)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x);
+}
+
+// The resident queries of a server, each over its own steps; each block
+// belongs to one query (descriptors in device memory).
+template <class P, class Tab, int G>
+__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch_multi(const StretchArgs<P, Tab> *descs,
+                                                                            const int32_t *prefix, int32_t nq) {
+    const int q = __builtin_amdgcn_readfirstlane(block_query(prefix, nq));
+    stretch_packs<P, Tab, G>((ConstArgs<P, Tab>)(uintptr_t)(descs + q), (int64_t)blockIdx.x - prefix[q]);
+}
+
 // Emission of one source over the steps of a stretch in one launch: step j
 // emits the packs [first[j], first[j + 1]) of this launch into the slots from
 // slot0[j] on.
@@ -424,9 +440,9 @@ struct EmitSteps {
     int64_t first[kStretchMax + 1], slot0[kStretchMax];
 };
 
+// Pack k of the launch.
 template <class P, class Tab>
-__global__ __launch_bounds__(256) void k_emit_stretch(EmitArgs<P, Tab> a, EmitSteps st) {
-    const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void emit_in_stretch(EmitArgs<P, Tab> a, const EmitSteps &st, int64_t k) {
     if (k >= st.first[st.n]) return;
     int32_t j = 0;
     while (k >= st.first[j + 1]) ++j;
@@ -434,6 +450,50 @@ __global__ __launch_bounds__(256) void k_emit_stretch(EmitArgs<P, Tab> a, EmitSt
     a.step += j;
     a.slot0 = st.slot0[j] - st.first[j];
     emit_one(a, k);
+}
+
+template <class P, class Tab>
+__global__ __launch_bounds__(256) void k_emit_stretch(EmitArgs<P, Tab> a, EmitSteps st) {
+    emit_in_stretch(a, st, (int64_t)blockIdx.x * blockDim.x + threadIdx.x);
+}
+
+// The sources of a server's queries.
+template <class P, class Tab>
+struct EmitStretchArgs {
+    EmitArgs<P, Tab> a;
+    EmitSteps st;
+};
+
+template <class P, class Tab>
+__global__ __launch_bounds__(256) void k_emit_stretch_multi(const EmitStretchArgs<P, Tab> *descs,
+                                                            const int32_t *prefix, int32_t nq) {
+    const int q = block_query(prefix, nq);
+    emit_in_stretch(descs[q].a, descs[q].st, (int64_t)(blockIdx.x - prefix[q]) * blockDim.x + threadIdx.x);
+}
+
+// Lanes per pack for a launch of several steps over n slots, or 0 where the
+// step kernels, one step a launch, are the faster ones.
+//
+// Lanes: the most, up to 16, that leave one wavefront per SIMD (65536 lanes);
+// the FP32 form's candidates cost less of what the lanes share out than of
+// what each repeats, and two wavefronts per SIMD still gain (FP64 form at
+// 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form at 3.2e4 packs: 4 lanes
+// 25 us, 2 lanes 27 us).  On the Langevin branch there is nothing to share.
+//
+// One lane per pack: wherever the collision loop does not dominate -- the
+// Langevin branch, or gas so thin that a step draws few candidates -- and up
+// to the populations where the step kernel's larger occupancy (three
+// wavefronts per SIMD in the FP64 form, five in the FP32 form) outweighs the
+// end of its launches: FP64 3e5 packs 380 against 380 us and 6e5 packs 716
+// against 669, FP32 6e5 packs 301 against 305 us and 1e6 479 against 468.
+constexpr int64_t kStretchLanes = 65536;
+constexpr int64_t kStretchPacks64 = 300000, kStretchPacks32 = 700000;
+inline int lanes_for(bool fp32, bool langevin, bool thin, int64_t n) {
+    if (n <= 0) return 0;
+    const int64_t lanes = fp32 && !langevin ? 2 * kStretchLanes : kStretchLanes;
+    int g = 16;
+    while (g > 1 && n * g > lanes) g >>= 1;
+    return g > 1 || langevin || thin || n <= (fp32 ? kStretchPacks32 : kStretchPacks64) ? g : 0;
 }
 
 }  // namespace mc
