@@ -203,6 +203,9 @@ struct StepArgs {
     // k_dt_finish -- (t0, dt, c0, ch, c1) of this step, then t0 and c0 of
     // the next -- read in place of the fields above; null with a fixed step
     const double *dyn;
+    // the blocks take the slots from the last one down (sorted slots whose last
+    // species collide most: the launch then ends with its short wavefronts)
+    int32_t from_last;
 };
 
 // Total field of Eq. 4 at (x, y, z), radial part projected by Eq. 3
@@ -724,7 +727,8 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step(StepArgs<P
     }
     P::prepare_tables(a.tables);
     StepCount n{0, 0, 0, 0, 0, 0, 0};
-    step_one<P, Tab, kOneSpecies>(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, n, a.k0, a.k1);
+    const unsigned block = !kOneSpecies && a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    step_one<P, Tab, kOneSpecies>(a, (int64_t)block * blockDim.x + threadIdx.x, n, a.k0, a.k1);
     flush_counts(a.t, n);
 }
 

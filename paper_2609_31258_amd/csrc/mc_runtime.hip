@@ -463,6 +463,10 @@ static StepArgs<P, Tab> step_args(mc_ctx *ctx, PackPtrs<typename P::T> p, double
     a.lv_dt_ref = op.dt;
     a.k0 = (uint32_t)ctx->opt.seed;
     a.k1 = (uint32_t)(ctx->opt.seed >> 32);
+    // sorted slots lie in the order of the species; in one gas their collision
+    // rates go with their cross sections.  Ten species from 200 to 5e4 Da, 8e5
+    // packs: 317 us a step from the lightest on, 247 us from the heaviest
+    a.from_last = op.sort_every > 0 && ctx->ions.size() > 1 && ctx->ions.back().ccs_m2 > ctx->ions.front().ccs_m2;
     return a;
 }
 

@@ -419,8 +419,9 @@ __device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t bl
 }
 
 template <class P, class Tab, int G>
-__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArgs<P, Tab>) {
-    stretch_packs<P, Tab, G>((ConstArgs<P, Tab>)__builtin_amdgcn_kernarg_segment_ptr(), blockIdx.x);
+__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArgs<P, Tab> args) {
+    stretch_packs<P, Tab, G>((ConstArgs<P, Tab>)__builtin_amdgcn_kernarg_segment_ptr(),
+                             args.a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
 }
 
 // The resident queries of a server, each over its own steps; each block

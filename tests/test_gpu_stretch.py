@@ -42,6 +42,10 @@ def _scenario(name):
         srcs = [synth.Source(kind=1, ion=1, current_a=1e-9, packs_per_step=37, n_total=300),
                 synth.Source(kind=2, ion=2, current_a=2e-9, weight=0.31, n_total=10_000, step_start=2)]
         snap["id"] += 1 << 50
+    elif name == "sorted":  # blocks from the last slot down (the last species collides most)
+        ions = synth.config_c5_species(3)
+        snap["tag"] = (np.arange(N) % 3).astype(np.int32)
+        op.sort_every = 2
     elif name == "window":
         op.langevin_on, op.lv_z_lo, op.lv_z_hi = 1, 1e-3, 3e-3
     elif name == "vacuum":
@@ -62,7 +66,7 @@ def _run(case, prec, tables, snap, per_call):
     return p, t, e
 
 
-@pytest.mark.parametrize("name", ["dense", "exits", "species", "window", "vacuum"])
+@pytest.mark.parametrize("name", ["dense", "exits", "species", "sorted", "window", "vacuum"])
 @pytest.mark.parametrize("prec,tables", [(0, False), (1, False), (1, True)])
 def test_stretch_equals_single_steps(name, prec, tables):
     _say("stretch", name, "fp32" if prec else "fp64", "fp32 tables" if tables else "")
