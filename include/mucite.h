@@ -361,10 +361,9 @@ int32_t mc_inject(mc_ctx *ctx, int32_t src_id, int64_t n);
  * observables"), collisions (Eq. 6 and the internal-energy exchange) or the
  * hybrid Langevin relaxation, and the dissociation hazard (Eq. 7).
  * Asynchronous with a fixed step.  With the adaptive step (Eq. 1) each
- * step's length is found on the device and the step kernels read it there;
- * the call reads the step record back once per stretch of steps before a
- * space-charge update could fall due, and at its end (while a source still
- * emits, whose Eq. 5 counts need each length on the host, once per step).
+ * step's length is found on the device by the step kernels themselves; the
+ * call reads the record of where the run stands back once per stretch of steps
+ * before a space-charge update, and at its end (while a source still emits, whose Eq. 5 counts need each length on the host, once per step).
  * Errors: MC_ESTATE, MC_ENOMEM (capacity), MC_ENUMERIC (adaptive step
  * collapsed; the step counter and time stay at the collapsed step),
  * MC_EDEVICE. */

@@ -199,10 +199,6 @@ struct StepArgs {
     double lv_z_lo, lv_z_hi, lv_switch, lv_dt_ref;  // switch: lambda lv_dt_ref >= lv_switch
     uint32_t k0, k1;
     const StepTables *tables;  // the FP64 step's logarithm and turn tables (device memory)
-    // adaptive step kept on the device: the step record written by
-    // k_dt_finish -- (t0, dt, c0, ch, c1) of this step, then t0 and c0 of
-    // the next -- read in place of the fields above; null with a fixed step
-    const double *dyn;
     // the blocks take the slots from the last one down (sorted slots whose last
     // species collide most: the launch then ends with its short wavefronts)
     int32_t from_last;
@@ -714,17 +710,6 @@ constexpr int step_waves() {
 
 template <class P, class Tab, bool kOneSpecies>
 __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step(StepArgs<P, Tab> a) {
-    if (a.dyn) {
-        // the step's time, length and RF stage coefficients from the device
-        // record; a zero length marks an adaptive run halted by a collapsed
-        // step (every thread returns: no barrier is left waiting)
-        if (!(a.dyn[1] > 0.0)) return;
-        a.t0 = a.dyn[0];
-        a.dt = a.dyn[1];
-        a.c0 = a.dyn[2];
-        a.ch = a.dyn[3];
-        a.c1 = a.dyn[4];
-    }
     P::prepare_tables(a.tables);
     StepCount n{0, 0, 0, 0, 0, 0, 0};
     const unsigned block = !kOneSpecies && a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
@@ -733,67 +718,98 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step(StepArgs<P
 }
 
 // ---------------------------------------------------------------------------
-// Adaptive step (Eq. 1): the per-pack limits at the start of a step (state at
-// t0, RF coefficient c0), minimised over the block and added into one of
-// kHotRep replica lines: word 0 holds the limit's bits (positive doubles
-// order like their bit patterns), word 1 flags a pack on the Langevin
-// branch.  Per pack: half a spacing over |v|; a tenth of the speed scale
+// Adaptive step (Eq. 1): a pack's limit at the start of a step (state at t0,
+// RF coefficient c0): half a spacing over |v|; a tenth of the speed scale
 // |v - u| + sqrt(kB T/m) over |qE/m| (the time to move half a spacing from
 // rest when there is no speed scale); 0.1 / lambda on the explicit branch.
+// lang: set where the pack takes the Langevin branch.
 // ---------------------------------------------------------------------------
 constexpr unsigned long long kInfBits = 0x7FF0000000000000ull;
 
-template <class P, class Tab>
-__global__ __launch_bounds__(256) void k_dt_limits(StepArgs<P, Tab> a, unsigned long long *rep) {
+template <class P, class Tab, class GatherE, class GatherG>
+__device__ __forceinline__ double pack_limit(const StepArgs<P, Tab> &a, const Species &sp, GatherE &&e_at,
+                                             GatherG &&gas_in, typename P::T x, typename P::T y, typename P::T z,
+                                             double Z, typename P::T vx, typename P::T vy, typename P::T vz, double c0,
+                                             bool &lang) {
     using T = typename P::T;
-    __shared__ double red[256];
-    __shared__ int any_lang;
-    if (threadIdx.x == 0) any_lang = 0;
-    __syncthreads();
-    const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     double lim = HUGE_VAL;
+    const T h = (T)(1.0 / fmax(a.inv_dr, a.inv_dz));
+    const T vn = P::sqrt_(vx * vx + vy * vy + vz * vz);
+    if (vn > (T)0) lim = fmin(lim, (double)((T)0.5 * P::div(h, vn)));
+    T ex, ey, ez;
+    efield(a, e_at, x, y, z, (T)c0, ex, ey, ez);
+    const T an = (T)fabs(sp.qm) * P::sqrt_(ex * ex + ey * ey + ez * ez);
+    const T rr = P::sqrt_(x * x + y * y);
+    const Cell<T> cl = locate<T>(rr, z, (T)a.inv_dr, (T)a.inv_dz, a.nr, a.nz);
+    const Q4<T> g = gas_in(cl);
+    const T sr = rr > (T)0 ? P::div(g.a, rr) : (T)0;
+    const T rx = vx - sr * x, ry = vy - sr * y, rz = vz - g.b, tg = g.d;
+    const T sv = P::sqrt_(rx * rx + ry * ry + rz * rz);
+    const T vth = tg > (T)0 ? P::sqrt_(P::div((T)kB * tg, (T)sp.m)) : (T)0;
+    if (an > (T)0)
+        lim = fmin(lim, (double)((sv + vth) > (T)0 ? (T)0.1 * P::div(sv + vth, an) : P::sqrt_(P::div(h, an))));
+    const T ngs = tg > (T)0 ? P::div(g.c, (T)kB * tg) * (T)sp.ccs : (T)0;
+    if (a.collisions_on && ngs > (T)0 && isfinite(ngs)) {
+        const T abar = P::sqrt_(P::div((T)kB * tg, (T)a.mg)) * (T)1.5957691216057308;
+        const T lam = ngs * (sv + abar);
+        const bool in_window = !(a.lv_z_hi > a.lv_z_lo) || (Z >= a.lv_z_lo && Z < a.lv_z_hi);
+        if (a.langevin_on && in_window && lam * (T)a.lv_dt_ref >= (T)a.lv_switch) lang = true;
+        else if (lam > (T)0) lim = fmin(lim, (double)P::div((T)0.1, lam));
+    }
+    return lim;
+}
+
+// Where an adaptive run on the device stands (mc_stretch.hpp): the time and RF
+// coefficient of its next step, the length of the last, 1 + the step at which
+// its step collapsed (0: none), the steps taken since the host looked.
+struct DtRecord {
+    double t, c, dt;
+    unsigned long long halted;
+    int64_t steps;
+};
+
+// The limit of the pack of slot s as it stands, minimised over the block (of
+// 256 threads) and added into one of n_lines replica lines: word 0 holds the
+// limit's bits (positive doubles order like their bit patterns), word 1 flags
+// a pack on the Langevin branch.
+template <class P, class Tab>
+__device__ __forceinline__ void block_limits(const StepArgs<P, Tab> &a, int64_t s, double c0, unsigned long long *rep,
+                                             int32_t n_lines) {
+    using T = typename P::T;
+    __shared__ double red[4];
+    __shared__ int any_lang[4];
+    double lim = HUGE_VAL;
+    bool lang = false;
     if (s < a.n_slots && a.p.status[s] == ST_ACTIVE) {
         const Species sp = a.sp[a.p.tag[s]];
         const T x = a.p.x[s], y = a.p.y[s], z = a.p.z[s];
         double Z = (double)z;
         if constexpr (P::kTwo) Z += (double)a.p.zl[s];
-        const T vx = a.p.vx[s], vy = a.p.vy[s], vz = a.p.vz[s];
-        const T h = (T)(1.0 / fmax(a.inv_dr, a.inv_dz));
-        const T vn = P::sqrt_(vx * vx + vy * vy + vz * vz);
-        if (vn > (T)0) lim = fmin(lim, (double)((T)0.5 * P::div(h, vn)));
-        T ex, ey, ez;
-        efield(a, [&](const Cell<T> &c) { return gather4<T>(a.etab, a.esc, c, a.nr); }, x, y, z,
-               (T)(a.dyn ? a.dyn[6] : a.c0), ex, ey, ez);
-        const T an = (T)fabs(sp.qm) * P::sqrt_(ex * ex + ey * ey + ez * ez);
-        const T rr = P::sqrt_(x * x + y * y);
-        const Cell<T> cl = locate<T>(rr, z, (T)a.inv_dr, (T)a.inv_dz, a.nr, a.nz);
-        const Q4<T> g = gather4<T>(a.gtab, a.gsc, cl, a.nr);
-        const T sr = rr > (T)0 ? P::div(g.a, rr) : (T)0;
-        const T rx = vx - sr * x, ry = vy - sr * y, rz = vz - g.b, tg = g.d;
-        const T sv = P::sqrt_(rx * rx + ry * ry + rz * rz);
-        const T vth = tg > (T)0 ? P::sqrt_(P::div((T)kB * tg, (T)sp.m)) : (T)0;
-        if (an > (T)0)
-            lim = fmin(lim, (double)((sv + vth) > (T)0 ? (T)0.1 * P::div(sv + vth, an) : P::sqrt_(P::div(h, an))));
-        const T ngs = tg > (T)0 ? P::div(g.c, (T)kB * tg) * (T)sp.ccs : (T)0;
-        if (a.collisions_on && ngs > (T)0 && isfinite(ngs)) {
-            const T abar = P::sqrt_(P::div((T)kB * tg, (T)a.mg)) * (T)1.5957691216057308;
-            const T lam = ngs * (sv + abar);
-            const bool in_window = !(a.lv_z_hi > a.lv_z_lo) || (Z >= a.lv_z_lo && Z < a.lv_z_hi);
-            if (a.langevin_on && in_window && lam * (T)a.lv_dt_ref >= (T)a.lv_switch) atomicOr(&any_lang, 1);
-            else if (lam > (T)0) lim = fmin(lim, (double)P::div((T)0.1, lam));
-        }
+        lim = pack_limit(
+            a, sp, [&](const Cell<T> &c) { return gather4<T>(a.etab, a.esc, c, a.nr); },
+            [&](const Cell<T> &c) { return gather4<T>(a.gtab, a.gsc, c, a.nr); }, x, y, z, Z, a.p.vx[s], a.p.vy[s],
+            a.p.vz[s], c0, lang);
     }
-    red[threadIdx.x] = lim;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) lim = fmin(lim, __shfl_xor(lim, o, 64));
+    const bool any = __ballot(lang) != 0ull;
+    const int wave = threadIdx.x >> 6;
+    if ((threadIdx.x & 63) == 0) {
+        red[wave] = lim;
+        any_lang[wave] = any;
+    }
     __syncthreads();
-    for (int w = blockDim.x / 2; w > 0; w >>= 1) {
-        if ((int)threadIdx.x < w) red[threadIdx.x] = fmin(red[threadIdx.x], red[threadIdx.x + w]);
-        __syncthreads();
-    }
     if (threadIdx.x == 0) {
-        unsigned long long *line = rep + (int64_t)(blockIdx.x & (kHotRep - 1)) * kHotStride;
-        atomicMin(line, (unsigned long long)__double_as_longlong(red[0]));
-        if (any_lang) atomicOr(line + 1, 1ull);
+        lim = fmin(fmin(red[0], red[1]), fmin(red[2], red[3]));
+        unsigned long long *line = rep + (int64_t)(blockIdx.x & (unsigned)(n_lines - 1)) * kHotStride;
+        atomicMin(line, (unsigned long long)__double_as_longlong(lim));
+        if (any_lang[0] | any_lang[1] | any_lang[2] | any_lang[3]) atomicOr(line + 1, 1ull);
     }
+}
+
+template <class P, class Tab>
+__global__ __launch_bounds__(256) void k_dt_limits(StepArgs<P, Tab> a, unsigned long long *rep, int32_t n_lines) {
+    block_limits(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, a.c0, rep, n_lines);
 }
 
 // Replica lines -> out[0] (limit bits), out[1] (Langevin flag); the lines are
@@ -819,61 +835,19 @@ static __global__ __launch_bounds__(kHotRep) void k_dt_reduce(unsigned long long
     }
 }
 
-// The adaptive step on the device (one block of kHotRep threads): the
-// replica lines reduced as in k_dt_reduce, then
-//   dt = min(dt_max, limit, rf_cap, lv_cap if a pack takes the Langevin
-//            branch, t_pic - t0)
-// (the caps are +inf where they do not apply), and the step record: this
-// step's (t0, dt, c0, ch, c1) with c = V_RF cos(w2 t + phase) at t0, t0 +
-// dt/2 and t0 + dt, then the next step's t0 = t0 + dt and c0.  A step below
-// `collapse` halts the run: the record's length becomes zero (the step
-// kernels return at once) and word 7 keeps 1 + the step index, the time
-// staying at the collapsed step's start.
-static __global__ __launch_bounds__(kHotRep) void k_dt_finish(unsigned long long *rep, double *rec, double dt_max,
-                                                              double rf_cap, double lv_cap, double t_pic,
-                                                              double collapse, double v_rf, double w2, double phase,
-                                                              int64_t step) {
-#pragma clang fp contract(off)
-    __shared__ unsigned long long mn[kHotRep], fl[kHotRep];
-    const int k = threadIdx.x;
-    mn[k] = rep[(int64_t)k * kHotStride];
-    fl[k] = rep[(int64_t)k * kHotStride + 1];
-    rep[(int64_t)k * kHotStride] = kInfBits;
-    rep[(int64_t)k * kHotStride + 1] = 0ull;
-    __syncthreads();
-    for (int w = kHotRep / 2; w > 0; w >>= 1) {
-        if (k < w) {
-            mn[k] = mn[k] < mn[k + w] ? mn[k] : mn[k + w];
-            fl[k] |= fl[k + w];
-        }
-        __syncthreads();
-    }
-    if (k != 0) return;
-    unsigned long long *halted = reinterpret_cast<unsigned long long *>(rec + 7);
-    const double t0 = rec[5], c0 = rec[6];
-    double d = fmin(dt_max, __longlong_as_double((long long)mn[0]));
-    d = fmin(d, rf_cap);
-    if (fl[0]) d = fmin(d, lv_cap);
-    d = fmin(d, t_pic - t0);
-    if (*halted || !(d > collapse)) {
-        if (!*halted) *halted = (unsigned long long)step + 1ull;
-        rec[1] = 0.0;
-        return;
-    }
-    const double t1 = t0 + d;
-    const double c1 = v_rf * cos(w2 * t1 + phase);
-    rec[0] = t0;
-    rec[1] = d;
-    rec[2] = c0;
-    rec[3] = v_rf * cos(w2 * (t0 + 0.5 * d) + phase);
-    rec[4] = c1;
-    rec[5] = t1;
-    rec[6] = c1;
+// One block of kHotRep threads per set of replica lines.
+static __global__ __launch_bounds__(kHotRep) void k_dt_reset(unsigned long long *rep) {
+    unsigned long long *line = rep + ((int64_t)blockIdx.x * kHotRep + threadIdx.x) * kHotStride;
+    line[0] = kInfBits;
+    line[1] = 0ull;
 }
 
-static __global__ __launch_bounds__(kHotRep) void k_dt_reset(unsigned long long *rep) {
-    rep[(int64_t)threadIdx.x * kHotStride] = kInfBits;
-    rep[(int64_t)threadIdx.x * kHotStride + 1] = 0ull;
+// The reset of a run's sets of lines, with its first record.
+static __global__ __launch_bounds__(kHotRep) void k_dt_begin(unsigned long long *rep, DtRecord *at, DtRecord rec) {
+    unsigned long long *line = rep + ((int64_t)blockIdx.x * kHotRep + threadIdx.x) * kHotStride;
+    line[0] = kInfBits;
+    line[1] = 0ull;
+    if (blockIdx.x == 0 && threadIdx.x == 0) *at = rec;
 }
 
 // All resident queries of a server advance one step in one launch; each
@@ -1371,11 +1345,10 @@ template <class T>
 __global__ __launch_bounds__(kSampleThreads) void k_sample(PackPtrs<T> p, const Species *sp, int64_t n_slots,
                                                            int64_t step, int64_t stride, mc_sample_rec *out,
                                                            unsigned long long *count, int64_t cap,
-                                                           const double *dyn = nullptr) {
+                                                           const DtRecord *rec = nullptr, double t_pause = 0.0) {
 #pragma clang fp contract(off)
-    // an adaptive run halted on the device takes no further samples (the
-    // record of the previous step has zero length)
-    if (dyn && !(dyn[1] > 0.0) && reinterpret_cast<const unsigned long long *>(dyn)[7]) return;
+    // an adaptive run that has halted or paused on the device takes no further samples
+    if (rec && (rec->halted || rec->t >= t_pause)) return;
     __shared__ unsigned int wave_base[kSampleThreads / 64];
     __shared__ unsigned long long block_base;
     const int64_t s = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;

@@ -80,8 +80,9 @@ struct mc_ctx {
     double *rhs = nullptr, *phi_tmp = nullptr;
     // adaptive step (Eq. 1)
     unsigned long long *dt_rep = nullptr, *dt_out = nullptr;
-    double *dt_rec = nullptr;   // the step record kept on the device (k_dt_finish)
-    bool dt_rec_valid = false;  // its next-step time matches t
+    DtRecord *dt_rec = nullptr;  // two records of an adaptive run on the device (k_stretch_adaptive)
+    double c_next = 0.0;         // RF coefficient at t, as the device found it
+    bool c_next_valid = false;
     double t = 0.0, t_next_pic = 0.0, last_dt = 0.0;
     // trajectory samples
     mc_sample_rec *samples = nullptr;
@@ -471,10 +472,9 @@ static StepArgs<P, Tab> step_args(mc_ctx *ctx, PackPtrs<typename P::T> p, double
 }
 
 template <class P, class Tab>
-static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, double dt, const double *dyn) {
+static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, double dt) {
     if (ctx->n_slots == 0) return MC_OK;
-    StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, t0, dt);
-    a.dyn = dyn;
+    const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, t0, dt);
     Timer t(ctx, MC_K_STEP);
     const unsigned nb = (unsigned)((ctx->n_slots + kStepBlock - 1) / kStepBlock);
     // one species defined: every pack carries tag 0 (tags are checked
@@ -507,10 +507,8 @@ static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
 }
 
 template <class P, class Tab>
-static int32_t launch_stretch(mc_ctx *ctx, PackPtrs<typename P::T> p, int lanes, const StretchSteps &st, double dt,
-                              const double *dyn) {
-    StretchArgs<P, Tab> a{step_args<P, Tab>(ctx, p, st.t0[0], dt), st};
-    a.a.dyn = dyn;
+static int32_t launch_stretch(mc_ctx *ctx, PackPtrs<typename P::T> p, int lanes, const StretchSteps &st, double dt) {
+    const StretchArgs<P, Tab> a{step_args<P, Tab>(ctx, p, st.t0[0], dt), st};
     Timer t(ctx, MC_K_STEP, st.n);
     const int64_t per = 64 / lanes, n = st.n_slots[st.n - 1];
     const unsigned nb = (unsigned)((n + per - 1) / per);
@@ -525,10 +523,32 @@ static int32_t launch_stretch(mc_ctx *ctx, PackPtrs<typename P::T> p, int lanes,
     return MC_OK;
 }
 
-static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, double dt, const double *dyn = nullptr) {
-    if (!ctx->fp32()) return launch_stretch<P64, double4>(ctx, ctx->p64, lanes, st, dt, dyn);
-    if (ctx->bf16()) return launch_stretch<P32, bf16x4>(ctx, ctx->p32, lanes, st, dt, dyn);
-    return launch_stretch<P32, float4>(ctx, ctx->p32, lanes, st, dt, dyn);
+static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, double dt) {
+    if (!ctx->fp32()) return launch_stretch<P64, double4>(ctx, ctx->p64, lanes, st, dt);
+    if (ctx->bf16()) return launch_stretch<P32, bf16x4>(ctx, ctx->p32, lanes, st, dt);
+    return launch_stretch<P32, float4>(ctx, ctx->p32, lanes, st, dt);
+}
+
+// One step of an adaptive run on the device.
+template <class P, class Tab>
+static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d) {
+    const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
+    Timer t(ctx, MC_K_STEP);
+    if constexpr (P::kTwo) {
+        const unsigned nb = std::max(1u, grid_for(ctx->n_slots));
+        if (ctx->ions.size() == 1) k_step_adaptive<P, Tab, true><<<nb, kBlock, 0, ctx->stream>>>(a, d);
+        else k_step_adaptive<P, Tab, false><<<nb, kBlock, 0, ctx->stream>>>(a, d);
+    } else {
+        AdaptiveArgs<P, Tab> all{};
+        all.s.a = a;
+        all.s.st.n = 1;
+        all.s.st.n_slots[0] = ctx->n_slots;
+        all.d = d;
+        const unsigned nb = (unsigned)std::max<int64_t>(1, (ctx->n_slots + 63) / 64);
+        k_stretch_adaptive<P, Tab><<<nb, 64, 0, ctx->stream>>>(all);
+    }
+    LAUNCHCHK();
+    return MC_OK;
 }
 
 // Entry j of a stretch: a step of length dt from t0 over n_slots slots.
@@ -542,18 +562,17 @@ static void stretch_step(const mc_ctx *ctx, StretchSteps &st, int j, double t0, 
     st.n_slots[j] = n_slots;
 }
 
-// One step (dyn: its record on the device, of an adaptive run).
-static int32_t step_once(mc_ctx *ctx, double t0, double dt, const double *dyn = nullptr) {
+static int32_t step_once(mc_ctx *ctx, double t0, double dt) {
     const int lanes = stretch_lanes(ctx, ctx->n_slots, 1);
     if (lanes > 0) {
         StretchSteps st;
         st.n = 1;
         stretch_step(ctx, st, 0, t0, dt, ctx->n_slots);
-        return step_stretch(ctx, lanes, st, dt, dyn);
+        return step_stretch(ctx, lanes, st, dt);
     }
-    if (!ctx->fp32()) return launch_step<P64, double4>(ctx, ctx->p64, t0, dt, dyn);
-    if (ctx->bf16()) return launch_step<P32, bf16x4>(ctx, ctx->p32, t0, dt, dyn);
-    return launch_step<P32, float4>(ctx, ctx->p32, t0, dt, dyn);
+    if (!ctx->fp32()) return launch_step<P64, double4>(ctx, ctx->p64, t0, dt);
+    if (ctx->bf16()) return launch_step<P32, bf16x4>(ctx, ctx->p32, t0, dt);
+    return launch_step<P32, float4>(ctx, ctx->p32, t0, dt);
 }
 
 // A source's emission over a stretch of steps.
@@ -573,12 +592,13 @@ static int32_t emit_stretch_t(mc_ctx *ctx, int si, const EmitSteps &em, PackPtrs
 // limit (+inf with no packs) and whether a pack takes the Langevin branch.
 template <class P, class Tab>
 static int32_t pack_limits_t(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, double *lim, bool *lang) {
+    unsigned long long *const rep = ctx->dt_rep + 3 * kHotLen;  // (the set that launches of adaptive steps leave alone)
     if (ctx->n_slots > 0) {
         const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, t0, ctx->op.dt);
-        k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, ctx->dt_rep);
+        k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, rep, kHotRep);
         LAUNCHCHK();
     }
-    k_dt_reduce<<<1, kHotRep, 0, ctx->stream>>>(ctx->dt_rep, ctx->dt_out);
+    k_dt_reduce<<<1, kHotRep, 0, ctx->stream>>>(rep, ctx->dt_out);
     LAUNCHCHK();
     unsigned long long h[2];
     HIPCHK(hipMemcpyAsync(h, ctx->dt_out, sizeof(h), hipMemcpyDeviceToHost, ctx->stream));
@@ -588,25 +608,25 @@ static int32_t pack_limits_t(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, 
     return MC_OK;
 }
 
-// The Eq. 1 limits of this step into the replica lines, with the RF
-// coefficient of the step's start from the device record.
+// The Eq. 1 limits of the packs as they stand into the first set of lines.
 template <class P, class Tab>
-static int32_t pack_limits_dev(mc_ctx *ctx, PackPtrs<typename P::T> p) {
+static int32_t seed_limits(mc_ctx *ctx, PackPtrs<typename P::T> p) {
     if (ctx->n_slots == 0) return MC_OK;
     StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
-    a.dyn = ctx->dt_rec;
-    k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, ctx->dt_rep);
+    a.c0 = ctx->c_next;
+    k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, ctx->dt_rep, kDtLines);
     LAUNCHCHK();
     return MC_OK;
 }
 
 static int32_t adaptive_buffers(mc_ctx *ctx) {
     if (ctx->dt_rep) return MC_OK;
-    int32_t rc = dalloc_t(ctx, &ctx->dt_rep, (size_t)kHotLen);
+    // three sets of lines for k_stretch_adaptive, one for a step that the host sizes
+    int32_t rc = dalloc_t(ctx, &ctx->dt_rep, 4 * (size_t)kHotLen);
     if (!rc) rc = dalloc_t(ctx, &ctx->dt_out, 2);
-    if (!rc) rc = dalloc_t(ctx, &ctx->dt_rec, 8);
+    if (!rc) rc = dalloc_t(ctx, &ctx->dt_rec, 2);
     if (rc) return rc;
-    k_dt_reset<<<1, kHotRep, 0, ctx->stream>>>(ctx->dt_rep);
+    k_dt_reset<<<4, kHotRep, 0, ctx->stream>>>(ctx->dt_rep);
     LAUNCHCHK();
     return MC_OK;
 }
@@ -1152,7 +1172,7 @@ int32_t mc_set_operating(mc_ctx *ctx, const mc_operating *op) {
     if (!first && op->n_exit_bins != ctx->op.n_exit_bins)
         return fail(ctx, MC_ESTATE, "the number of exit bins is fixed by the first operating point");
     ctx->op = *op;
-    ctx->dt_rec_valid = false;  // RF and step settings may have changed
+    ctx->c_next_valid = false;  // RF and step settings may have changed
     ctx->has_op = true;
     for (size_t k = 0; k < ctx->ions.size(); ++k) ctx_alpha(ctx, k);
     int32_t rc = upload_species(ctx);
@@ -1210,9 +1230,9 @@ int32_t mc_inject(mc_ctx *ctx, int32_t src_id, int64_t n) {
 }
 
 // Trajectory samples at the start of the current step when it is one of the
-// sampled steps (dyn: the device step record of an adaptive run, whose
-// halted state stops sampling).
-static int32_t sample_if_due(mc_ctx *ctx, const double *dyn) {
+// sampled steps (rec: where an adaptive run on the device stands, which takes
+// no samples once it has halted or reached t_pause).
+static int32_t sample_if_due(mc_ctx *ctx, const DtRecord *rec, double t_pause) {
     if (!(ctx->op.sample_every > 0 && ctx->op.sample_stride > 0 && ctx->step % ctx->op.sample_every == 0 &&
           ctx->n_slots > 0))
         return MC_OK;
@@ -1220,11 +1240,11 @@ static int32_t sample_if_due(mc_ctx *ctx, const double *dyn) {
     if (ctx->fp32())
         k_sample<float><<<sgrid, kSampleThreads, 0, ctx->stream>>>(ctx->p32, ctx->sp_dev, ctx->n_slots, ctx->step,
                                                                    ctx->op.sample_stride, ctx->samples,
-                                                                   ctx->sample_count, ctx->sample_cap, dyn);
+                                                                   ctx->sample_count, ctx->sample_cap, rec, t_pause);
     else
         k_sample<double><<<sgrid, kSampleThreads, 0, ctx->stream>>>(ctx->p64, ctx->sp_dev, ctx->n_slots, ctx->step,
                                                                     ctx->op.sample_stride, ctx->samples,
-                                                                    ctx->sample_count, ctx->sample_cap, dyn);
+                                                                    ctx->sample_count, ctx->sample_cap, rec, t_pause);
     LAUNCHCHK();
     return MC_OK;
 }
@@ -1238,23 +1258,23 @@ static bool sources_idle(const mc_ctx *ctx) {
 }
 
 // Adaptive steps with the step length kept on the device: up to max_steps
-// steps, as many as can run before a space-charge update could fall due
-// (the time grows by at most dt_max per step), then one read of the step
-// record.  *done receives the steps taken.
+// steps, as many as run before the next space-charge update falls due, then
+// one read of the record.  How many that will be is guessed from the last
+// step's length; steps enqueued beyond it are not taken on the device.  (With
+// the kernels timed, only as many are enqueued as are sure to be taken.)
+// *done receives the steps taken.
 static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     *done = 0;
     int32_t rc = adaptive_buffers(ctx);
     if (rc) return rc;
     const mc_operating &op = ctx->op;
-    if (!ctx->dt_rec_valid) {
-        double init[8] = {ctx->t, 0.0, 0.0, 0.0, 0.0, ctx->t, 0.0, 0.0};
+    const double inf = HUGE_VAL, tol = 1e-6 * op.dt, t0 = ctx->t;
+    if (!ctx->c_next_valid) {
         double c[3];
-        rf_stages_at(op, ctx->t, 0.0, c);
-        init[6] = c[0];
-        HIPCHK(hipMemcpyAsync(ctx->dt_rec, init, sizeof(init), hipMemcpyHostToDevice, ctx->stream));
-        ctx->dt_rec_valid = true;
+        rf_stages_at(op, t0, 0.0, c);
+        ctx->c_next = c[0];
+        ctx->c_next_valid = true;
     }
-    const double tol = 1e-6 * op.dt, t0 = ctx->t;
     int64_t k = max_steps;
     if (op.sort_every > 0) {
         // the stretch ends before the next sorted step
@@ -1262,46 +1282,66 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         if (rc) return rc;
         k = std::min<int64_t>(k, op.sort_every - ctx->step % op.sort_every);
     }
-    for (int64_t j = 0; j < k; ++j) {
-        rc = sample_if_due(ctx, ctx->dt_rec);
-        if (rc) return rc;
-        if (j == 0 && op.sc_on) {
-            if (t0 >= ctx->t_next_pic - tol) {
-                rc = pic_update(ctx);
-                if (rc) return rc;
-                const double period = op.sc_every * op.dt;
-                while (ctx->t_next_pic <= t0 + tol) ctx->t_next_pic += period;
-            }
-            // the first step whose start could reach the next update's time
-            const double room = ctx->t_next_pic - tol - t0;
-            k = std::min<int64_t>(k, std::max<int64_t>(1, (int64_t)std::ceil(room / op.dt)));
+    rc = sample_if_due(ctx, nullptr, 0.0);
+    if (rc) return rc;
+    if (op.sc_on) {
+        if (t0 >= ctx->t_next_pic - tol) {
+            rc = pic_update(ctx);
+            if (rc) return rc;
+            const double period = op.sc_every * op.dt;
+            while (ctx->t_next_pic <= t0 + tol) ctx->t_next_pic += period;
         }
-        if (!ctx->fp32()) rc = pack_limits_dev<P64, double4>(ctx, ctx->p64);
-        else if (ctx->bf16()) rc = pack_limits_dev<P32, bf16x4>(ctx, ctx->p32);
-        else rc = pack_limits_dev<P32, float4>(ctx, ctx->p32);
-        if (rc) return rc;
-        const double inf = HUGE_VAL;
-        k_dt_finish<<<1, kHotRep, 0, ctx->stream>>>(
-            ctx->dt_rep, ctx->dt_rec, op.dt, (op.v_rf != 0.0 && op.f_rf > 0.0) ? 0.05 / op.f_rf : inf,
-            op.lv_dt_max > 0.0 ? op.lv_dt_max : inf, op.sc_on ? ctx->t_next_pic : inf, 1e-9 * op.dt, op.v_rf,
-            2.0 * kPi * op.f_rf, op.phase_rf, ctx->step);
-        LAUNCHCHK();
-        rc = step_once(ctx, 0.0, op.dt, ctx->dt_rec);
-        if (rc) return rc;
-        ctx->step++;
-        ++*done;
+        // the steps before the next update's time: at least those of the
+        // largest length, likely those of the last one's
+        const double room = ctx->t_next_pic - tol - t0;
+        const bool guess = !ctx->opt.timing && ctx->last_dt > 0.0 && ctx->last_dt < op.dt;
+        const double n = std::ceil(room / (guess ? ctx->last_dt : op.dt)) + (guess ? 1.0 : 0.0);
+        k = std::min<int64_t>(k, (int64_t)std::max(1.0, std::min(n, 1024.0)));
     }
-    double rec[8];
-    HIPCHK(hipMemcpyAsync(rec, ctx->dt_rec, sizeof(rec), hipMemcpyDeviceToHost, ctx->stream));
+    // the record and the limits the first step starts from
+    DtRecord rec{t0, ctx->c_next, 0.0, 0ull, 0};
+    k_dt_begin<<<3, kHotRep, 0, ctx->stream>>>(ctx->dt_rep, ctx->dt_rec, rec);
+    LAUNCHCHK();
+    if (!ctx->fp32()) rc = seed_limits<P64, double4>(ctx, ctx->p64);
+    else if (ctx->bf16()) rc = seed_limits<P32, bf16x4>(ctx, ctx->p32);
+    else rc = seed_limits<P32, float4>(ctx, ctx->p32);
+    if (rc) return rc;
+    DtArgs d{};
+    d.dt_max = op.dt;
+    d.rf_cap = op.v_rf != 0.0 && op.f_rf > 0.0 ? 0.05 / op.f_rf : inf;
+    d.lv_cap = op.lv_dt_max > 0.0 ? op.lv_dt_max : inf;
+    d.t_pic = op.sc_on ? ctx->t_next_pic : inf;
+    d.t_pause = op.sc_on ? ctx->t_next_pic - tol : inf;
+    d.collapse = 1e-9 * op.dt;
+    d.v_rf = op.v_rf;
+    d.w2 = 2.0 * kPi * op.f_rf;
+    d.phase = op.phase_rf;
+    const int64_t step0 = ctx->step;
+    for (int64_t j = 0; j < k && !rc; ++j) {
+        d.in = ctx->dt_rec + (j & 1);
+        d.out = ctx->dt_rec + ((j + 1) & 1);
+        d.limits = ctx->dt_rep + (j % 3) * kHotLen;
+        d.next = ctx->dt_rep + ((j + 1) % 3) * kHotLen;
+        d.clear = ctx->dt_rep + ((j + 2) % 3) * kHotLen;
+        d.step = ctx->step;
+        if (j > 0) rc = sample_if_due(ctx, d.in, d.t_pause);
+        if (rc) break;
+        if (!ctx->fp32()) rc = launch_adaptive<P64, double4>(ctx, ctx->p64, d);
+        else if (ctx->bf16()) rc = launch_adaptive<P32, bf16x4>(ctx, ctx->p32, d);
+        else rc = launch_adaptive<P32, float4>(ctx, ctx->p32, d);
+        ctx->step++;  // (the step that sample_if_due and the launches go by)
+    }
+    ctx->step = step0;
+    if (rc) return rc;
+    HIPCHK(hipMemcpyAsync(&rec, ctx->dt_rec + (k & 1), sizeof(rec), hipMemcpyDeviceToHost, ctx->stream));
     HIPCHK(hipStreamSynchronize(ctx->stream));
-    uint64_t halted;
-    std::memcpy(&halted, &rec[7], sizeof(halted));
-    ctx->t = rec[5];
-    if (halted) {
-        ctx->step = (int64_t)halted - 1;
+    ctx->t = rec.t;
+    ctx->c_next = rec.c;
+    ctx->step = step0 + rec.steps;
+    *done = rec.steps;
+    if (rec.halted)
         return fail(ctx, MC_ENUMERIC, "adaptive step collapsed below 1e-9 dt at step " + std::to_string(ctx->step));
-    }
-    ctx->last_dt = rec[1];
+    ctx->last_dt = rec.dt;
     return MC_OK;
 }
 
@@ -1382,10 +1422,10 @@ int32_t mc_step(mc_ctx *ctx, int64_t n_steps) {
             it += done;
             continue;
         }
-        ctx->dt_rec_valid = false;  // the host advances the time below
+        ctx->c_next_valid = false;  // the host advances the time below
         rc = sort_if_due(ctx);
         if (rc) return rc;
-        rc = sample_if_due(ctx, nullptr);
+        rc = sample_if_due(ctx, nullptr, 0.0);
         if (rc) return rc;
         double t0 = (double)ctx->step * ctx->op.dt, dt = ctx->op.dt;
         if (ctx->op.adaptive) {
@@ -1726,7 +1766,7 @@ int32_t mc_load_state(mc_ctx *ctx, const char *path) {
     if (!ctx || !path) return MC_EINVAL;
     if (!ctx->has_fields || !ctx->has_op) return fail(ctx, MC_ESTATE, "fields and operating point required");
     HIPCHK(hipSetDevice(ctx->opt.device));
-    ctx->dt_rec_valid = false;
+    ctx->c_next_valid = false;
     HIPCHK(hipStreamSynchronize(ctx->stream));
     FILE *f = std::fopen(path, "rb");
     if (!f) return fail(ctx, MC_EINVAL, std::string("cannot read ") + path);

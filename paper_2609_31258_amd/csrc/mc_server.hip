@@ -481,7 +481,7 @@ static int32_t adaptive_steps(mc_server *S, std::vector<Query *> &act) {
         }
         if (Q.n_slots > 0) {
             const StepArgs<P, Tab> a = query_step_args<P, Tab>(S, Q, Q.t, op.dt);
-            k_dt_limits<P, Tab><<<blocks_for(Q.n_slots), kBlk, 0, S->stream>>>(a, Q.dt_rep);
+            k_dt_limits<P, Tab><<<blocks_for(Q.n_slots), kBlk, 0, S->stream>>>(a, Q.dt_rep, kHotRep);
         }
         k_dt_reduce<<<1, kHotRep, 0, S->stream>>>(Q.dt_rep, Q.dt_out);
         SCHK(hipGetLastError());

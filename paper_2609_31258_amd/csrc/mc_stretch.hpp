@@ -222,6 +222,91 @@ __device__ __forceinline__ void collide_group(const StepArgs<P, Tab> &a, const S
     }
 }
 
+// Adaptive steps (Eq. 1) without the host: a launch takes one step of the
+// length that the packs' limits allow.  Every block reduces the limits that
+// the launch before left (kDtLines replica lines) and finds the same step,
+//   dt = min(dt_max, limit, rf_cap, lv_cap if a pack takes the Langevin
+//            branch, t_pic - t)
+// (the caps are +inf where they do not apply), takes its packs through it and
+// leaves their limits for the launch after; the first block writes the record.
+// Records and lines change places from launch to launch: two records, three
+// sets of lines (read, filled, cleared).  A step below `collapse` halts the
+// run; one that would start at t_pause or later is not taken (the host's
+// space-charge update comes first): then the launches that follow only hand
+// the record on.  One launch instead of three (limits, their reduction, step):
+// 1e5 packs 24.5 -> 15.1 us a step in the FP32 form (Langevin branch), 36.8 ->
+// 22.1 in FP64; 1e6 packs 55.2 -> 52.1 and 166 -> 125.  Below 1e5 packs what is
+// left is the launch and the chain of loads, limits and step in each.
+constexpr int kDtLines = 64;  // a lane of the reducing wavefront per line
+static_assert(kDtLines <= kHotRep);
+struct DtArgs {
+    const unsigned long long *limits;
+    unsigned long long *next, *clear;
+    const DtRecord *in;
+    DtRecord *out;
+    double dt_max, rf_cap, lv_cap, t_pic, t_pause, collapse, v_rf, w2, phase;
+    int64_t step;
+};
+
+template <class P, class Tab>
+struct AdaptiveArgs {
+    StretchArgs<P, Tab> s;
+    DtArgs d;
+};
+
+struct DtStep {
+    double t0, dt, c0, ch, c1;
+    bool go;
+};
+
+// Lane l's value, in scalar registers.
+__device__ __forceinline__ double from_lane(double v, int l) {
+    return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                            __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
+__device__ __forceinline__ DtStep dt_step(const DtArgs &d) {
+#pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
+    const DtRecord r = *d.in;
+    DtRecord o = r;
+    DtStep s{r.t, 0.0, r.c, 0.0, 0.0, false};
+    if (!r.halted && r.t < d.t_pause) {
+        unsigned long long mn = d.limits[(int64_t)lane * kHotStride];
+        const bool lang = __ballot(d.limits[(int64_t)lane * kHotStride + 1] != 0ull) != 0ull;
+#pragma unroll
+        for (int o2 = 32; o2 > 0; o2 >>= 1) {
+            const unsigned long long other = __shfl_xor(mn, o2, 64);
+            mn = other < mn ? other : mn;
+        }
+        double dt = fmin(d.dt_max, __longlong_as_double((long long)mn));
+        dt = fmin(dt, d.rf_cap);
+        if (lang) dt = fmin(dt, d.lv_cap);
+        dt = fmin(dt, d.t_pic - r.t);
+        if (dt > d.collapse) {
+            s.go = true;
+            s.dt = from_lane(dt, 0);
+            const double t1 = r.t + dt;
+            // both RF coefficients by one cosine: every wavefront pays for it
+            const double c = d.v_rf * cos(d.w2 * (lane & 1 ? t1 : r.t + 0.5 * dt) + d.phase);
+            s.ch = from_lane(c, 0);
+            s.c1 = from_lane(c, 1);
+            o.t = t1;
+            o.c = s.c1;
+            o.dt = dt;
+            ++o.steps;
+        } else {
+            o.halted = (unsigned long long)d.step + 1ull;
+        }
+    }
+    if (blockIdx.x == 0) {
+        if (lane == 0) *d.out = o;
+        d.clear[(int64_t)lane * kHotStride] = kInfBits;
+        d.clear[(int64_t)lane * kHotStride + 1] = 0ull;
+    }
+    return s;
+}
+
 // Counters of a stretch: totals over its steps, kept below 2^25 per lane
 // (a step adds less than 2^23 + 64 to any of them) so that a wavefront's sum
 // fits 32 bits.
@@ -253,13 +338,16 @@ constexpr int stretch_waves() {
 template <class P, class Tab>
 using ConstArgs = const __attribute__((address_space(4))) StretchArgs<P, Tab> *;
 
-template <class P, class Tab, int G>
-__device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t block) {
+template <class P, class Tab, int G, bool kAdaptive = false>
+__device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t block, const DtArgs *dt = nullptr) {
     using T = typename P::T;
     __shared__ T lds[G > 1 ? DR_N : 1][64];
     const auto &args = *(const StretchArgs<P, Tab> *)from;
-    const double *const dyn = args.a.dyn;  // an adaptive run's single step: its record on the device (k_step)
-    if (dyn && !(dyn[1] > 0.0)) return;
+    DtStep now_dt{};
+    if constexpr (kAdaptive) {  // (a single step)
+        now_dt = dt_step(*dt);
+        if (!now_dt.go) return;
+    }
     const int32_t n_steps = args.st.n;
     P::prepare_tables(args.a.tables);
     const int lane = threadIdx.x & 63, sub = lane & (G - 1), col = lane & ~(G - 1);
@@ -304,11 +392,18 @@ __device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t bl
         const uint32_t k0 = a.k0, k1 = a.k1;
         const Species &sp = a.sp[tag];
         a.step += j;
-        a.t0 = dyn ? dyn[0] : st.t0[j];
-        if (dyn) a.dt = dyn[1];
-        a.c0 = dyn ? dyn[2] : st.c0[j];
-        a.ch = dyn ? dyn[3] : st.ch[j];
-        a.c1 = dyn ? dyn[4] : st.c1[j];
+        if constexpr (kAdaptive) {
+            a.t0 = now_dt.t0;
+            a.dt = now_dt.dt;
+            a.c0 = now_dt.c0;
+            a.ch = now_dt.ch;
+            a.c1 = now_dt.c1;
+        } else {
+            a.t0 = st.t0[j];
+            a.c0 = st.c0[j];
+            a.ch = st.ch[j];
+            a.c1 = st.c1[j];
+        }
         if (status == ST_ACTIVE && s < st.n_slots[j]) {
             PackCount pc{0, 0, 0, 0, 0, 0};
             const double X0 = (double)m.x + (double)m.xl, Y0 = (double)m.y + (double)m.yl,
@@ -395,6 +490,23 @@ __device__ __forceinline__ void stretch_packs(ConstArgs<P, Tab> from, int64_t bl
             }
         }
         if (__ballot(n.cand >> 24) != 0ull) flush_stretch(a.t, n);
+        if constexpr (kAdaptive) {  // the limits of the step after this one
+            double lim = HUGE_VAL;
+            bool lang = false;
+            if (status == ST_ACTIVE)
+                lim = pack_limit(
+                    a, sp, [&](const Cell<T> &c) { return ecell.gather(a.etab, a.esc, c, a.nr); },
+                    [&](const Cell<T> &c) { return gcell.gather(a.gtab, a.gsc, c, a.nr); }, m.x, m.y, m.z,
+                    (double)m.z + (double)m.zl, m.vx, m.vy, m.vz, a.c1, lang);
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) lim = fmin(lim, __shfl_xor(lim, o, 64));
+            const bool any = __ballot(lang) != 0ull;
+            if (lane == 0) {
+                unsigned long long *line = dt->next + (int64_t)(blockIdx.x & (kDtLines - 1)) * kHotStride;
+                if (lim < HUGE_VAL) atomicMin(line, (unsigned long long)__double_as_longlong(lim));
+                if (any) atomicOr(line + 1, 1ull);
+            }
+        }
     }
     const StepArgs<P, Tab> &a = ((const StretchArgs<P, Tab> *)from)->a;
     if (mine && sub == 0) {
@@ -422,6 +534,44 @@ template <class P, class Tab, int G>
 __global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch(StretchArgs<P, Tab> args) {
     stretch_packs<P, Tab, G>((ConstArgs<P, Tab>)__builtin_amdgcn_kernarg_segment_ptr(),
                              args.a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x);
+}
+
+// Its FP64 form: a single step of the stretch kernel, one pack a lane (an
+// adaptive step draws 0.1 candidates a pack), whose limits come from the state
+// and the cell in registers.
+template <class P, class Tab>
+__global__ __launch_bounds__(64, (stretch_waves<P>())) void k_stretch_adaptive(AdaptiveArgs<P, Tab> args) {
+    stretch_packs<P, Tab, 1, true>((ConstArgs<P, Tab>)__builtin_amdgcn_kernarg_segment_ptr(),
+                                   args.s.a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x, &args.d);
+}
+
+// Its FP32 form: the step by k_step's code, which leaves five wavefronts a SIMD
+// where the stretch kernel's leaves three, the limits from the state just
+// written; one wavefront of a block looks for the step.  Us a step at 3e4 /
+// 1e5 / 3e5 / 1e6 packs: FP32 11.5 / 14.1 / 22.8 / 56.1 here, 14.1 / 15.1 /
+// 26.9 / 65.8 the other way; FP64 20.4 / 28.9 / 57.7 / 157 against 17.2 /
+// 22.1 / 47.8 / 125.
+template <class P, class Tab, bool kOneSpecies>
+__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_adaptive(StepArgs<P, Tab> a, DtArgs d) {
+    __shared__ DtStep found;
+    if (threadIdx.x < 64) {
+        const DtStep s = dt_step(d);
+        if (threadIdx.x == 0) found = s;
+    }
+    __syncthreads();
+    if (!found.go) return;
+    a.t0 = from_lane(found.t0, 0);
+    a.dt = from_lane(found.dt, 0);
+    a.c0 = from_lane(found.c0, 0);
+    a.ch = from_lane(found.ch, 0);
+    a.c1 = from_lane(found.c1, 0);
+    P::prepare_tables(a.tables);
+    StepCount n{0, 0, 0, 0, 0, 0, 0};
+    const unsigned block = !kOneSpecies && a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    const int64_t s = (int64_t)block * blockDim.x + threadIdx.x;
+    step_one<P, Tab, kOneSpecies>(a, s, n, a.k0, a.k1);
+    flush_counts(a.t, n);
+    block_limits(a, s, a.c1, d.next, kDtLines);
 }
 
 // The resident queries of a server, each over its own steps; each block

@@ -1,0 +1,67 @@
+"""Adaptive steps of one call (each launch takes the limits that the launch
+before left, and steps enqueued beyond a space-charge update are not taken)
+against one call per step (each starts from a pass over the packs as they
+stand), bit for bit: both take the same minimum over the same packs."""
+import sys
+
+import numpy as np
+import pytest
+
+from paper_2609_31258_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _say(*a):
+    print(*a, flush=True)
+    sys.stdout.flush()
+
+
+def _run(n, precision, tables, species, per_call):
+    from paper_2609_31258_amd import mucite
+    f, ions, _, op, _ = synth.config_c1t(n)
+    if species > 1:
+        ions = synth.config_c5_species(species)
+    op.adaptive, op.sc_on, op.sc_every, op.sort_every = 1, 1, 2, 13
+    op.sample_every, op.sample_stride = 5, 3
+    op.langevin_on, op.lv_switch, op.lv_dt_max = int(species > 1), 0.05, 0.3 * op.dt
+    snap = synth.pack_snapshot(n, f, seed=4, z_hi=4e-3, r_hi=5e-4, v_sigma=60.0)
+    snap["tag"] = (np.arange(n) % species).astype(np.int32)
+    out = []
+    with mucite.Sim(seed=3, pack_capacity=n + 100, precision=precision, fp32_tables=tables,
+                    sample_capacity=40 * (n + 100)) as g:
+        g.setup(f, ions, [], op)
+        g.write_packs(snap)
+
+        def advance(steps):
+            left = steps
+            while left > 0:
+                g.step(min(per_call, left))
+                left -= per_call
+            i = g.info()
+            out.append(np.array([i["time"], i["last_dt"], i["step"]]))
+
+        advance(40)
+        # a source makes the host size the steps, until it has emitted all
+        g.define_source(synth.Source(kind=1, current_a=1e-9, packs_per_step=7, n_total=21, sigma_r=1e-4, r_trunc=3e-4))
+        advance(3)
+        advance(20)
+        p = g.read_packs()
+        o = np.argsort(p["id"], kind="stable")
+        out += [p[k][o] for k in sorted(p)]
+        t = g.read_tallies()
+        out += [np.asarray(t[k]) for k in ("n_cand", "n_coll", "n_langevin", "pack_steps", "class_n")]
+        s = g.read_samples()
+        out.append(np.sort(s, order=list(s.dtype.names)))
+    return out
+
+
+@pytest.mark.parametrize("n,precision,tables,species", [
+    (1, 0, False, 1), (257, 0, False, 3), (3000, 0, False, 1),
+    (1, 1, False, 1), (255, 1, True, 1), (3000, 1, False, 3)])
+def test_steps_of_one_call_equal_calls_of_one_step(n, precision, tables, species):
+    _say("adaptive launches:", n, "packs, precision", precision, "species", species)
+    one, many = _run(n, precision, tables, species, 1), _run(n, precision, tables, species, 1000)
+    assert one[0][1] > 0.0 and one[0][2] == 40
+    for a, b in zip(one, many):
+        assert a.shape == b.shape and a.tobytes() == b.tobytes()
