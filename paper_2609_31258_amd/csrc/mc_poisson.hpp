@@ -11,8 +11,8 @@
 //                    the FFT length does not fit in a workgroup's LDS)
 //   k_tri_table, k_tri  per-mode tridiagonal solve in r by scans, one
 //                    wavefront per mode (FP64 form)
-//   k_pcr            the same solve by parallel cyclic reduction, one
-//                    wavefront per mode, FP64 arithmetic (FP32 form)
+//   k_pcr            the same solve by parallel cyclic reduction, a thread
+//                    per row or two, FP64 arithmetic (FP32 form)
 //   k_thomas_coef, k_thomas  the same solve by Thomas sweeps (one thread per
 //                    mode), for grids taller than these take
 //   k_mask_*         the metal-mask Dirichlet condition by a capacitance-
@@ -188,41 +188,44 @@ __global__ __launch_bounds__(256) void k_thomas(D *bh, const double *cp, const d
     }
 }
 
-// The same systems by parallel cyclic reduction: one wavefront per mode k,
-// its nu = nr - 1 rows padded with identity rows to 64 R (R rows per lane,
-// held in LDS), W wavefronts (modes) per block.  Step h = 1, 2, 4, ...
-// eliminates every row's couplings to the rows h away:
+// The same systems by parallel cyclic reduction: T threads per mode k, its nu
+// = nr - 1 rows padded with identity rows to N = T R (R rows per thread, held
+// in registers and, for the neighbours, in LDS), W modes per block.  Step h =
+// 1, 2, 4, ... eliminates every row's couplings to the rows h away:
 //   alpha = -a_i / b_{i-h},  gamma = -c_i / b_{i+h},
 //   a_i <- alpha a_{i-h},  c_i <- gamma c_{i+h},
 //   b_i <- b_i + alpha c_{i-h} + gamma a_{i+h},  d_i <- d_i + alpha d_{i-h} + gamma d_{i+h},
-// rows outside [0, 64 R) taken as identity rows; after log2(64 R) steps
-// x_i = d_i / b_i.  FP64 throughout; each step reads one LDS copy of the
-// rows and writes the other.  The rows are those of k_thomas_coef
+// rows outside [0, N) taken as identity rows; after log2 N steps x_i = d_i /
+// b_i.  FP64 throughout; each step reads one LDS copy of the rows and writes
+// the other.  The rows are those of k_thomas_coef
 // (lower lo_i, upper up_i, diagonal -(lo_i + up_i) + lambda_k; the axis row
 // -4/dr^2 + lambda_k, 4/dr^2; x = 0 beyond the last row): strictly
 // diagonally dominant since lambda_k < 0, where cyclic reduction is stable.
-// 1022 modes of 255 rows are 1022 wavefronts across the chip instead of
-// 1022 threads stepping through 255 dependent rows.  The rows of the block's
-// W modes are read and written together, W neighbours at a time.
+// The rows of the block's W modes are read and written together, W neighbours
+// at a time.  What bounds it is the chain of loads, division and barrier of
+// each level, so the rows of a mode are spread over as many threads as LDS
+// leaves room for (4 to 8 wavefronts a SIMD): with a wavefront per mode there
+// was one a SIMD.  1022 modes of 255 rows 12.6 -> 8.3 us, 2046 modes of 511
+// rows 62 -> 24 us, the whole solve of 2046 modes of 1023 rows 325 -> 129 us.
 //
 // The FP32 form keeps this solve beside the faster scans (below): it rounds
 // the modes to FP32, and its transforms carry the last bit of a mode into the
 // seventh digit of the potential, so a run of it (from a saved state, or with
 // the capacitance matrix of its mask) stays what it was bit for bit.
-template <class D, int R, int W>
-__global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, double dr, double dz) {
-    constexpr int N = 64 * R;
+template <class D, int T, int R, int W>
+__global__ __launch_bounds__(T * W) void k_pcr(D *bh, int32_t nr, int32_t nz, double dr, double dz) {
+    constexpr int N = T * R;
     // two copies of (a, b, c, d): each step reads one and writes the other
     __shared__ double s_abcd[2][4][W][N];
     const int32_t m = nz - 2, nu = nr - 1;
-    const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int w = threadIdx.x / T, at = threadIdx.x % T;
     const int32_t k0 = xcd_place((m + W - 1) / W) * W;  // first mode (less one) of the block
     if (k0 >= m) return;
     const int32_t k = k0 + w + 1;  // mode 1..m (uniform per wavefront)
     const int wi = threadIdx.x % W, i0 = threadIdx.x / W;
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        const int32_t i = i0 + 64 * q;
+        const int32_t i = i0 + T * q;
         s_abcd[0][3][wi][i] = i < nu && k0 + wi < m ? (double)bh[(int64_t)i * m + k0 + wi] : 0.0;
     }
     const bool live = k <= m;
@@ -231,9 +234,10 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
         const double sk = sin(kPi * (double)k / (2.0 * (double)(nz - 1)));
         lam = -(4.0 / (dz * dz)) * sk * sk;
     }
+    double ra[R], rb[R], rc[R], rd[R];
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        const int32_t i = lane + 64 * q;
+        const int32_t i = at + T * q;
         double a = 0.0, b = 1.0, c = 0.0;
         if (live && i < nu) {
             if (i == 0) {
@@ -247,35 +251,37 @@ __global__ __launch_bounds__(64 * W) void k_pcr(D *bh, int32_t nr, int32_t nz, d
             }
             if (i == nu - 1) c = 0.0;  // Phi = 0 at r = R
         }
-        s_abcd[0][0][w][i] = a;
-        s_abcd[0][1][w][i] = b;
-        s_abcd[0][2][w][i] = c;
+        ra[q] = s_abcd[0][0][w][i] = a;
+        rb[q] = s_abcd[0][1][w][i] = b;
+        rc[q] = s_abcd[0][2][w][i] = c;
     }
     __syncthreads();
+#pragma unroll
+    for (int q = 0; q < R; ++q) rd[q] = s_abcd[0][3][w][at + T * q];
     int src = 0;
     for (int h = 1; h < N; h <<= 1) {
         const double *A = s_abcd[src][0][w], *B = s_abcd[src][1][w], *C = s_abcd[src][2][w], *Dv = s_abcd[src][3][w];
         double *A2 = s_abcd[1 - src][0][w], *B2 = s_abcd[1 - src][1][w], *C2 = s_abcd[1 - src][2][w],
                *D2 = s_abcd[1 - src][3][w];
-#pragma unroll 4
+#pragma unroll
         for (int q = 0; q < R; ++q) {
-            const int32_t i = lane + 64 * q, l = i - h, u = i + h;
+            const int32_t i = at + T * q, l = i - h, u = i + h;
             const double al = l >= 0 ? A[l] : 0.0, bl = l >= 0 ? B[l] : 1.0, cl = l >= 0 ? C[l] : 0.0,
                          dl = l >= 0 ? Dv[l] : 0.0;
             const double au = u < N ? A[u] : 0.0, bu = u < N ? B[u] : 1.0, cu = u < N ? C[u] : 0.0,
                          du = u < N ? Dv[u] : 0.0;
-            const double alpha = -A[i] / bl, gamma = -C[i] / bu;
-            A2[i] = alpha * al;
-            C2[i] = gamma * cu;
-            B2[i] = B[i] + alpha * cl + gamma * au;
-            D2[i] = Dv[i] + alpha * dl + gamma * du;
+            const double alpha = -ra[q] / bl, gamma = -rc[q] / bu;
+            A2[i] = ra[q] = alpha * al;
+            C2[i] = rc[q] = gamma * cu;
+            B2[i] = rb[q] = rb[q] + alpha * cl + gamma * au;
+            D2[i] = rd[q] = rd[q] + alpha * dl + gamma * du;
         }
         __syncthreads();
         src = 1 - src;
     }
 #pragma unroll
     for (int q = 0; q < R; ++q) {
-        const int32_t i = i0 + 64 * q;
+        const int32_t i = i0 + T * q;
         if (i < nu && k0 + wi < m) bh[(int64_t)i * m + k0 + wi] = (D)(s_abcd[src][3][wi][i] / s_abcd[src][1][wi][i]);
     }
 }
@@ -978,11 +984,11 @@ inline hipError_t poisson_solve(const PoissonGrid &g, const unsigned long long *
     } else if (takes_thomas(nu, m)) {
         k_thomas<D><<<(m + 255) / 256, 256, 0, st>>>(bh, g.tcp, g.tinv, g.nr, g.nz, g.dr);
     } else if (nu <= 256) {
-        k_pcr<D, 4, 4><<<xcd_blocks((m + 3) / 4), 256, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+        k_pcr<D, 256, 1, 4><<<xcd_blocks((m + 3) / 4), 1024, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
     } else if (nu <= 512) {
-        k_pcr<D, 8, 2><<<xcd_blocks((m + 1) / 2), 128, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+        k_pcr<D, 512, 1, 2><<<xcd_blocks((m + 1) / 2), 1024, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
     } else {
-        k_pcr<D, 16, 1><<<xcd_blocks(m), 64, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
+        k_pcr<D, 512, 2, 1><<<xcd_blocks(m), 512, 0, st>>>(bh, g.nr, g.nz, g.dr, g.dz);
     }
     if ((e = hipGetLastError()) != hipSuccess) return e;
     if (B.L > 0)

@@ -1,6 +1,7 @@
 """The Poisson solve at the edges of its kernels against the oracle: row counts
 on both sides of each rows-per-lane class of the tridiagonal scans (2, 4, 8, 16
-rows per lane, Thomas sweeps beyond 1024 rows), and row lengths on both sides
+rows per lane, Thomas sweeps beyond 1024 rows) and of the cyclic
+reduction (256 and 512 rows, blocks not full of modes), and row lengths on both sides
 of each FFT length.  Bars: FP64 Phi within 1e-10 of max|Phi|, E within 1e-8 of
 max|E|; FP32 form (rounding 6e-8 per operation, about 13 butterfly levels in
 each of four FFTs) Phi within 5e-6 and E within 1e-4."""
@@ -17,7 +18,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("precision,nr,nz", [
     (0, 3, 5), (0, 4, 34), (0, 129, 34), (0, 130, 34), (0, 257, 34), (0, 258, 34), (0, 513, 34), (0, 514, 34),
-    (0, 1025, 34), (0, 1026, 34), (1, 129, 34), (1, 258, 34), (1, 514, 34), (1, 1025, 34),
+    (0, 1025, 34), (0, 1026, 34), (1, 129, 34), (1, 257, 35), (1, 258, 34), (1, 513, 35), (1, 514, 34), (1, 1025, 34),
     (0, 9, 130), (0, 9, 131), (0, 9, 258), (0, 9, 259), (0, 9, 514), (0, 9, 515), (0, 9, 1026), (0, 9, 1027),
     (0, 9, 2050), (0, 270, 1500), (1, 9, 258), (1, 9, 259), (1, 9, 515), (1, 9, 1027), (1, 9, 2050), (1, 9, 2051)])
 def test_poisson_kernel_edges(precision, nr, nz):
