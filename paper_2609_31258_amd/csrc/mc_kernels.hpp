@@ -707,9 +707,14 @@ template <class P, class Tab>
 constexpr int step_waves() {
     return P::kTwo ? (sizeof(Tab) == 8 ? 5 : 4) : 3;
 }
+// No more than five: the FP32 form's one-species kernel, which fits six
+// without spilling, takes 2.7 % longer with them (1e6 packs at 1e5 Pa: 411 us
+// a step with six, 400 with five, 406 with four, 431 with three).
+constexpr int kStepWavesMax = 5;
 
 template <class P, class Tab, bool kOneSpecies>
-__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step(StepArgs<P, Tab> a) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+k_step(StepArgs<P, Tab> a) {
     P::prepare_tables(a.tables);
     StepCount n{0, 0, 0, 0, 0, 0, 0};
     const unsigned block = !kOneSpecies && a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
@@ -854,8 +859,8 @@ static __global__ __launch_bounds__(kHotRep) void k_dt_begin(unsigned long long 
 // block belongs to one query (descriptors in device memory, whose member a is
 // the query's).
 template <class P, class Tab, class Desc>
-__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_multi(const Desc *descs, const int32_t *prefix,
-                                                                            int32_t nq) {
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+k_step_multi(const Desc *descs, const int32_t *prefix, int32_t nq) {
     const int q = block_query(prefix, nq);
     const StepArgs<P, Tab> &a = descs[q].a;
     P::prepare_tables(a.tables);

@@ -931,8 +931,9 @@ struct PoissonGrid {
 // up to 1024 rows while the modes are too few to fill the GPU with Thomas
 // sweeps (one thread per mode), Thomas sweeps otherwise: on the 1024 x 8192
 // grid (8190 modes of 1023 rows) the sweeps took 0.21 ms and cyclic reduction
-// 0.80 ms; on the 256 x 1024 grid (1022 modes of 255 rows) the sweeps took
-// 0.056 ms and cyclic reduction 0.015 ms.
+// (then a wavefront per mode) 0.80 ms; on the 256 x 1024 grid (1022 modes of
+// 255 rows) the sweeps took 0.056 ms and cyclic reduction 0.015 ms, now 0.008.
+// A grid keeps its solve: the two differ in the last bits.
 constexpr int32_t kPcrMaxModes = 4096;
 inline bool takes_scans(bool fp32, int32_t nu) { return !fp32 && nu <= kTriMaxRows; }
 inline bool takes_thomas(int32_t nu, int32_t m) { return !(nu <= 256 || (nu <= 1024 && m < kPcrMaxModes)); }
