@@ -813,8 +813,10 @@ __device__ __forceinline__ void block_limits(const StepArgs<P, Tab> &a, int64_t 
 }
 
 template <class P, class Tab>
-__global__ __launch_bounds__(256) void k_dt_limits(StepArgs<P, Tab> a, unsigned long long *rep, int32_t n_lines) {
-    block_limits(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, a.c0, rep, n_lines);
+__global__ __launch_bounds__(256) void k_dt_limits(StepArgs<P, Tab> a, unsigned long long *rep, int32_t n_lines,
+                                                   const DtRecord *rec = nullptr) {
+    // (rec: at the RF coefficient of the step that the record names next)
+    block_limits(a, (int64_t)blockIdx.x * blockDim.x + threadIdx.x, rec ? rec->c : a.c0, rep, n_lines);
 }
 
 // Replica lines -> out[0] (limit bits), out[1] (Langevin flag); the lines are

@@ -40,7 +40,8 @@ constexpr int64_t kAggBlocks = 1024;
 struct EvPair {
     hipEvent_t a, b;
     int kind;
-    int64_t count;  // launches that the pair stands for: a stretch's launch counts as its steps
+    int64_t count;  // launches that the pair stands for: a stretch's launch counts as its steps, an
+                    // adaptive step's that found no step to take as none
 };
 
 inline unsigned grid_for(int64_t n) { return (unsigned)((n + kBlock - 1) / kBlock); }
@@ -81,6 +82,7 @@ struct mc_ctx {
     // adaptive step (Eq. 1)
     unsigned long long *dt_rep = nullptr, *dt_out = nullptr;
     DtRecord *dt_rec = nullptr;  // two records of an adaptive run on the device (k_stretch_adaptive)
+    DtStep *dt_found = nullptr;  // the step found (k_dt_find)
     double c_next = 0.0;         // RF coefficient at t, as the device found it
     bool c_next_valid = false;
     double t = 0.0, t_next_pic = 0.0, last_dt = 0.0;
@@ -275,7 +277,7 @@ static void resolve_timing(mc_ctx *ctx) {
     for (auto &p : ctx->ev_used) {
         float ms = 0.f;
         (void)hipEventSynchronize(p.b);
-        if (hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) ctx->t_ms[p.kind] += ms;
+        if (p.count > 0 && hipEventElapsedTime(&ms, p.a, p.b) == hipSuccess) ctx->t_ms[p.kind] += ms;
         ctx->t_launch[p.kind] += p.count;
         ctx->ev_pool.push_back(p.a);
         ctx->ev_pool.push_back(p.b);
@@ -533,6 +535,24 @@ static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, doub
 template <class P, class Tab>
 static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d) {
     const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
+    if constexpr (P::kTwo) {
+        if (ctx->n_slots > kAdaptivePacks32) {
+            k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
+            LAUNCHCHK();
+            {
+                Timer t(ctx, MC_K_STEP);
+                const unsigned nb = (unsigned)((ctx->n_slots + kStepBlock - 1) / kStepBlock);
+                if (ctx->ions.size() == 1)
+                    k_step_found<P, Tab, true><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
+                else
+                    k_step_found<P, Tab, false><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
+            }
+            LAUNCHCHK();
+            k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, d.next, kDtLines, d.out);
+            LAUNCHCHK();
+            return MC_OK;
+        }
+    }
     Timer t(ctx, MC_K_STEP);
     if constexpr (P::kTwo) {
         const unsigned nb = std::max(1u, grid_for(ctx->n_slots));
@@ -625,6 +645,7 @@ static int32_t adaptive_buffers(mc_ctx *ctx) {
     int32_t rc = dalloc_t(ctx, &ctx->dt_rep, 4 * (size_t)kHotLen);
     if (!rc) rc = dalloc_t(ctx, &ctx->dt_out, 2);
     if (!rc) rc = dalloc_t(ctx, &ctx->dt_rec, 2);
+    if (!rc) rc = dalloc_t(ctx, &ctx->dt_found, 1);
     if (rc) return rc;
     k_dt_reset<<<4, kHotRep, 0, ctx->stream>>>(ctx->dt_rep);
     LAUNCHCHK();
@@ -1260,8 +1281,7 @@ static bool sources_idle(const mc_ctx *ctx) {
 // Adaptive steps with the step length kept on the device: up to max_steps
 // steps, as many as run before the next space-charge update falls due, then
 // one read of the record.  How many that will be is guessed from the last
-// step's length; steps enqueued beyond it are not taken on the device.  (With
-// the kernels timed, only as many are enqueued as are sure to be taken.)
+// step's length; steps enqueued beyond it are not taken on the device.
 // *done receives the steps taken.
 static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     *done = 0;
@@ -1294,7 +1314,7 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         // the steps before the next update's time: at least those of the
         // largest length, likely those of the last one's
         const double room = ctx->t_next_pic - tol - t0;
-        const bool guess = !ctx->opt.timing && ctx->last_dt > 0.0 && ctx->last_dt < op.dt;
+        const bool guess = ctx->last_dt > 0.0 && ctx->last_dt < op.dt;
         const double n = std::ceil(room / (guess ? ctx->last_dt : op.dt)) + (guess ? 1.0 : 0.0);
         k = std::min<int64_t>(k, (int64_t)std::max(1.0, std::min(n, 1024.0)));
     }
@@ -1339,6 +1359,9 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     ctx->c_next = rec.c;
     ctx->step = step0 + rec.steps;
     *done = rec.steps;
+    if (ctx->opt.timing)  // (a pair per launch, the last of those enqueued)
+        for (int64_t j = 0; j < k - rec.steps && j < (int64_t)ctx->ev_used.size(); ++j)
+            ctx->ev_used[ctx->ev_used.size() - 1 - (size_t)j].count = 0;
     if (rec.halted)
         return fail(ctx, MC_ENUMERIC, "adaptive step collapsed below 1e-9 dt at step " + std::to_string(ctx->step));
     ctx->last_dt = rec.dt;

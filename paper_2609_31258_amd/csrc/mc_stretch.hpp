@@ -235,7 +235,7 @@ __device__ __forceinline__ void collide_group(const StepArgs<P, Tab> &a, const S
 // space-charge update comes first): then the launches that follow only hand
 // the record on.  One launch instead of three (limits, their reduction, step):
 // 1e5 packs 24.5 -> 15.1 us a step in the FP32 form (Langevin branch), 36.8 ->
-// 22.1 in FP64; 1e6 packs 55.2 -> 52.1 and 166 -> 125.  Below 1e5 packs what is
+// 22.1 in FP64; 1e6 FP64 packs 166 -> 125.  Below 1e5 packs what is
 // left is the launch and the chain of loads, limits and step in each.
 constexpr int kDtLines = 64;  // a lane of the reducing wavefront per line
 static_assert(kDtLines <= kHotRep);
@@ -572,6 +572,36 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_adaptive(S
     step_one<P, Tab, kOneSpecies>(a, s, n, a.k0, a.k1);
     flush_counts(a.t, n);
     block_limits(a, s, a.c1, d.next, kDtLines);
+}
+
+// Above kAdaptivePacks32 packs the FP32 form takes its adaptive step in three
+// launches: a wavefront finds the step, k_step's code takes it, k_dt_limits
+// follows.  There the look for the step at the start of every block, in each
+// round of blocks, costs more than the launches: 1e6 packs spread over 0.3 mm
+// 51.5 us a step so against 54.0 in one launch, on the Langevin branch 53.7
+// against 54.8.  (Three launches with a pass of their own for the reduction
+// took 4e5 packs 35 to 38 us, one launch 28.)
+constexpr int64_t kAdaptivePacks32 = 800'000;
+
+static __global__ __launch_bounds__(64) void k_dt_find(DtArgs d, DtStep *found) {
+    const DtStep s = dt_step(d);
+    if (threadIdx.x == 0) *found = s;
+}
+
+template <class P, class Tab, bool kOneSpecies>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+k_step_found(StepArgs<P, Tab> a, const DtStep *found) {
+    if (!found->go) return;
+    a.t0 = found->t0;
+    a.dt = found->dt;
+    a.c0 = found->c0;
+    a.ch = found->ch;
+    a.c1 = found->c1;
+    P::prepare_tables(a.tables);
+    StepCount n{0, 0, 0, 0, 0, 0, 0};
+    const unsigned block = !kOneSpecies && a.from_last ? gridDim.x - 1 - blockIdx.x : blockIdx.x;
+    step_one<P, Tab, kOneSpecies>(a, (int64_t)block * blockDim.x + threadIdx.x, n, a.k0, a.k1);
+    flush_counts(a.t, n);
 }
 
 // The resident queries of a server, each over its own steps; each block
