@@ -66,19 +66,9 @@ OPS_PACK_STEP = 567       # RK4 with four bilinear field gathers, classification
 OPS_CANDIDATE = 276       # every candidate inside the step: two Philox blocks, wait, partner draw, test
 OPS_ACCEPTED = 161        # accepted candidate: third block, impulsive update, scattering
 OPS_EXCHANGE = 18         # internal-energy exchange (taken with probability alpha)
+OPS_LANGEVIN = 550        # a pack-step on the hybrid Langevin branch: RK4, classification and gas gather as
+                          # above, one Philox block, friction, decay and three normals for wait and dissociation
 
-# Algorithmic HBM bytes per active pack-step of the fused step kernel in a
-# context that defines one species (every workload timed here): read status,
-# id, position, velocity, internal energy and hazard; write back position,
-# velocity, internal energy and hazard.  FP64: 76 + 64 B.  FP32 form
-# (two-float position and internal energy, FP32 velocity and hazard):
-# 60 + 48 B.  With several species each pack also reads its 4-byte tag.  An
-# inactive slot costs its status word (4 B).
-BYTES_STEP = {"fp64": 140, "fp32": 108}
-# A pack on the hybrid Langevin branch neither reads nor writes its internal
-# energy and hazard: FP32 form 48 B read (status, id, position, velocity) +
-# 36 B written (position, velocity).
-BYTES_LANGEVIN = {"fp64": 108, "fp32": 84}
 # Deposit: status, position (FP64, or the FP32 form's hi+lo pairs) and the
 # int64 charge of every active pack (the LDS-aggregated grid atomics are
 # counted as L2 traffic, not HBM), plus one write of the int64 grid.
@@ -89,7 +79,7 @@ HBM_PEAK = 8.0e12
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "k_step_c2_traffic.txt")
 VALU_FILE = os.path.join(ROOT, "profiles", "k_step_c2_valu.txt")
 KERNEL_SOURCES = [os.path.join(ROOT, "paper_2609_31258_amd", "csrc", f)
-                  for f in ("mc_kernels.hpp", "mc_device.hpp", "mc_math64.hpp")]
+                  for f in ("mc_kernels.hpp", "mc_stretch.hpp", "mc_device.hpp", "mc_math64.hpp")]
 
 
 def _code_only(text: str) -> str:
@@ -261,10 +251,10 @@ def run_gpu(precision: int, steps: int, warmup: int, langevin: bool = False, sor
 def run_population_sweep(populations, steps: int, sort_every: int):
     """The hybrid form's step kernel at several populations of the 256x1024
     workload (its emission ramp cut to each population, then `steps` steps
-    with HIP events): per-launch time against packs, fitted as intercept +
-    slope x packs.  The slope is the marginal cost of a pack (its bytes over
-    it give the bandwidth the kernel sustains once it is full); the intercept
-    is what a launch costs beyond that (ramp-up, drain, the events)."""
+    with HIP events): time per step (a launch takes the steps up to the next
+    update) against packs, fitted as intercept + slope x packs.  The slope is
+    the marginal cost of a pack; the intercept is what a launch costs beyond
+    that (ramp-up, drain, the events), over its steps."""
     import numpy as np
     from paper_2609_31258_amd import mucite, synth
     rows = []
@@ -283,53 +273,46 @@ def run_population_sweep(populations, steps: int, sort_every: int):
         rows.append({"packs": n, "active": r["active"], "wavefronts": (n + 63) // 64, "step_ms": ms,
                      "langevin_fraction": r["langevin"] / max(r["pack_steps"], 1)})
         _say(f"sweep: {n} packs, step kernel {ms:.5f} ms")
-    out = {"kernel": "k_step (hybrid form)", "steps_per_population": steps, "rows": rows}
+    out = {"kernel": "k_stretch (hybrid form)", "steps_per_population": steps, "rows": rows}
     if len(rows) >= 2:
         x = np.array([q["active"] for q in rows], dtype=np.float64)
         y = np.array([q["step_ms"] for q in rows], dtype=np.float64)
         slope, icpt = np.polyfit(x, y, 1)
-        out["fit"] = {"slope_ps_per_pack": slope * 1e9, "intercept_us": icpt * 1e3,
-                      "marginal_GBps": BYTES_LANGEVIN["fp32"] / (slope * 1e-3) / 1e9 if slope > 0 else None,
-                      "bytes_per_pack_step": BYTES_LANGEVIN["fp32"]}
+        out["fit"] = {"slope_ps_per_pack": slope * 1e9, "intercept_us": icpt * 1e3}
     return out
 
 
-def hbm_roofline(r, precision: str, kernel: str, traffic_key=None):
-    """HBM roofline of a bandwidth-bound kernel from its algorithmic bytes."""
-    key = {"step": "step", "deposit": "deposit"}[kernel]
-    ms, launches = r["timing"]["ms"][key], max(r["timing"]["launches"][key], 1)
+def deposit_roofline(r, precision: str):
+    """HBM roofline of the deposit from its algorithmic bytes."""
+    ms, launches = r["timing"]["ms"]["deposit"], max(r["timing"]["launches"]["deposit"], 1)
     avg_s = ms / 1e3 / launches
-    if kernel == "step":
-        idle = max(r["slots"] * r["steps"] - r["pack_steps"], 0)
-        lang = r.get("langevin", 0)
-        nbytes = ((r["pack_steps"] - lang) * BYTES_STEP[precision] + lang * BYTES_LANGEVIN[precision] +
-                  4 * idle) / launches
-    else:
-        nbytes = r["active"] * BYTES_DEPOSIT[precision] + GRID_BYTES  # population nearly constant in the window
+    nbytes = r["active"] * BYTES_DEPOSIT[precision] + GRID_BYTES  # population nearly constant in the window
     achieved = nbytes / avg_s if avg_s > 0 else 0.0
     return {"bound": "hbm", "achieved": achieved / 1e9, "peak": HBM_PEAK / 1e9, "unit": "GB/s",
-            "frac": achieved / HBM_PEAK, "traffic": measured_traffic(traffic_key) if traffic_key else None,
-            "kernel": "deposit (k_deposit)" if kernel == "deposit" else "k_step", "avg_launch_ms": avg_s * 1e3,
-            "launches": launches, "bytes_per_launch": nbytes,
-            "issue": measured_issue(traffic_key) if kernel == "step" and traffic_key else None}
+            "frac": achieved / HBM_PEAK, "traffic": measured_traffic("deposit_" + precision),
+            "kernel": "deposit (k_deposit)", "avg_launch_ms": avg_s * 1e3,
+            "launches": launches, "bytes_per_launch": nbytes, "issue": None}
 
 
-def roofline(r, precision: str, alpha: float):
-    """Vector-ALU roofline of the fused step: algorithmic operations per
-    launch over the launch's average HIP-event duration, against the
-    published vector peak of the form's arithmetic type."""
+def roofline(r, form: str, alpha: float):
+    """Vector-ALU roofline of the fused step: algorithmic operations per step
+    over the step's average HIP-event duration, against the published vector
+    peak of the form's arithmetic type.  (The hybrid form's launches take the
+    steps between two updates; they are counted by their steps.)"""
     ms = r["timing"]["ms"]["step"]
     launches = max(r["timing"]["launches"]["step"], 1)
     avg_s = ms / 1e3 / launches
-    ops = (r["pack_steps"] * OPS_PACK_STEP + r["cand"] * OPS_CANDIDATE +
+    lang = r.get("langevin", 0)
+    ops = ((r["pack_steps"] - lang) * OPS_PACK_STEP + lang * OPS_LANGEVIN + r["cand"] * OPS_CANDIDATE +
            r["coll"] * OPS_ACCEPTED + r.get("exch", alpha * r["coll"]) * OPS_EXCHANGE)
     ops_per_launch = ops / launches
     achieved = ops_per_launch / avg_s
-    peak = PEAK_OPS[precision if precision in PEAK_OPS else "fp32"]
+    peak = PEAK_OPS[form if form in PEAK_OPS else "fp32"]
     return {"bound": "alu", "achieved": achieved / 1e12, "peak": peak / 1e12, "unit": "TFLOP/s",
-            "frac": achieved / peak, "traffic": measured_traffic(precision),
-            "kernel": "k_step (fused push/classify/collide)", "avg_launch_ms": avg_s * 1e3, "launches": launches,
-            "ops_per_launch": ops_per_launch, "issue": measured_issue(precision)}
+            "frac": achieved / peak, "traffic": measured_traffic(form),
+            "kernel": ("k_stretch (the step's code, several steps a launch)" if form == "hybrid"
+                       else "k_step (fused push/classify/collide)"), "avg_launch_ms": avg_s * 1e3,
+            "launches": launches, "ops_per_launch": ops_per_launch, "issue": measured_issue(form)}
 
 
 def default_alpha() -> float:
@@ -756,22 +739,21 @@ def main():
                    "ramp_steps": r["ramp_steps"], "first_timed_step": r["start_step"], "sc_every": 10,
                    "sort_every": args.sort_every,
                    "dt_s": 0.5e-9, "precision": main_key},
-        "roofline": hbm_roofline(r["ev"], "fp32", "step", "hybrid") if main_key == "hybrid"
-        else roofline(r["ev"], main_key, default_alpha()),
+        "roofline": roofline(r["ev"], main_key, default_alpha()),
         "collisions_per_s": r["coll"] / r["wall"],
         "candidates_per_pack_step": r["cand"] / max(r["pack_steps"], 1),
         "kernel_ms": r["ev"]["timing"]["ms"],
         "ms_per_step_with_kernel_events": r["ev"]["wall"] * 1e3 / args.steps,
     }
     if main_key != "hybrid":
-        out["deposit_roofline"] = hbm_roofline(r["ev"], main_key, "deposit", "deposit_" + main_key)
+        out["deposit_roofline"] = deposit_roofline(r["ev"], main_key)
     if "fp32" in res and main_key == "fp64":
         q = res["fp32"]
         out["fp32_form"] = {"value": q["pack_steps"] / q["wall"], "unit": "pack-steps/s",
                             "ms_per_step": q["wall"] * 1e3 / args.steps, "dtype": "f32 (BF16 tables)",
                             "active": q["active"], "speedup_vs_fp64": (q["pack_steps"] / q["wall"]) / value,
                             "roofline": roofline(q["ev"], "fp32", default_alpha()), "collisions_per_s": q["coll"] / q["wall"],
-                            "deposit_roofline": hbm_roofline(q["ev"], "fp32", "deposit", "deposit_fp32"),
+                            "deposit_roofline": deposit_roofline(q["ev"], "fp32"),
                             "kernel_ms": q["ev"]["timing"]["ms"],
                             "ms_per_step_with_kernel_events": q["ev"]["wall"] * 1e3 / args.steps,
                             "error_vs_fp64": precision_report(r["tallies"], q["tallies"])}
@@ -783,7 +765,7 @@ def main():
                               "active": h["active"], "langevin_fraction": h["langevin"] / max(h["pack_steps"], 1),
                               "speedup_vs_explicit_fp32": (h["pack_steps"] / h["wall"]) / (ref["pack_steps"] / ref["wall"])
                               if ref else None,
-                              "roofline": hbm_roofline(h["ev"], "fp32", "step", "hybrid"),
+                              "roofline": roofline(h["ev"], "hybrid", default_alpha()),
                               "kernel_ms": h["ev"]["timing"]["ms"],
                               "ms_per_step_with_kernel_events": h["ev"]["wall"] * 1e3 / args.steps}
     out["cpu_baseline"] = None if args.no_cpu_baseline else cpu_baseline(args.cpu_steps)
