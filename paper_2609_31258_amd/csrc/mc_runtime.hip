@@ -534,6 +534,11 @@ static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, doub
 // One step of an adaptive run on the device.
 template <class P, class Tab>
 static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d) {
+    if (ctx->n_slots == 0) {  // time alone
+        k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
+        LAUNCHCHK();
+        return MC_OK;
+    }
     const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
     if constexpr (P::kTwo) {
         if (ctx->n_slots > kAdaptivePacks32) {
@@ -555,7 +560,7 @@ static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtA
     }
     Timer t(ctx, MC_K_STEP);
     if constexpr (P::kTwo) {
-        const unsigned nb = std::max(1u, grid_for(ctx->n_slots));
+        const unsigned nb = grid_for(ctx->n_slots);
         if (ctx->ions.size() == 1) k_step_adaptive<P, Tab, true><<<nb, kBlock, 0, ctx->stream>>>(a, d);
         else k_step_adaptive<P, Tab, false><<<nb, kBlock, 0, ctx->stream>>>(a, d);
     } else {
@@ -564,7 +569,7 @@ static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtA
         all.s.st.n = 1;
         all.s.st.n_slots[0] = ctx->n_slots;
         all.d = d;
-        const unsigned nb = (unsigned)std::max<int64_t>(1, (ctx->n_slots + 63) / 64);
+        const unsigned nb = (unsigned)((ctx->n_slots + 63) / 64);
         k_stretch_adaptive<P, Tab><<<nb, 64, 0, ctx->stream>>>(all);
     }
     LAUNCHCHK();
@@ -1359,7 +1364,7 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     ctx->c_next = rec.c;
     ctx->step = step0 + rec.steps;
     *done = rec.steps;
-    if (ctx->opt.timing)  // (a pair per launch, the last of those enqueued)
+    if (ctx->opt.timing && ctx->n_slots > 0)  // (a pair per launch, the last of those enqueued)
         for (int64_t j = 0; j < k - rec.steps && j < (int64_t)ctx->ev_used.size(); ++j)
             ctx->ev_used[ctx->ev_used.size() - 1 - (size_t)j].count = 0;
     if (rec.halted)

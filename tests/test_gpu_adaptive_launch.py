@@ -31,7 +31,8 @@ def _run(n, precision, tables, species, per_call):
     with mucite.Sim(seed=3, pack_capacity=n + 100, precision=precision, fp32_tables=tables,
                     sample_capacity=min(40 * (n + 100), 5_000_000)) as g:
         g.setup(f, ions, [], op)
-        g.write_packs(snap)
+        if n:
+            g.write_packs(snap)
 
         def advance(steps):
             left = steps
@@ -57,7 +58,7 @@ def _run(n, precision, tables, species, per_call):
 
 
 @pytest.mark.parametrize("n,precision,tables,species", [
-    (1, 0, False, 1), (257, 0, False, 3), (3000, 0, False, 1),
+    (0, 0, False, 1), (0, 1, False, 1), (1, 0, False, 1), (257, 0, False, 3), (3000, 0, False, 1),
     (1, 1, False, 1), (255, 1, True, 1), (3000, 1, False, 3),
     (800_000, 1, False, 1), (800_001, 1, False, 3)])
 def test_steps_of_one_call_equal_calls_of_one_step(n, precision, tables, species):
