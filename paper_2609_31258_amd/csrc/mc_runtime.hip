@@ -1048,6 +1048,9 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     if (!valid_tables(t, (int64_t)g->nr * g->nz))
         return fail(ctx, MC_EINVAL, "field table with a non-finite value or a negative pressure or temperature");
     HIPCHK(hipSetDevice(ctx->opt.device));
+    // (nothing of a load that was refused half way: the solve goes by which of its tables are there)
+    ctx->pg = PoissonGrid{};
+    ctx->blu = Bluestein{};
     ctx->nr = g->nr;
     ctx->nz = g->nz;
     ctx->dr = g->dr;

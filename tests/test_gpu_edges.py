@@ -194,3 +194,36 @@ def test_vacuum_and_zero_temperature_gas_match_the_oracle(precision):
     assert ta["n_cand"] == 0 and tb["n_cand"] == 0
     for k in ("x", "y", "z", "vx", "vy", "vz", "e_int", "h", "status"):
         assert np.array_equal(pa[k], pb[k]), k
+
+
+def test_a_load_after_a_refused_one_solves_with_its_own_tables():
+    """A load refused for memory leaves nothing that the next one's solve goes by: a grid of 39 Poisson rows is
+    refused by the budget at its staging buffer, then one of 1099 rows, which takes another tridiagonal solve, must
+    give the potential of a context that loaded nothing before, bit for bit."""
+    from paper_2609_31258_amd import mucite
+    _say("load after a refused load")
+    big, tall = synth.uniform_fields(40, 2000, 5e-5), synth.uniform_fields(1100, 8, 5e-5)
+    ion = synth.config_c1(10)[1][0]
+    snap = synth.pack_snapshot(500, tall, seed=3, z_lo=0.2 * tall.grid.L, z_hi=0.8 * tall.grid.L, r_hi=0.5 * tall.grid.R)
+    probe = mucite.Sim(seed=1, pack_capacity=500)
+    probe.load_fields(big)
+    staging = 32 * big.grid.nr * big.grid.nz  # the four raw tables, returned at the end of the load
+    transform = 16 * (1998 + 2048 + 4096)      # the sine transform's tables, which come after them
+    budget = probe.info()["device_bytes"] - transform + staging - 1024
+    probe.close()
+    out = []
+    for refused_first in (True, False):
+        s = mucite.Sim(seed=1, pack_capacity=500, hbm_budget=budget)
+        if refused_first:
+            with pytest.raises(mucite.MucateError) as err:
+                s.load_fields(big)
+            assert err.value.code == mucite.MC_EBUDGET
+        op = synth.Operating(dt=1e-9, z_det=tall.grid.L, r_det=tall.grid.R, sc_on=1)
+        s.setup(tall, [ion], [], op)
+        s.write_packs(snap)
+        s.pic_update()
+        out.append(s.read_sc())
+        s.close()
+    assert np.abs(out[1][0]).max() > 0.0
+    for a, b in zip(*out):
+        assert np.array_equal(a, b)
