@@ -18,6 +18,7 @@
 #include "mc_host.hpp"
 #include "mc_io.hpp"
 #include "mc_kernels.hpp"
+#include "mc_plan.hpp"
 #include "mc_poisson.hpp"
 #include "mc_sort.hpp"
 #include "mc_stretch.hpp"
@@ -1339,7 +1340,7 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     d.rf_cap = op.v_rf != 0.0 && op.f_rf > 0.0 ? 0.05 / op.f_rf : inf;
     d.lv_cap = op.lv_dt_max > 0.0 ? op.lv_dt_max : inf;
     d.t_pic = op.sc_on ? ctx->t_next_pic : inf;
-    d.t_pause = op.sc_on ? ctx->t_next_pic - tol : inf;
+    d.t_pause = op.sc_on ? pause_time(t0, ctx->t_next_pic, tol) : inf;
     d.collapse = 1e-9 * op.dt;
     d.v_rf = op.v_rf;
     d.w2 = 2.0 * kPi * op.f_rf;
