@@ -465,6 +465,7 @@ int32_t mc_deposit_cic_noalloc(const mc_cic_packs *packs, const mc_grid *grid, i
 
 /* ------------------------------------------------------------------------- */
 /* Serving: continuous batching of design queries over shared field tables.   */
+/*                                                                            */
 /*                                                                           */
 /* A server owns one field set (grid, potentials, gas, mask, hit distance and */
 /* gas species shared by all queries) and a device pool of hbm_budget bytes.  */
@@ -472,11 +473,13 @@ int32_t mc_deposit_cic_noalloc(const mc_cic_packs *packs, const mc_grid *grid, i
 /* seed, step count): its packs, space-charge grids, folded field table and   */
 /* tallies stay resident in one pool block from admission to completion.     */
 /* A worker thread admits pending queries in arrival order while their block  */
-/* fits in the pool and fewer than max_resident are resident, advances every  */
-/* resident query by one step per co-step (one launch of the step kernel for  */
-/* all of them; emission likewise; space-charge updates per query), and      */
-/* retires finished queries into host results.  A query's arithmetic does   */
-/* not depend on which others share its launches: its result is the same     */
+/* fits in the pool and fewer than max_resident are resident, advances the    */
+/* resident queries in rounds of up to steps_per_sync steps each (one launch  */
+/* takes every one of them as far as it gets on its own, to its next space-   */
+/* charge update or snapshot, 32 steps at most; emission likewise; updates    */
+/* per query; adaptive queries one step a launch), and retires finished       */
+/* queries into host results.  A query's arithmetic does                      */
+/* not depend on which others share its launches: its result is the same      */
 /* alone and in any mix.  submit/poll/wait/stats are thread-safe.            */
 /* ------------------------------------------------------------------------- */
 typedef struct mc_server_options {
@@ -484,7 +487,7 @@ typedef struct mc_server_options {
     int32_t device;
     int64_t hbm_budget;      /* bytes of the query pool (> 0) */
     int32_t max_resident;    /* queries co-stepped at once, 1..4096 */
-    int32_t steps_per_sync;  /* co-steps enqueued between host synchronisations, >= 1 */
+    int32_t steps_per_sync;  /* steps of each query enqueued between host synchronisations, >= 1 */
     void *stream;            /* hipStream_t, NULL = server-owned */
     mc_alloc_fn alloc;       /* optional allocator for the pool and shared tables */
     mc_free_fn free;
@@ -500,8 +503,8 @@ typedef struct mc_server_options {
  * packs at the query's first step.  exit_capacity: exit records kept (0 = none);
  * sample_capacity: trajectory samples kept (0 = none), taken on the schedule of
  * op.sample_every / op.sample_stride as in a single run.  op.adaptive selects
- * the Eq. 1 step as in mc_step: each co-step then reduces the query's step
- * limits and reads them back (one synchronisation per co-step for all adaptive
+ * the Eq. 1 step as in mc_step: each launch then reduces the query's step
+ * limits and reads them back (one synchronisation per launch for all adaptive
  * queries); a query whose step collapses fails with MC_ENUMERIC alone. */
 typedef struct mc_query {
     mc_ion ion;
@@ -538,7 +541,8 @@ typedef struct mc_query_result {
 typedef struct mc_server_stats {
     int64_t submitted, admitted, completed, failed, resident, pending;
     int64_t pool_bytes, pool_in_use, pool_peak, shared_bytes;
-    int64_t co_steps, pack_steps, max_resident_seen;
+    int64_t co_steps;        /* steps of the query farthest on in each round, summed over the rounds */
+    int64_t pack_steps, max_resident_seen;
     double busy_s, wall_s;
 } mc_server_stats;
 

@@ -49,7 +49,7 @@ struct Query {
     Species sp{};
     Src src{};
     int64_t n_slots = 0, step = 0, emitted_n = 0, emitted_w = 0, partial_len = 0;
-    int64_t left = 0;  // steps it may still take in this round
+    int64_t given = 0, left = 0;  // steps it may take in this round, and those it still may
     // device views into the query's pool block
     PackPtrs<double> p64{};
     PackPtrs<float> p32{};
@@ -682,7 +682,6 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     }
     SCHK(hipEventRecord(S->ring_ev[slot], S->stream));
     S->ring_used[slot] = true;
-    S->st.co_steps++;
     return MC_OK;
 }
 
@@ -811,7 +810,8 @@ static int32_t worker_round(mc_server *S) {
         std::lock_guard<std::mutex> lk(S->mu);
         act = S->resident;
     }
-    for (Query *Q : act) Q->left = std::min<int64_t>(S->opt.steps_per_sync, Q->q.n_steps - Q->step);
+    for (Query *Q : act) Q->given = Q->left = std::min<int64_t>(S->opt.steps_per_sync, Q->q.n_steps - Q->step);
+    int64_t counted = 0;
     for (;;) {
         std::vector<Query *> live;
         for (Query *Q : act)
@@ -819,6 +819,13 @@ static int32_t worker_round(mc_server *S) {
         if (live.empty()) break;
         int32_t rc = co_step<P, Tab>(S, live);
         if (rc) return rc;
+        // counted in steps, however many of them a launch takes: as far as the
+        // query farthest on has come (a step that fails its query counts)
+        int64_t reached = counted;
+        for (const Query *Q : live) reached = std::max(reached, Q->given - Q->left + (Q->fail_code ? 1 : 0));
+        std::lock_guard<std::mutex> lk(S->mu);
+        S->st.co_steps += reached - counted;
+        counted = reached;
     }
     SCHK(hipStreamSynchronize(S->stream));
     for (Query *Q : act) {

@@ -272,3 +272,17 @@ def test_fp32_table_server_equals_the_single_context_run():
     sim.close()
     assert r["state"] == mucite.Q_DONE and t["pack_steps"] > 0
     _same(r["tallies"], t, exact_fp=False)
+
+
+@pytest.mark.parametrize("steps_per_sync", [7, 32])
+def test_co_steps_count_steps(steps_per_sync):
+    """The server counts its co-steps in steps of the query farthest on, however many of them a launch takes."""
+    from paper_2609_31258_amd import mucite
+    f = _fields()
+    _say("serving co-step count, steps per sync", steps_per_sync)
+    with mucite.Server(f, hbm_budget=1 << 30, precision=1, max_resident=4, steps_per_sync=steps_per_sync) as s:
+        for steps, sc in ((100, 0), (45, 1)):
+            before = s.stats()["co_steps"]
+            ion, src, op, _, seed = _query(f, sc=sc)
+            assert s.wait(s.submit(ion, src, op, n_steps=steps, seed=seed))["state"] == mucite.Q_DONE
+            assert s.stats()["co_steps"] - before == steps
