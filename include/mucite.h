@@ -75,7 +75,9 @@ typedef struct mc_options {
     int32_t device;          /* HIP device ordinal */
     uint64_t seed;           /* key of the counter-based random streams */
     int64_t pack_capacity;   /* maximum number of pack slots (> 0) */
-    int64_t exit_capacity;   /* exit-record buffer size; 0 = pack_capacity */
+    int64_t exit_capacity;   /* exit-record buffer size; 0 = pack_capacity.  Of more exits than that, those of
+                              * earlier launches are kept; of one launch (up to 32 steps between two space-
+                              * charge updates, sorts or snapshots), any */
     int64_t hbm_budget;      /* device bytes this ctx may allocate; 0 = unlimited */
     void *stream;            /* hipStream_t to enqueue on; NULL = ctx-owned stream */
     mc_alloc_fn alloc;       /* optional device allocator (both or neither) */
@@ -465,21 +467,20 @@ int32_t mc_deposit_cic_noalloc(const mc_cic_packs *packs, const mc_grid *grid, i
 
 /* ------------------------------------------------------------------------- */
 /* Serving: continuous batching of design queries over shared field tables.   */
-/*                                                                            */
 /*                                                                           */
-/* A server owns one field set (grid, potentials, gas, mask, hit distance and */
-/* gas species shared by all queries) and a device pool of hbm_budget bytes.  */
-/* Each query is a complete simulation (its own ion, source, operating point, */
-/* seed, step count): its packs, space-charge grids, folded field table and   */
-/* tallies stay resident in one pool block from admission to completion.     */
-/* A worker thread admits pending queries in arrival order while their block  */
-/* fits in the pool and fewer than max_resident are resident, advances the    */
-/* resident queries in rounds of up to steps_per_sync steps each (one launch  */
-/* takes every one of them as far as it gets on its own, to its next space-   */
-/* charge update or snapshot, 32 steps at most; emission likewise; updates    */
-/* per query; adaptive queries one step a launch), and retires finished       */
-/* queries into host results.  A query's arithmetic does                      */
-/* not depend on which others share its launches: its result is the same      */
+/* A server owns one field set (grid, potentials, gas, mask, hit distance    */
+/* and gas species shared by all queries) and a device pool of hbm_budget    */
+/* bytes. Each query is a complete simulation (its own ion, source,          */
+/* operating point, seed, step count): its packs, space-charge grids, folded */
+/* field table and tallies stay resident in one pool block from admission to */
+/* completion. A worker thread admits pending queries in arrival order while */
+/* their block fits in the pool and fewer than max_resident are resident,    */
+/* advances the resident queries in rounds of up to steps_per_sync steps     */
+/* each (one launch takes every one of them as far as it gets on its own, to */
+/* its next space-charge update or snapshot, 32 steps at most; emission      */
+/* likewise; updates per query; adaptive queries one step a launch), and     */
+/* retires finished queries into host results.  A query's arithmetic does    */
+/* not depend on which others share its launches: its result is the same     */
 /* alone and in any mix.  submit/poll/wait/stats are thread-safe.            */
 /* ------------------------------------------------------------------------- */
 typedef struct mc_server_options {
@@ -522,8 +523,8 @@ enum { MC_Q_PENDING = 0, MC_Q_RUNNING = 1, MC_Q_DONE = 2, MC_Q_FAILED = 3 };
  * (sizes as for mc_read_tallies with the query's n_exit_bins) or NULL, and
  * the exit-record and sample buffers with their lengths in records (or NULL).
  * Once the query is done, n_exits / n_samples give the records it kept (at
- * most its capacities) and the first min(n, length) of them, in the order the
- * device appended them, are copied into the buffers.  Times are seconds on the
+ * most its capacities) and the first min(n, length) of them, in the order of
+ * their steps, are copied into the buffers.  Times are seconds on the
  * server clock (0 at creation). */
 typedef struct mc_query_result {
     int32_t state, error;

@@ -718,6 +718,9 @@ static int32_t retire_query(mc_server *S, Query &Q, PackPtrs<T> p) {
         SCHK(hipMemcpyAsync(Q.r_samples.data(), Q.samples, nsm * sizeof(mc_sample_rec), hipMemcpyDeviceToHost,
                             S->stream));
     if (nex > 0 || nsm > 0) SCHK(hipStreamSynchronize(S->stream));
+    // (the packs of a launch of several steps append theirs in no order of the steps)
+    std::stable_sort(Q.r_exits.begin(), Q.r_exits.end(),
+                     [](const mc_exit_rec &a, const mc_exit_rec &b) { return a.step < b.step; });
     fold_hot(tal.data() + (Q.tal_len - kHotLen), tal.data());
     mc_tallies &r = Q.r;
     r.emitted_n = Q.emitted_n;

@@ -286,3 +286,15 @@ def test_co_steps_count_steps(steps_per_sync):
             ion, src, op, _, seed = _query(f, sc=sc)
             assert s.wait(s.submit(ion, src, op, n_steps=steps, seed=seed))["state"] == mucite.Q_DONE
             assert s.stats()["co_steps"] - before == steps
+
+
+def test_exit_records_of_a_query_come_in_the_order_of_their_steps():
+    """Also where a launch takes the packs through several steps at once."""
+    from paper_2609_31258_amd import mucite
+    _say("serving exit order")
+    f, ions, srcs, op, _ = synth.config_c1x()
+    with mucite.Server(f, hbm_budget=1 << 30, precision=0, max_resident=2) as s:
+        r = s.wait(s.submit(ions[0], srcs[0], op, n_steps=1500, seed=5, exit_capacity=20_000))
+    step = r["exits"]["step"]
+    assert len(step) > 1000 and len(np.unique(step)) > 50
+    assert np.all(np.diff(step) >= 0)
