@@ -303,8 +303,8 @@ __global__ __launch_bounds__(T * W) void k_pcr(D *bh, int32_t nr, int32_t nz, do
 constexpr int kTriMaxRows = 1024;
 inline int tri_rows_per_lane(int32_t nu) { return nu <= 128 ? 2 : nu <= 256 ? 4 : nu <= 512 ? 8 : 16; }
 
-// inv_i of every mode, [mode][np] with np = 64 R rows (zero beyond nu), and
-// after them lo_i and up_i, [np] each, which no mode changes.
+// inv_i of every mode, [mode][nu], and after them lo_i and up_i, [np] each with
+// np = 64 R rows (zero beyond nu), which no mode changes.
 static __global__ __launch_bounds__(64) void k_tri_table(double *inv, int32_t nr, int32_t nz, double dr, double dz,
                                                          int32_t np) {
     const int32_t m = nz - 2, nu = nr - 1;
@@ -312,7 +312,7 @@ static __global__ __launch_bounds__(64) void k_tri_table(double *inv, int32_t nr
     if (k > m) return;
     const double sk = sin(kPi * (double)k / (2.0 * (double)(nz - 1)));
     const double lam = -(4.0 / (dz * dz)) * sk * sk;
-    double *row = inv + (int64_t)(k - 1) * np, *ends = inv + (int64_t)m * np;
+    double *row = inv + (int64_t)(k - 1) * nu, *ends = inv + (int64_t)m * nu;
     double cprev = 0.0;
     for (int32_t i = 0; i < np; ++i) {
         double lo = 0.0, up = 0.0, v = 0.0;
@@ -327,7 +327,7 @@ static __global__ __launch_bounds__(64) void k_tri_table(double *inv, int32_t nr
             v = 1.0 / (di - lo * cprev);
             cprev = up * v;
         }
-        row[i] = v;
+        if (i < nu) row[i] = v;
         if (k == 1) {
             ends[i] = lo;
             ends[np + i] = up;
@@ -376,10 +376,12 @@ __global__ __launch_bounds__(64 * W) void k_tri(D *bh, const double *inv, int32_
     double v[R], lo[R], up[R];
     {
         // the lane's rows of the tables, read while the modes' rows come in
-        const double *t = inv + (int64_t)(k < m ? k : m - 1) * N + lane * R, *e = inv + (int64_t)m * N + lane * R;
+        // (rows beyond the last are read from what follows, at most 2 N doubles)
+        const double *t = inv + (int64_t)(k < m ? k : m - 1) * nu + lane * R, *e = inv + (int64_t)m * nu + lane * R;
 #pragma unroll
         for (int q = 0; q < R; ++q) {
             v[q] = t[q];
+            if (lane * R + q >= nu) v[q] = 0.0;
             lo[q] = e[q];
             up[q] = e[N + q];
         }
@@ -940,7 +942,7 @@ inline bool takes_thomas(int32_t nu, int32_t m) { return !(nu <= 256 || (nu <= 1
 
 // Doubles of its tables: tri of the scans, tcp and tinv of the sweeps.
 inline size_t tri_len(bool fp32, int32_t nr, int32_t nz) {
-    return takes_scans(fp32, nr - 1) ? (size_t)64 * tri_rows_per_lane(nr - 1) * nz : 0;
+    return takes_scans(fp32, nr - 1) ? (size_t)(nr - 1) * (nz - 2) + 2 * 64 * tri_rows_per_lane(nr - 1) : 0;
 }
 inline size_t thomas_len(bool fp32, int32_t nr, int32_t nz) {
     return !takes_scans(fp32, nr - 1) && takes_thomas(nr - 1, nz - 2) ? (size_t)(nr - 1) * (nz - 2) : 0;

@@ -42,3 +42,23 @@ def test_poisson_kernel_edges(precision, nr, nz):
     ee = max(np.abs(ra - rb).max(), np.abs(za - zb).max()) / max(np.abs(rb).max(), np.abs(zb).max())
     print(f"  phi {ep:.2e} E {ee:.2e}", flush=True)
     assert ep <= (5e-6 if precision else 1e-10) and ee <= (1e-4 if precision else 1e-8)
+
+
+@pytest.mark.parametrize("nr,nz,precision", [(3, 1000, 0), (7, 1000, 0), (33, 129, 0), (258, 300, 0), (1026, 64, 0),
+                                             (3, 1000, 1), (258, 300, 1)])
+def test_device_memory_of_a_context(nr, nz, precision):
+    """A context takes no more than its arrays: per node the three static fields and that of the charges (64 bytes),
+    potential and charge grids (24), mask and hit bytes, one table record each of field and gas, the modes and two
+    coefficients a mode and row for their solve, and the loss map; 128 KiB hold all that does not grow with the grid
+    or is that of a row."""
+    from paper_2609_31258_amd import mucite
+    f = synth.uniform_fields(nr, nz, 5e-5)
+    op = synth.Operating(dt=1e-9, z_det=f.grid.L, r_det=f.grid.R, sc_on=1, sc_every=1)
+    nn, record, real = nr * nz, (32, 8)[precision], (8, 4)[precision]
+    with mucite.Sim(seed=1, pack_capacity=256, precision=precision) as s:
+        s.setup(f, [synth.config_c1(10)[1][0]], [], op)
+        s.step(1)
+        used = s.info()["device_bytes"]
+    transform = 2 * real * (5 * nz + 2 * 4 * nz)  # chirp and FFT tables of at most 8 nz points
+    print("device memory", nr, nz, precision, used, flush=True)
+    assert used <= nn * (64 + 24 + 2 + 2 * record + real + 16 + 8) + transform + 16 * nz + 131_072
