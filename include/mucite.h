@@ -321,7 +321,8 @@ int32_t mc_abi_version(void);
  * templates, sources, operating point).  *out receives the handle.
  * Errors: MC_EINVAL (bad options), MC_EDEVICE. */
 int32_t mc_create(const mc_options *options, mc_ctx **out);
-/* Release all device memory and the ctx-owned stream.  NULL is a no-op. */
+/* Release all device memory and the ctx-owned stream.  (A piece of 4 MiB of
+ * pinned host memory waits for the process's next context.)  NULL is a no-op. */
 void mc_destroy(mc_ctx *ctx);
 /* Message of the last failed call on ctx (ctx-owned; valid until the next call). */
 const char *mc_last_error(const mc_ctx *ctx);

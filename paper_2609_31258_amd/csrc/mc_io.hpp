@@ -8,56 +8,23 @@
 // read of 1e4 packs (211 us, NN us so; its write 202 -> NN us), eight small
 // ones a read of the tallies (192 -> NN us).
 #pragma once
-#include <mutex>
-
 #include "mc_kernels.hpp"
+#include "mc_pool.hpp"
 
 namespace mc {
 
 // Pinned staging memory, lent for the length of one call: pieces of two halves
-// each.  Making one takes 1.5 ms, so those not in use wait for the next call
-// of any context, at most kStageKept of them, and go back to the system with
-// the last context.  Safe from any thread.
+// each.
 constexpr size_t kStageHalf = 2u << 20;
-class StagePool {
-public:
-    char *take() {
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            if (n_idle_ > 0) return idle_[--n_idle_];
-        }
+struct PinnedPiece {
+    static char *make() {
         void *p = nullptr;
         return hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocPortable) == hipSuccess ? static_cast<char *>(p) : nullptr;
     }
-    void put(char *p) {
-        {
-            std::lock_guard<std::mutex> lock(mu_);
-            if (contexts_ > 0 && n_idle_ < kStageKept) {
-                idle_[n_idle_++] = p;
-                return;
-            }
-        }
-        (void)hipHostFree(p);
-    }
-    void join() {
-        std::lock_guard<std::mutex> lock(mu_);
-        ++contexts_;
-    }
-    void leave() {
-        std::lock_guard<std::mutex> lock(mu_);
-        if (--contexts_ > 0) return;
-        while (n_idle_ > 0) (void)hipHostFree(idle_[--n_idle_]);
-    }
-
-private:
-    static constexpr int kStageKept = 4;
-    std::mutex mu_;
-    char *idle_[kStageKept] = {};
-    int n_idle_ = 0;
-    int64_t contexts_ = 0;
+    static void free(char *p) { (void)hipHostFree(p); }
 };
-inline StagePool &stage_pool() {
-    static StagePool pool;
+inline StagePool<PinnedPiece> &stage_pool() {
+    static StagePool<PinnedPiece> pool;
     return pool;
 }
 
