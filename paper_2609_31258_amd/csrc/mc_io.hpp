@@ -19,7 +19,7 @@ constexpr size_t kStageHalf = 2u << 20;
 struct PinnedPiece {
     static char *make() {
         void *p = nullptr;
-        return hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocPortable) == hipSuccess ? static_cast<char *>(p) : nullptr;
+        return hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess ? static_cast<char *>(p) : nullptr;
     }
     static void free(char *p) { (void)hipHostFree(p); }
 };
