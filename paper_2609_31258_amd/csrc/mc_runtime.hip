@@ -86,6 +86,7 @@ struct mc_ctx {
     DtStep *dt_found = nullptr;  // the step found (k_dt_find)
     double c_next = 0.0;         // RF coefficient at t, as the device found it
     bool c_next_valid = false;
+    StepPace pace;
     double t = 0.0, t_next_pic = 0.0, last_dt = 0.0;
     // trajectory samples
     mc_sample_rec *samples = nullptr;
@@ -1289,8 +1290,8 @@ static bool sources_idle(const mc_ctx *ctx) {
 
 // Adaptive steps with the step length kept on the device: up to max_steps
 // steps, as many as run before the next space-charge update falls due, then
-// one read of the record.  How many that will be is guessed from the last
-// step's length; steps enqueued beyond it are not taken on the device.
+// one read of the record.  How many that will be is guessed (StepPace); steps
+// enqueued beyond it are not taken on the device.
 // *done receives the steps taken.
 static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     *done = 0;
@@ -1320,12 +1321,7 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
             const double period = op.sc_every * op.dt;
             while (ctx->t_next_pic <= t0 + tol) ctx->t_next_pic += period;
         }
-        // the steps before the next update's time: at least those of the
-        // largest length, likely those of the last one's
-        const double room = ctx->t_next_pic - tol - t0;
-        const bool guess = ctx->last_dt > 0.0 && ctx->last_dt < op.dt;
-        const double n = std::ceil(room / (guess ? ctx->last_dt : op.dt)) + (guess ? 1.0 : 0.0);
-        k = std::min<int64_t>(k, (int64_t)std::max(1.0, std::min(n, 1024.0)));
+        k = std::min(k, ctx->pace.steps_for(ctx->t_next_pic - tol - t0, op.dt));
     }
     // the record and the limits the first step starts from
     DtRecord rec{t0, ctx->c_next, 0.0, 0ull, 0};
@@ -1374,6 +1370,7 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     if (rec.halted)
         return fail(ctx, MC_ENUMERIC, "adaptive step collapsed below 1e-9 dt at step " + std::to_string(ctx->step));
     ctx->last_dt = rec.dt;
+    ctx->pace.took(rec.steps, rec.t - t0, rec.dt, rec.t >= d.t_pause);
     return MC_OK;
 }
 

@@ -36,3 +36,43 @@ def test_a_run_of_adaptive_steps_always_takes_one(tmp_path):
         }
     }
     CHECK(pause_time(0.0, 5e-9, 5e-16) == 5e-9 - 5e-16);''')
+
+
+def test_adaptive_steps_enqueued_beyond_an_update_stay_few(tmp_path):
+    """Runs of steps at a limit, updates every ten largest steps: a step more than are taken in each run, and the
+    runs no more than two an update, whatever is left for the step that an update cuts short."""
+    _check(tmp_path, "pace", r'''
+    std::mt19937_64 rng(5);
+    for (int trial = 0; trial < 400; ++trial) {
+        const double dt = 5e-9, period = 10 * dt, tol = 1e-6 * dt;
+        // limits from dt/60 up to dt; every other one with a tiny remainder
+        double limit = dt / (1.0 + (double)(rng() % 59000) / 1000);
+        if (trial % 2) limit = period / (std::floor(period / limit) + std::ldexp(1.0, -4 - (int)(rng() % 12)));
+        StepPace pace;
+        double t = 0.0, next = period;
+        long enqueued = 0, taken = 0, runs = 0;
+        const int updates = 100;
+        for (int u = 0; u < updates; ) {
+            while (next <= t + tol) { next += period; ++u; }
+            const double t0 = t, pause = pause_time(t0, next, tol);
+            const long k = pace.steps_for(next - tol - t0, dt);
+            CHECK(k >= 1 && k <= 1024);
+            long j = 0;
+            double d = 0.0;
+            for (; j < k && t < pause; ++j) {
+                d = std::min(std::min(dt, limit * (0.98 + (double)(rng() % 400) / 10000)), next - t);
+                t += d;
+            }
+            pace.took(j, t - t0, d, t >= pause);
+            enqueued += k;
+            taken += j;
+            ++runs;
+        }
+        CHECK(taken <= enqueued);
+        CHECK(runs <= 2 * updates + 10);
+        CHECK(enqueued <= taken + taken / 20 + 2 * runs);
+    }
+    StepPace fresh;
+    CHECK(fresh.steps_for(5e-9, 5e-9) == 1 && fresh.steps_for(51e-9, 5e-9) == 11 && fresh.steps_for(-1e-12, 5e-9) == 1);
+    fresh.took(1, 1e-15, 1e-15, true);  // nothing but a step cut short
+    CHECK(fresh.steps_for(50e-9, 5e-9) == 10);''')
