@@ -60,7 +60,7 @@ struct mc_ctx {
     bool has_fields = false, has_op = false;
     int32_t nr = 0, nz = 0;
     double dr = 0, dz = 0, inv_dr = 0, inv_dz = 0, R = 0;
-    double gas_n_max = 0, gas_t_max = 0;  // largest number density and temperature of the gas table
+    GasRows gas;
 
     double2 *e_dc = nullptr, *e_off = nullptr, *e_rf = nullptr, *e_sc = nullptr;
     StepTables *tables = nullptr;  // the FP64 step's logarithm and turn tables
@@ -499,8 +499,9 @@ constexpr double kThinGas = 16.0;
 static double densest_step(const mc_ctx *ctx) {
     double ccs = 0.0;
     for (const mc_ion &i : ctx->ions) ccs = std::max(ccs, i.ccs_m2);
-    const double abar = std::sqrt(8.0 * kB * ctx->gas_t_max / (kPi * ctx->op.gas_mass_da * kDa));
-    return ctx->op.collisions_on ? ctx->gas_n_max * ccs * abar * ctx->op.dt : 0.0;
+    const double abar = std::sqrt(8.0 * kB * ctx->gas.t_max / (kPi * ctx->op.gas_mass_da * kDa));
+    const double n = *std::max_element(ctx->gas.densest.begin(), ctx->gas.densest.end()) / kB;
+    return ctx->op.collisions_on ? n * ccs * abar * ctx->op.dt : 0.0;
 }
 
 // Lanes per pack of the stretch kernel for a launch of `steps` steps over n
@@ -1106,7 +1107,11 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     for (int k = 0; k < 4; ++k) {
         if (gas[k]) HIPCHK(hipMemcpyAsync(tmp + k * nn, gas[k], nn * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
         else HIPCHK(hipMemsetAsync(tmp + k * nn, 0, nn * sizeof(double), ctx->stream));
-        ctx->gsc[k] = scale_of(absmax(gas[k], nn));
+    }
+    ctx->gas.scan(t->gas_p, t->gas_t, g->nr, g->nz);
+    if (ctx->bf16()) {  // (pressure and temperature are not negative)
+        const double most[4] = {absmax(gas[0], nn), absmax(gas[1], nn), ctx->gas.p_max, ctx->gas.t_max};
+        for (int k = 0; k < 4; ++k) ctx->gsc[k] = scale_of(most[k]);
     }
     if (!ctx->fp32())
         k_gas<double4><<<grid_for(nn), kBlock, 0, ctx->stream>>>(static_cast<double4 *>(ctx->gtab), tmp, tmp + nn,
@@ -1120,11 +1125,6 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
                                                                  tmp + 2 * nn, tmp + 3 * nn, nn, 1, 1, 1, 1);
     LAUNCHCHK();
     if (!ctx->bf16()) std::fill(ctx->gsc, ctx->gsc + 4, 1.0f);
-    ctx->gas_n_max = ctx->gas_t_max = 0.0;
-    for (int64_t k = 0; k < nn; ++k) {
-        if (t->gas_t[k] > 0.0) ctx->gas_n_max = std::max(ctx->gas_n_max, t->gas_p[k] / (kB * t->gas_t[k]));
-        ctx->gas_t_max = std::max(ctx->gas_t_max, t->gas_t[k]);
-    }
     if (t->mask) HIPCHK(hipMemcpyAsync(ctx->mask, t->mask, nn, hipMemcpyHostToDevice, ctx->stream));
     else HIPCHK(hipMemsetAsync(ctx->mask, 0, nn, ctx->stream));
     k_sine_table<<<grid_for(2 * (g->nz - 1)), kBlock, 0, ctx->stream>>>(ctx->sine, g->nz);

@@ -76,3 +76,29 @@ def test_adaptive_steps_enqueued_beyond_an_update_stay_few(tmp_path):
     CHECK(fresh.steps_for(5e-9, 5e-9) == 1 && fresh.steps_for(51e-9, 5e-9) == 11 && fresh.steps_for(-1e-12, 5e-9) == 1);
     fresh.took(1, 1e-15, 1e-15, true);  // nothing but a step cut short
     CHECK(fresh.steps_for(50e-9, 5e-9) == 10);''')
+
+
+def test_densest_gas_of_each_row(tmp_path):
+    """Largest p/T of a row over its nodes with gas, from division; rows of vacuum and of zero temperature."""
+    _check(tmp_path, "gas", r'''
+    std::mt19937_64 rng(9);
+    std::uniform_real_distribution<double> u(0.0, 1.0);
+    const int nr = 37, nz = 50;
+    std::vector<double> p(nr * nz), t(nr * nz);
+    for (int k = 0; k < nr * nz; ++k) {
+        p[k] = k / nr == 3 ? 0.0 : std::exp(12 * u(rng));
+        t[k] = k / nr == 5 || u(rng) < 0.1 ? 0.0 : 20 + 400 * u(rng);
+    }
+    GasRows g;
+    g.scan(p.data(), t.data(), nr, nz);
+    double t_max = 0;
+    for (int j = 0; j < nz; ++j) {
+        double most = 0;
+        for (int k = j * nr; k < (j + 1) * nr; ++k) {
+            if (t[k] > 0) most = std::max(most, p[k] / t[k]);
+            t_max = std::max(t_max, t[k]);
+        }
+        CHECK(std::fabs(g.densest[j] - most) <= 1e-14 * most);
+    }
+    CHECK(g.t_max == t_max && g.p_max == *std::max_element(p.begin(), p.end()));
+    CHECK( g.densest[3] == 0.0 && g.densest[5] == 0.0);''')
