@@ -61,6 +61,8 @@ struct mc_ctx {
     int32_t nr = 0, nz = 0;
     double dr = 0, dz = 0, inv_dr = 0, inv_dz = 0, R = 0;
     GasRows gas;
+    double most_cand = 0.0;  // densest_explicit of the ions
+    LangevinShare lv_share;
 
     double2 *e_dc = nullptr, *e_off = nullptr, *e_rf = nullptr, *e_sc = nullptr;
     StepTables *tables = nullptr;  // the FP64 step's logarithm and turn tables
@@ -491,24 +493,22 @@ static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, do
     return MC_OK;
 }
 
-// Candidates per step below which gas counts as thin (lanes_for).
-constexpr double kThinGas = 16.0;
-
-// Largest candidate count per step that the gas, the ions and the step allow
-// a pack moving slowly in the gas.
-static double densest_step(const mc_ctx *ctx) {
-    double ccs = 0.0;
-    for (const mc_ion &i : ctx->ions) ccs = std::max(ccs, i.ccs_m2);
-    const double abar = std::sqrt(8.0 * kB * ctx->gas.t_max / (kPi * ctx->op.gas_mass_da * kDa));
-    const double n = *std::max_element(ctx->gas.densest.begin(), ctx->gas.densest.end()) / kB;
-    return ctx->op.collisions_on ? n * ccs * abar * ctx->op.dt : 0.0;
-}
-
 // Lanes per pack of the stretch kernel for a launch of `steps` steps over n
 // slots, or 0 for k_step (with one lane, a single step is k_step's).
 static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
-    const int g = lanes_for(ctx->fp32(), ctx->op.langevin_on, densest_step(ctx) < kThinGas, n);
+    const bool thin = ctx->most_cand < kThinGas;
+    const bool lang = ctx->op.langevin_on &&
+                      (thin || mostly_langevin(ctx->lv_share.at(ctx->step), ctx->op.sort_every > 0));
+    const int g = lanes_for(ctx->fp32(), lang, thin || lang, n);
     return g == 1 && steps < 2 ? 0 : g;
+}
+
+// What a pack on the explicit branch may meet, after a change of the ions or
+// the operating point.
+static void find_most_cand(mc_ctx *ctx) {
+    double ccs = 0.0;
+    for (const mc_ion &i : ctx->ions) ccs = std::max(ccs, i.ccs_m2);
+    ctx->most_cand = densest_explicit(ctx->gas, ctx->dz, ctx->op, ccs, ctx->op.gas_mass_da);
 }
 
 template <class P, class Tab>
@@ -1185,7 +1185,10 @@ int32_t mc_define_ion(mc_ctx *ctx, const mc_ion *ion, int32_t *ion_id) {
     ctx->ions.push_back(*ion);
     ctx->sp_host.push_back(make_species(ion));
     ctx->charge_host.push_back(ion->charge_z);
-    if (ctx->has_op) ctx_alpha(ctx, ctx->ions.size() - 1);
+    if (ctx->has_op) {
+        ctx_alpha(ctx, ctx->ions.size() - 1);
+        find_most_cand(ctx);
+    }
     if (ion_id) *ion_id = (int32_t)ctx->ions.size() - 1;
     return upload_species(ctx);
 }
@@ -1206,6 +1209,8 @@ int32_t mc_set_operating(mc_ctx *ctx, const mc_operating *op) {
     ctx->c_next_valid = false;  // RF and step settings may have changed
     ctx->has_op = true;
     for (size_t k = 0; k < ctx->ions.size(); ++k) ctx_alpha(ctx, k);
+    find_most_cand(ctx);
+    ctx->lv_share.forget(false);
     int32_t rc = upload_species(ctx);
     if (rc) return rc;
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
@@ -1614,6 +1619,7 @@ int32_t mc_read_tallies(mc_ctx *ctx, mc_tallies *out) {
     out->exit_dropped = (int64_t)cnt[TC_EXDROP];
     out->n_langevin = (int64_t)cnt[TC_LANG];
     out->n_exchange = (int64_t)cnt[TC_EXCH];
+    ctx->lv_share.read(ctx->step, out->n_langevin, out->pack_steps);
     out->sum_w_ke_active = sums[0];
     out->sum_w_eint_active = sums[1];
     out->sum_w_dissoc_terminal = sums[2];
@@ -1843,6 +1849,7 @@ int32_t mc_load_state(mc_ctx *ctx, const char *path) {
     }
     ctx->n_slots = h.n_slots;
     ctx->step = h.step;
+    ctx->lv_share.forget(true);
     ctx->emitted_n = h.emitted_n;
     ctx->emitted_w = h.emitted_w;
     ctx->t = h.t;
@@ -1912,6 +1919,7 @@ int32_t mc_read_timing(mc_ctx *ctx, mc_timing *out) {
         fold_hot(hot.data(), cnt.data());
     }
     out->pack_steps = (int64_t)cnt[TC_PACKSTEPS];
+    ctx->lv_share.read(ctx->step, (int64_t)cnt[TC_LANG], out->pack_steps);
     return MC_OK;
 }
 

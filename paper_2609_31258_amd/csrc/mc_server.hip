@@ -24,6 +24,7 @@
 #include "mc_host.hpp"
 #include "mc_kernels.hpp"
 #include "mc_poisson.hpp"
+#include "mc_plan.hpp"
 #include "mc_pool.hpp"
 #include "mc_stretch.hpp"
 
@@ -608,7 +609,7 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
                                    Q->n_slots + (Q->src.in.kind == 1 ? Q->src.in.packs_per_step : 0));
         langevin = langevin && step_cost(*Q) == 0.0;
     }
-    const int lanes = lanes_for(S->fp32(), langevin, false, total);
+    const int lanes = lanes_for(S->fp32(), langevin, langevin, total);
     for (Query *Qp : act) {
         Query &Q = *Qp;
         if (Q.fail_code) continue;

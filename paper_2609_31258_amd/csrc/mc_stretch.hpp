@@ -29,8 +29,7 @@
 //
 // Every value is computed by the expressions of k_step (mc_kernels.hpp), in
 // the same order, so the two kernels agree bit for bit; which of them a
-// population takes is a matter of speed alone (stretch_lanes in
-// mc_runtime.hip).
+// population takes is a matter of speed alone (lanes_for in mc_plan.hpp).
 #pragma once
 #include "mc_kernels.hpp"
 
@@ -650,31 +649,6 @@ __global__ __launch_bounds__(256) void k_emit_stretch_multi(const EmitStretchArg
                                                             const int32_t *prefix, int32_t nq) {
     const int q = block_query(prefix, nq);
     emit_in_stretch(descs[q].a, descs[q].st, (int64_t)(blockIdx.x - prefix[q]) * blockDim.x + threadIdx.x);
-}
-
-// Lanes per pack for a launch of several steps over n slots, or 0 where the
-// step kernels, one step a launch, are the faster ones.
-//
-// Lanes: the most, up to 16, that leave one wavefront per SIMD (65536 lanes);
-// the FP32 form's candidates cost less of what the lanes share out than of
-// what each repeats, and two wavefronts per SIMD still gain (FP64 form at
-// 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form at 3.2e4 packs: 4 lanes
-// 25 us, 2 lanes 27 us).  On the Langevin branch there is nothing to share.
-//
-// One lane per pack: wherever the collision loop does not dominate -- the
-// Langevin branch, or gas so thin that a step draws few candidates -- and up
-// to the populations where the step kernel's larger occupancy (three
-// wavefronts per SIMD in the FP64 form, five in the FP32 form) outweighs the
-// end of its launches: FP64 3e5 packs 380 against 380 us and 6e5 packs 716
-// against 669, FP32 6e5 packs 301 against 305 us and 1e6 479 against 468.
-constexpr int64_t kStretchLanes = 65536;
-constexpr int64_t kStretchPacks64 = 300000, kStretchPacks32 = 700000;
-inline int lanes_for(bool fp32, bool langevin, bool thin, int64_t n) {
-    if (n <= 0) return 0;
-    const int64_t lanes = fp32 && !langevin ? 2 * kStretchLanes : kStretchLanes;
-    int g = 16;
-    while (g > 1 && n * g > lanes) g >>= 1;
-    return g > 1 || langevin || thin || n <= (fp32 ? kStretchPacks32 : kStretchPacks64) ? g : 0;
 }
 
 }  // namespace mc

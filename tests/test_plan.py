@@ -102,3 +102,76 @@ def test_densest_gas_of_each_row(tmp_path):
     }
     CHECK(g.t_max == t_max && g.p_max == *std::max_element(p.begin(), p.end()));
     CHECK( g.densest[3] == 0.0 && g.densest[5] == 0.0);''')
+
+
+def test_which_populations_take_the_stretch_kernel(tmp_path):
+    """Large populations take it only where no pack, or next to none, runs the collision loop in dense gas: not for
+    the Langevin branch being on, with a window or a switch that leaves dense gas to the explicit branch."""
+    _check(tmp_path, "lanes", r'''
+    // 100 rows 50 um apart, 1e5 Pa in the first 40, 100 Pa from there on; about 49 candidates a step in the dense gas
+    const int nr = 4, nz = 100;
+    const double dz = 5e-5;
+    std::vector<double> p(nr * nz), t(nr * nz, 300.0);
+    for (int k = 0; k < nr * nz; ++k) p[k] = k / nr < 40 ? 1e5 : 100.0;
+    GasRows g;
+    g.scan(p.data(), t.data(), nr, nz);
+    mc_operating op{};
+    op.dt = 0.5e-9;
+    op.collisions_on = 1;
+    op.lv_switch = 0.05;
+    const double ccs = 9.28e-18;
+    const auto most = [&] { return densest_explicit(g, dz, op, ccs, 28.0134); };
+    const double dense = most();
+    CHECK(dense > 40.0 && dense < 70.0);
+    op.langevin_on = 1;                                   // no window: explicit only below the switch
+    CHECK(most() == 0.05);
+    op.lv_switch = 20.0;
+    CHECK(most() == 20.0);
+    op.lv_switch = 1e9;
+    CHECK(most() == dense);
+    op.lv_switch = 0.05;
+    op.lv_z_hi = 1e-3;                                    // dense gas beyond the window
+    CHECK(most() == dense);
+    op.lv_z_hi = 39 * dz + 1e-9;                          // rows of dense gas share cells with the end of the window
+    CHECK(most() == dense);
+    op.lv_z_hi = 42 * dz;                                 // the window holds the dense gas
+    CHECK(std::fabs(most() - dense * 1e-3) < 1e-12);
+    op.lv_z_lo = 10 * dz;                                 // dense gas before the window
+    CHECK(most() == dense);
+    op.lv_z_lo = 0.0, op.lv_z_hi = 1.0;                   // over the whole grid
+    CHECK(most() == 0.05);
+    op.collisions_on = 0;
+    CHECK(most() == 0.0);
+    CHECK(densest_explicit(GasRows{}, dz, op, ccs, 28.0134) == 0.0);
+
+    for (int fp32 = 0; fp32 < 2; ++fp32) {
+        const int64_t edge = fp32 ? kStretchPacks32 : kStretchPacks64;
+        CHECK(lanes_for(fp32, false, false, 0) == 0 && lanes_for(fp32, true, true, 0) == 0);
+        CHECK(lanes_for(fp32, false, false, edge) == 1 && lanes_for(fp32, false, false, edge + 1) == 0);
+        CHECK(lanes_for(fp32, false, true, 1 << 28) == 1 && lanes_for(fp32, true, true, 1 << 28) == 1);
+        for (int langevin = 0; langevin < 2; ++langevin) {
+            const int64_t lanes = fp32 && !langevin ? 131072 : 65536;
+            for (int g = 16; g > 1; g /= 2) {
+                CHECK(lanes_for(fp32, langevin, langevin, lanes / g) == g);
+                CHECK(lanes_for(fp32, langevin, langevin, lanes / g + 1) == g / 2);
+            }
+        }
+    }
+
+    LangevinShare s;
+    CHECK(!mostly_langevin(s.at(0), true));
+    s.read(10, 995, 1000);
+    CHECK(mostly_langevin(s.at(10), false) && mostly_langevin(s.at(1010), false) && !mostly_langevin(s.at(1011), true));
+    s.read(20, 1095, 2000);                               // 100 of the next 1000
+    CHECK(s.at(20) == 0.1 && !mostly_langevin(s.at(20), true));
+    s.read(30, 1095, 2000);                               // no steps since: what is known stays
+    CHECK(s.at(1020) == 0.1 && s.at(1021) == -1.0);
+    s.forget(false);
+    CHECK(s.at(20) == -1.0);
+    s.read(40, 2095, 3000);
+    CHECK(s.at(40) == 1.0);
+    s.forget(true);                                       // a state from elsewhere: its counters say nothing
+    s.read(5, 7000, 7000);
+    CHECK(s.at(5) == -1.0);
+    s.read(15, 7950, 8000);
+    CHECK(s.at(15) == 0.95 && mostly_langevin(s.at(15), true) && !mostly_langevin(s.at(15), false));''')
