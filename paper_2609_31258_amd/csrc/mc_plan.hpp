@@ -157,4 +157,16 @@ inline int lanes_for(bool fp32, bool langevin, bool light, int64_t n) {
     return g > 1 || light || n <= (fp32 ? kStretchPacks32 : kStretchPacks64) ? g : 0;
 }
 
+// Whether no pack of a run meets more than thin gas but on the Langevin branch.
+inline bool takes_only_langevin(const mc_operating &op, double most_cand) {
+    return op.langevin_on && most_cand < kThinGas;
+}
+
+// What a step of a query's packs costs at most, to order the queries of a
+// launch by: the long ones go first, or the launch ends with their wavefronts
+// alone on the chip.
+inline double step_cost(const mc_operating &op, double most_cand, double dt_now) {
+    return op.adaptive ? most_cand * (dt_now / op.dt) : most_cand;
+}
+
 }  // namespace mc

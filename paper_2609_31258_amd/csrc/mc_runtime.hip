@@ -496,10 +496,9 @@ static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, do
 // Lanes per pack of the stretch kernel for a launch of `steps` steps over n
 // slots, or 0 for k_step (with one lane, a single step is k_step's).
 static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
-    const bool thin = ctx->most_cand < kThinGas;
-    const bool lang = ctx->op.langevin_on &&
-                      (thin || mostly_langevin(ctx->lv_share.at(ctx->step), ctx->op.sort_every > 0));
-    const int g = lanes_for(ctx->fp32(), lang, thin || lang, n);
+    const bool lang = takes_only_langevin(ctx->op, ctx->most_cand) ||
+                      (ctx->op.langevin_on && mostly_langevin(ctx->lv_share.at(ctx->step), ctx->op.sort_every > 0));
+    const int g = lanes_for(ctx->fp32(), lang, lang || ctx->most_cand < kThinGas, n);
     return g == 1 && steps < 2 ? 0 : g;
 }
 

@@ -65,6 +65,7 @@ struct Query {
     // update, this step's length, the limit reduction's replicated lines
     double t = 0.0, t_next_pic = 0.0, dt_now = 0.0;
     unsigned long long *dt_rep = nullptr, *dt_out = nullptr;
+    double most_cand = 0.0;  // densest_explicit of its ion
     int32_t fail_code = MC_OK;  // set when the query stops on its own error (its step collapsed)
     TallyPtrs tp{};
     Species *sp_dev = nullptr;
@@ -93,6 +94,7 @@ struct mc_server {
     double *sine = nullptr;
     Bluestein blu;
     PoissonGrid pg;
+    GasRows gas;
     std::vector<int32_t> mask_nodes;  // metal-mask nodes among the Poisson unknowns
     MaskCap cap;                      // their capacitance correction, built at first use
     std::vector<std::pair<void *, size_t>> allocs;
@@ -553,19 +555,12 @@ static void plan_query(mc_server *S, const Query &Q, int64_t most, StretchArgs<P
     }
 }
 
-// What a step of a query's packs costs, to order the queries of a launch by:
-// the long ones go first, or the launch ends with their wavefronts alone on
-// the chip.  (The queries share the gas, so their collision rates go with the
-// cross section and the step; on the Langevin branch there are no candidates.)
-static double step_cost(const Query &Q) {
-    const mc_operating &op = Q.q.op;
-    return op.langevin_on || !op.collisions_on ? 0.0 : Q.q.ion.ccs_m2 * (op.adaptive ? Q.dt_now : op.dt);
-}
-
 template <class P, class Tab, int G>
 static void launch_multi(mc_server *S, unsigned blocks, const StretchArgs<P, Tab> *d, const int32_t *prefix, int n) {
     k_stretch_multi<P, Tab, G><<<blocks, 64, 0, S->stream>>>(d, prefix, n);
 }
+
+static double cost_of(const Query &Q) { return step_cost(Q.q.op, Q.most_cand, Q.dt_now); }
 
 // One co-step of the queries `act`, each of which may take Q.left more steps
 // this round.
@@ -599,15 +594,15 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
         }
     }
     std::stable_sort(act.begin(), act.end(),
-                     [](const Query *a, const Query *b) { return step_cost(*a) > step_cost(*b); });
+                     [](const Query *a, const Query *b) { return cost_of(*a) > cost_of(*b); });
     // the lanes that all queries' packs together leave to each
     int64_t total = 0;
-    bool langevin = true;
+    bool langevin = true;  // (nearly) no pack of any query collides explicitly
     for (const Query *Q : act) {
         if (Q->fail_code) continue;
         total += std::min<int64_t>(Q->q.source.n_total,
                                    Q->n_slots + (Q->src.in.kind == 1 ? Q->src.in.packs_per_step : 0));
-        langevin = langevin && step_cost(*Q) == 0.0;
+        langevin = langevin && takes_only_langevin(Q->q.op, Q->most_cand);
     }
     const int lanes = lanes_for(S->fp32(), langevin, langevin, total);
     for (Query *Qp : act) {
@@ -965,7 +960,11 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
     for (int k = 0; k < 4; ++k) {
         if (gas[k]) SC2(hipMemcpyAsync(tmp + k * nn, gas[k], nn * 8, hipMemcpyHostToDevice, S->stream));
         else SC2(hipMemsetAsync(tmp + k * nn, 0, nn * 8, S->stream));
-        S->gsc[k] = absmax_h(gas[k], nn) > 0 ? (float)absmax_h(gas[k], nn) : 1.0f;
+    }
+    S->gas.scan(t->gas_p, t->gas_t, g->nr, g->nz);
+    if (S->bf16()) {  // (pressure and temperature are not negative)
+        const double most[4] = {absmax_h(gas[0], nn), absmax_h(gas[1], nn), S->gas.p_max, S->gas.t_max};
+        for (int k = 0; k < 4; ++k) S->gsc[k] = most[k] > 0 ? (float)most[k] : 1.0f;
     }
     if (!S->fp32())
         k_gas<double4><<<blocks_for(nn), kBlk, 0, S->stream>>>((double4 *)S->gtab, tmp, tmp + nn, tmp + 2 * nn,
@@ -1093,6 +1092,7 @@ int32_t mc_server_submit(mc_server *S, const mc_query *q, uint64_t *qid) {
     Q->sp = make_species(&Q->q.ion);
     species_alpha(Q->sp, Q->q.ion, S->opt.gas_mass_da);
     Q->src = make_source(Q->q.source, Q->q.ion.charge_z, Q->q.op.dt);
+    Q->most_cand = densest_explicit(S->gas, S->dz, Q->q.op, Q->q.ion.ccs_m2, S->opt.gas_mass_da);
     Q->bytes = query_layout(S, *Q, [](const char *, int64_t, int64_t) {});
     std::lock_guard<std::mutex> lk(S->mu);
     if (S->dead) {

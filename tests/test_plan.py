@@ -175,3 +175,31 @@ def test_which_populations_take_the_stretch_kernel(tmp_path):
     CHECK(s.at(5) == -1.0);
     s.read(15, 7950, 8000);
     CHECK(s.at(15) == 0.95 && mostly_langevin(s.at(15), true) && !mostly_langevin(s.at(15), false));''')
+
+
+def test_queries_are_ordered_by_the_collisions_of_their_packs(tmp_path):
+    """The branch being on does not make a query cheap: where its window leaves dense gas to the explicit branch it
+    costs what an explicit one does."""
+    _check(tmp_path, "cost", r'''
+    const int nr = 3, nz = 60;
+    std::vector<double> p(nr * nz, 1e5), t(nr * nz, 300.0);
+    GasRows g;
+    g.scan(p.data(), t.data(), nr, nz);
+    mc_operating op{};
+    op.dt = 0.5e-9;
+    op.collisions_on = 1;
+    op.lv_switch = 0.05;
+    const auto cost = [&](double ccs, double dt_now = 0.0) {
+        return step_cost(op, densest_explicit(g, 5e-5, op, ccs, 28.0134), dt_now);
+    };
+    const double small = cost(1e-18), large = cost(5e-18);
+    CHECK(small > 0.0 && std::fabs(large - 5 * small) < 1e-9 * large);
+    op.langevin_on = 1;
+    CHECK(cost(5e-18) < small && takes_only_langevin(op, densest_explicit(g, 5e-5, op, 5e-18, 28.0134)));
+    op.lv_z_hi = 1e-3;
+    CHECK(cost(5e-18) == large && !takes_only_langevin(op, densest_explicit(g, 5e-5, op, 5e-18, 28.0134)));
+    op.langevin_on = 0;
+    op.adaptive = 1;
+    CHECK(std::fabs(cost(5e-18, 0.1 * op.dt) - 0.1 * large) < 1e-9 * large);
+    op.collisions_on = 0;
+    CHECK(cost(5e-18, op.dt) == 0.0);''')
