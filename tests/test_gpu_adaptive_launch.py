@@ -67,3 +67,12 @@ def test_steps_of_one_call_equal_calls_of_one_step(n, precision, tables, species
     assert one[0][1] > 0.0 and one[0][2] == 40
     for a, b in zip(one, many):
         assert a.shape == b.shape and a.tobytes() == b.tobytes()
+
+
+def test_large_one_species_steps_of_one_call_equal_calls_of_one_step():
+    """The one-species step kernel of the large FP32 populations' three launches."""
+    _say("adaptive launches: 800001 packs, precision 1, species 1")
+    one, many = _run(800_001, 1, False, 1, 1), _run(800_001, 1, False, 1, 1000)
+    assert one[0][1] > 0.0 and one[0][2] == 40
+    for a, b in zip(one, many):
+        assert a.shape == b.shape and a.tobytes() == b.tobytes()

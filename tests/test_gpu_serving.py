@@ -298,3 +298,27 @@ def test_exit_records_of_a_query_come_in_the_order_of_their_steps():
     step = r["exits"]["step"]
     assert len(step) > 1000 and len(np.unique(step)) > 50
     assert np.all(np.diff(step) >= 0)
+
+
+@pytest.mark.parametrize("precision,n,pps", [(0, 330_001, 20_000), (1, 730_001, 40_000)])
+def test_queries_that_grow_through_every_launch_equal_single_context_runs(precision, n, pps):
+    """A query that emits from some lanes per pack through one lane to the launches of the step kernel, beside a
+    small one: each equals its single-context run, its snapshots bit for bit."""
+    from paper_2609_31258_amd import mucite
+    _say("serving through every launch, precision", precision)
+    f = _fields()
+    qs = [_query(f, m=5000.0, z=5, n=n, pps=pps, steps=22, seed=21), _query(f, m=700.0, n=3000, pps=300, steps=20, seed=22)]
+    for q in qs:
+        q[2].sc_every, q[2].sample_every, q[2].sample_stride = 3, 7, 997
+    with mucite.Server(f, hbm_budget=2 << 30, precision=precision, max_resident=4, steps_per_sync=32) as s:
+        ids = [s.submit(*q[:3], n_steps=q[3], seed=q[4], sample_capacity=5000) for q in qs]
+        rs = [s.wait(i) for i in ids]
+    for (ion, src, op, steps, seed), r in zip(qs, rs):
+        assert r["state"] == mucite.Q_DONE
+        with mucite.Sim(seed=seed, pack_capacity=src.n_total, precision=precision, sample_capacity=5000) as sim:
+            sim.setup(f, [ion], [src], op)
+            sim.step(steps)
+            _same(r["tallies"], sim.read_tallies(), exact_fp=False)
+            a, b = np.sort(r["samples"], order=["step", "id"]), sim.read_samples()
+        assert r["tallies"]["emitted_n"] == min(src.n_total, steps * src.packs_per_step)
+        assert len(b) > 0 and np.array_equal(a, b)
