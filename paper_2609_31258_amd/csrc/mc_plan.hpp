@@ -157,6 +157,19 @@ inline int lanes_for(bool fp32, bool langevin, bool light, int64_t n) {
     return g > 1 || light || n <= (fp32 ? kStretchPacks32 : kStretchPacks64) ? g : 0;
 }
 
+// Whether a launch of a single step, too, is better off with several lanes per
+// pack.  They must have candidates to share: with none, their loads and draws
+// make the step slower than the step kernel's.  Us a step, step kernel against
+// lanes, at 0 / 0.05 / 1 / 4 / 15 candidates: FP32 form 4000 packs 4.8 / 6.7 / 9.9 /
+// 15 / 30 against 6.9 / 8.1 / 9.4 / 11 / 18, 3e4 packs 5.0 / 7.4 / 11 / 17 / 33
+// against 6.8 / 9.5 / 11 / 15 / 25, 6e4 (two lanes) 5.3 / 7.8 / 11 / 17 / 32 against
+// 5.4 / 9.9 / 13 / 18 / 31; FP64 4000 packs 7.7 / 11 / 16 / 25 / 50 against 9.4 / 12 /
+// 13 / 16 / 26, 3e4 packs 9.3 / 12 / 19 / 29 / 57 against 9.4 / 13 / 17 / 24 / 44.
+// (Of two steps or more all of these are faster in one launch.)
+inline bool lanes_pay_in_one_step(bool fp32, int lanes, double candidates) {
+    return lanes > 1 && candidates >= (!fp32 ? 1.0 : lanes > 2 ? 4.0 : 10.0);
+}
+
 // Whether no pack of a run meets more than thin gas but on the Langevin branch.
 inline bool takes_only_langevin(const mc_operating &op, double most_cand) {
     return op.langevin_on && most_cand < kThinGas;

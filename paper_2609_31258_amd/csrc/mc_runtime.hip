@@ -494,12 +494,16 @@ static int32_t launch_step(mc_ctx *ctx, PackPtrs<typename P::T> p, double t0, do
 }
 
 // Lanes per pack of the stretch kernel for a launch of `steps` steps over n
-// slots, or 0 for k_step (with one lane, a single step is k_step's).
+// slots, or 0 for k_step.
 static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
-    const bool lang = takes_only_langevin(ctx->op, ctx->most_cand) ||
-                      (ctx->op.langevin_on && mostly_langevin(ctx->lv_share.at(ctx->step), ctx->op.sort_every > 0));
+    const mc_operating &op = ctx->op;
+    const double share = op.langevin_on ? ctx->lv_share.at(ctx->step) : 0.0;
+    const bool lang = takes_only_langevin(op, ctx->most_cand) || mostly_langevin(share, op.sort_every > 0);
     const int g = lanes_for(ctx->fp32(), lang, lang || ctx->most_cand < kThinGas, n);
-    return g == 1 && steps < 2 ? 0 : g;
+    if (steps >= 2) return g;
+    // (an adaptive step holds a tenth of a candidate; with a window, only what is known counts)
+    const bool collide = !op.adaptive && !lang && share >= 0.0 && !mostly_langevin(share, true);
+    return collide && lanes_pay_in_one_step(ctx->fp32(), g, ctx->most_cand) ? g : 0;
 }
 
 // What a pack on the explicit branch may meet, after a change of the ions or

@@ -203,3 +203,14 @@ def test_queries_are_ordered_by_the_collisions_of_their_packs(tmp_path):
     CHECK(std::fabs(cost(5e-18, 0.1 * op.dt) - 0.1 * large) < 1e-9 * large);
     op.collisions_on = 0;
     CHECK(cost(5e-18, op.dt) == 0.0);''')
+
+
+def test_single_steps_take_lanes_only_with_candidates_to_share(tmp_path):
+    _check(tmp_path, "single", r'''
+    for (int fp32 = 0; fp32 < 2; ++fp32)
+        for (int lanes = 1; lanes <= 16; lanes *= 2) {
+            CHECK(!lanes_pay_in_one_step(fp32, lanes, 0.0) && !lanes_pay_in_one_step(fp32, lanes, 0.05));
+            CHECK(lanes_pay_in_one_step(fp32, lanes, 50.0) == (lanes > 1));
+        }
+    CHECK(lanes_pay_in_one_step(false, 2, 1.0) && !lanes_pay_in_one_step(true, 16, 1.0));
+    CHECK(lanes_pay_in_one_step(true, 4, 4.0) && !lanes_pay_in_one_step(true, 2, 4.0));''')
