@@ -87,13 +87,6 @@ inline double densest_explicit(const GasRows &gas, double dz, const mc_operating
     return most;
 }
 
-// Fewer candidates a step than these count as thin gas: one lane per pack is
-// then the better one for any population.  1e6 packs, us a step, against one
-// launch of the step kernel per step: FP32 form 41 / 53 / 77 / 106 / 181 at 0.3
-// / 0.9 / 2.7 / 5.4 / 13 candidates, 52 / 61 / 84 / 112 / 184 by the step
-// kernel; FP64 74 / 101 / 157 / 226 / 395 against 136 / 146 / 183 / 244 / 408.
-constexpr double kThinGas = 16.0;
-
 // Share of the pack-steps on the Langevin branch from which a large population
 // that has both kinds is the stretch kernel's: one explicit pack keeps its whole
 // wavefront, so it takes nearly all of them, or the slots sorted by cell.  1e6
@@ -131,30 +124,59 @@ private:
     bool known_ = true;  // a context's counters begin at zero
 };
 
-// Lanes per pack for a launch of several steps over n slots, or 0 where the
-// step kernels, one step a launch, are the faster ones.  light: no pack, or
-// nearly none, runs the collision loop for more than thin gas; langevin: most
-// take the Langevin branch.
-//
-// Lanes: the most, up to 16, that leave one wavefront per SIMD (65536 lanes);
-// the FP32 form's candidates cost less of what the lanes share out than of
-// what each repeats, and two wavefronts per SIMD still gain (FP64 form at
-// 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form at 3.2e4 packs: 4 lanes
-// 25 us, 2 lanes 27 us).  On the Langevin branch there is nothing to share.
-//
-// One lane per pack: for light populations, and up to the sizes where the step
-// kernel's larger occupancy (three wavefronts per SIMD in the FP64 form, five
-// in the FP32 form) outweighs the end of its launches: FP64 3e5 packs 380
-// against 380 us and 6e5 packs 716 against 669, FP32 6e5 packs 301 against 305
-// us and 1e6 479 against 468.
+// Lanes per pack for a launch over n slots: the most, up to 16, that leave one
+// wavefront per SIMD (65536 lanes); the FP32 form's candidates cost less of what
+// the lanes share out than of what each repeats, and two wavefronts per SIMD
+// still gain (FP64 form at 1.2e4 packs: 4 lanes 31 us, 8 lanes 34 us; FP32 form
+// at 3.2e4 packs: 4 lanes 25 us, 2 lanes 27 us).  On the Langevin branch there is
+// nothing to share.
 constexpr int64_t kStretchLanes = 65536;
-constexpr int64_t kStretchPacks64 = 300000, kStretchPacks32 = 700000;
-inline int lanes_for(bool fp32, bool langevin, bool light, int64_t n) {
-    if (n <= 0) return 0;
+inline int lanes_for(bool fp32, bool langevin, int64_t n) {
     const int64_t lanes = fp32 && !langevin ? 2 * kStretchLanes : kStretchLanes;
     int g = 16;
     while (g > 1 && n * g > lanes) g >>= 1;
-    return g > 1 || light || n <= (fp32 ? kStretchPacks32 : kStretchPacks64) ? g : 0;
+    return g;
+}
+
+// Whether a launch of `steps` steps with one lane per pack is the better one for
+// n packs of up to `candidates` a step, against a launch of the step kernel per
+// step.  What it saves -- the ends of the launches and the state's way to memory
+// and back -- it saves per step beyond the first; what it loses, by a lower
+// occupancy (two wavefronts per SIMD against three in the FP64 form, three
+// against five in the FP32 form), goes with packs and candidates, and begins
+// where the packs no longer fit on the chip at once (131072 in the FP64 form).
+// The rows are the candidates measured and a tenth more, the columns 2, 3 to 4, 5
+// to 9 and more steps, and what they hold the largest of 1.4e5, 2e5, 3e5, 5e5,
+// 7e5, 1e6, 2e6 and 4e6 packs that gained (or lost less than a hundredth).  Step
+// kernel against stretch kernel, us a step of ten: FP64 1 candidate 1e6 packs 128
+// / 90, 4 candidates 1e6 181 / 171, 4e6 657 / 644, 10 candidates 7e5 216 / 214, 1e6
+// 295 / 303, 25 candidates 3e5 206 / 204, 5e5 304 / 313, 49 candidates 1.2e5 172 /
+// 152, 1.4e5 224 / 226, 1e6 957 / 1059; FP32 0.05 candidates 4e6 108 / 95, 1
+// candidate 2e6 87 / 84, 4e6 158 / 162, 4 candidates 1e6 81 / 79, 2e6 144 / 148, 10
+// candidates 7e5 99 / 95, 1e6 133 / 134, 49 candidates 5e5 238 / 234, 7e5 312 / 316,
+// 1e6 430 / 445.
+struct OneLaneLimit {
+    double candidates;
+    int64_t packs[4];
+};
+inline bool one_lane_pays(bool fp32, bool langevin, double candidates, int64_t n, int64_t steps) {
+    constexpr int64_t any = INT64_MAX;
+    constexpr OneLaneLimit limits64[] = {{1.1, {any, any, any, any}},
+                                         {4.4, {500'000, 1'000'000, 2'000'000, any}},
+                                         {11.0, {300'000, 500'000, 500'000, 700'000}},
+                                         {27.0, {131'072, 200'000, 300'000, 300'000}},
+                                         {HUGE_VAL, {131'072, 131'072, 131'072, 131'072}}};
+    constexpr OneLaneLimit limits32[] = {{0.1, {1'000'000, any, any, any}},
+                                         {1.1, {700'000, 2'000'000, 2'000'000, 2'000'000}},
+                                         {4.4, {500'000, 1'000'000, 1'000'000, 1'000'000}},
+                                         {11.0, {300'000, 700'000, 700'000, 700'000}},
+                                         {27.0, {300'000, 500'000, 500'000, 700'000}},
+                                         {HUGE_VAL, {300'000, 300'000, 500'000, 500'000}}};
+    if (steps < 2) return false;
+    const int column = steps < 3 ? 0 : steps < 5 ? 1 : steps < 10 ? 2 : 3;
+    const OneLaneLimit *row = fp32 ? limits32 : limits64;
+    while (!langevin && candidates > row->candidates) ++row;  // (on the Langevin branch: as without candidates)
+    return n <= row->packs[column];
 }
 
 // Whether a launch of a single step, too, is better off with several lanes per
@@ -170,9 +192,10 @@ inline bool lanes_pay_in_one_step(bool fp32, int lanes, double candidates) {
     return lanes > 1 && candidates >= (!fp32 ? 1.0 : lanes > 2 ? 4.0 : 10.0);
 }
 
-// Whether no pack of a run meets more than thin gas but on the Langevin branch.
+// Whether no pack of a run meets a candidate to speak of but on the Langevin
+// branch.
 inline bool takes_only_langevin(const mc_operating &op, double most_cand) {
-    return op.langevin_on && most_cand < kThinGas;
+    return op.langevin_on && most_cand <= 0.1;
 }
 
 // What a step of a query's packs costs at most, to order the queries of a
@@ -180,6 +203,17 @@ inline bool takes_only_langevin(const mc_operating &op, double most_cand) {
 // alone on the chip.
 inline double step_cost(const mc_operating &op, double most_cand, double dt_now) {
     return op.adaptive ? most_cand * (dt_now / op.dt) : most_cand;
+}
+
+// Lanes per pack for the queries of a server, over the packs of all of them; 0:
+// the step kernel, one step a launch.  (Queries of unlike ions leave more of
+// every launch's end idle than one population does, so that many steps a launch
+// still pay where one_lane_pays has long said no.)
+constexpr int64_t kQueryPacks64 = 300'000, kQueryPacks32 = 700'000;
+inline int query_lanes(bool fp32, bool langevin, int64_t n) {
+    if (n <= 0) return 0;
+    const int g = lanes_for(fp32, langevin, n);
+    return g > 1 || langevin || n <= (fp32 ? kQueryPacks32 : kQueryPacks64) ? g : 0;
 }
 
 }  // namespace mc

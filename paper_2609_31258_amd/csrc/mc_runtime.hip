@@ -499,7 +499,9 @@ static int stretch_lanes(const mc_ctx *ctx, int64_t n, int64_t steps) {
     const mc_operating &op = ctx->op;
     const double share = op.langevin_on ? ctx->lv_share.at(ctx->step) : 0.0;
     const bool lang = takes_only_langevin(op, ctx->most_cand) || mostly_langevin(share, op.sort_every > 0);
-    const int g = lanes_for(ctx->fp32(), lang, lang || ctx->most_cand < kThinGas, n);
+    if (n <= 0) return 0;
+    const int g = lanes_for(ctx->fp32(), lang, n);
+    if (g == 1) return one_lane_pays(ctx->fp32(), lang, ctx->most_cand, n, steps) ? 1 : 0;
     if (steps >= 2) return g;
     // (an adaptive step holds a tenth of a candidate; with a window, only what is known counts)
     const bool collide = !op.adaptive && !lang && share >= 0.0 && !mostly_langevin(share, true);

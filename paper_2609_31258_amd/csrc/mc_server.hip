@@ -604,7 +604,7 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
                                    Q->n_slots + (Q->src.in.kind == 1 ? Q->src.in.packs_per_step : 0));
         langevin = langevin && takes_only_langevin(Q->q.op, Q->most_cand);
     }
-    const int lanes = lanes_for(S->fp32(), langevin, langevin, total);
+    const int lanes = query_lanes(S->fp32(), langevin, total);
     for (Query *Qp : act) {
         Query &Q = *Qp;
         if (Q.fail_code) continue;

@@ -144,19 +144,18 @@ def test_which_populations_take_the_stretch_kernel(tmp_path):
     CHECK(most() == 0.0);
     CHECK(densest_explicit(GasRows{}, dz, op, ccs, 28.0134) == 0.0);
 
-    for (int fp32 = 0; fp32 < 2; ++fp32) {
-        const int64_t edge = fp32 ? kStretchPacks32 : kStretchPacks64;
-        CHECK(lanes_for(fp32, false, false, 0) == 0 && lanes_for(fp32, true, true, 0) == 0);
-        CHECK(lanes_for(fp32, false, false, edge) == 1 && lanes_for(fp32, false, false, edge + 1) == 0);
-        CHECK(lanes_for(fp32, false, true, 1 << 28) == 1 && lanes_for(fp32, true, true, 1 << 28) == 1);
+    for (int fp32 = 0; fp32 < 2; ++fp32)
         for (int langevin = 0; langevin < 2; ++langevin) {
             const int64_t lanes = fp32 && !langevin ? 131072 : 65536;
             for (int g = 16; g > 1; g /= 2) {
-                CHECK(lanes_for(fp32, langevin, langevin, lanes / g) == g);
-                CHECK(lanes_for(fp32, langevin, langevin, lanes / g + 1) == g / 2);
+                CHECK(lanes_for(fp32, langevin, lanes / g) == g);
+                CHECK(lanes_for(fp32, langevin, lanes / g + 1) == g / 2);
             }
+            CHECK(lanes_for(fp32, langevin, 1) == 16 && lanes_for(fp32, langevin, INT64_C(1) << 40) == 1);
+            CHECK(query_lanes(fp32, langevin, 0) == 0);
+            const int64_t edge = fp32 ? kQueryPacks32 : kQueryPacks64;
+            CHECK(query_lanes(fp32, langevin, edge) == 1 && query_lanes(fp32, langevin, edge + 1) == langevin);
         }
-    }
 
     LangevinShare s;
     CHECK(!mostly_langevin(s.at(0), true));
@@ -214,3 +213,31 @@ def test_single_steps_take_lanes_only_with_candidates_to_share(tmp_path):
         }
     CHECK(lanes_pay_in_one_step(false, 2, 1.0) && !lanes_pay_in_one_step(true, 16, 1.0));
     CHECK(lanes_pay_in_one_step(true, 4, 4.0) && !lanes_pay_in_one_step(true, 2, 4.0));''')
+
+
+def test_one_lane_per_pack_by_candidates_and_steps(tmp_path):
+    """More packs, more candidates or fewer steps never bring the stretch kernel back; a million packs in dense gas
+    are the step kernel's, a million in next to none are not."""
+    _check(tmp_path, "one_lane", r'''
+    const double cand[] = {0.0, 0.05, 0.06, 0.9, 1.0, 1.1, 4.0, 5.0, 10.0, 11.0, 25.0, 26.0, 1e4, HUGE_VAL};
+    const int64_t packs[] = {70'000, 131'072, 131'073, 200'000, 300'001, 500'000, 700'001, 1'000'000, 2'000'001, 1 << 28};
+    const int64_t steps[] = {2, 3, 4, 5, 9, 10, 32};
+    for (int fp32 = 0; fp32 < 2; ++fp32) {
+        for (double c : cand)
+            for (int64_t n : packs) {
+                CHECK(!one_lane_pays(fp32, false, c, n, 1) && !one_lane_pays(fp32, true, c, n, 1));
+                bool before = false;
+                for (int64_t k : steps) {
+                    const bool pays = one_lane_pays(fp32, false, c, n, k);
+                    CHECK(pays || !before);
+                    before = pays;
+                    if (pays)
+                        for (double c2 : cand)
+                            for (int64_t n2 : packs)
+                                if (c2 <= c && n2 <= n) CHECK(one_lane_pays(fp32, false, c2, n2, k));
+                    CHECK(one_lane_pays(fp32, true, c, n, k) == one_lane_pays(fp32, false, 0.0, n, k));
+                }
+            }
+        CHECK(one_lane_pays(fp32, false, 0.05, 1'000'000, 10) && !one_lane_pays(fp32, false, 49.0, 1'000'000, 10));
+        CHECK(!one_lane_pays(fp32, false, 10.0, 1'000'000, 32) && one_lane_pays(fp32, false, 120.0, 100'000, 2));
+    }''')
