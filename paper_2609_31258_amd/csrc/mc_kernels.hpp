@@ -701,19 +701,26 @@ __device__ __forceinline__ void flush_counts(const TallyPtrs &t, const StepCount
 // Waves per SIMD the step kernel is compiled for (its register budget):
 // the FP64 form holds its loop state in register pairs and runs three waves
 // in 143 registers (three measured 3 % faster than two and 2 % faster than
-// four, which spill); the FP32 form with BF16
-// tables fits five.  Neither spills.
+// four, which spill); the FP32 form fits five.  No register is spilled to
+// memory.
 template <class P, class Tab>
 constexpr int step_waves() {
-    return P::kTwo ? (sizeof(Tab) == 8 ? 5 : 4) : 3;
+    return P::kTwo ? 5 : 3;
 }
-// No more than five: the FP32 form's one-species kernel, which fits six
-// without spilling, takes 2.7 % longer with them (1e6 packs at 1e5 Pa: 411 us
-// a step with six, 400 with five, 406 with four, 431 with three).
-constexpr int kStepWavesMax = 5;
+// No more than five in the FP32 form: with BF16 tables the one-species kernel
+// fits six without spilling and takes 2.7 % longer with them (1e6 packs at 1e5
+// Pa: 411 us a step with six, 400 with five, 406 with four, 431 with three).
+// With FP32 tables it fits five at most, and comes out better where the compiler
+// is not told so: 1e6 packs at 1e5 Pa 437 us a step against 448, 1000 packs on
+// the Langevin branch 4.2 against 4.9 (four species, 1e6 packs: 1648 against 1624).
+template <class P, class Tab, bool kOneSpecies>
+constexpr int step_waves_max() {
+    return !P::kTwo || (kOneSpecies && sizeof(Tab) != sizeof(bf16x4)) ? 8 : 5;
+}
 
 template <class P, class Tab, bool kOneSpecies>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), (step_waves_max<P, Tab, kOneSpecies>())))) void
 k_step(StepArgs<P, Tab> a) {
     P::prepare_tables(a.tables);
     StepCount n{0, 0, 0, 0, 0, 0, 0};
@@ -861,7 +868,8 @@ static __global__ __launch_bounds__(kHotRep) void k_dt_begin(unsigned long long 
 // block belongs to one query (descriptors in device memory, whose member a is
 // the query's).
 template <class P, class Tab, class Desc>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), (step_waves_max<P, Tab, false>())))) void
 k_step_multi(const Desc *descs, const int32_t *prefix, int32_t nq) {
     const int q = block_query(prefix, nq);
     const StepArgs<P, Tab> &a = descs[q].a;

@@ -588,7 +588,8 @@ static __global__ __launch_bounds__(64) void k_dt_find(DtArgs d, DtStep *found) 
 }
 
 template <class P, class Tab, bool kOneSpecies>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), kStepWavesMax))) void
+__global__ __launch_bounds__(256)
+__attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), (step_waves_max<P, Tab, kOneSpecies>())))) void
 k_step_found(StepArgs<P, Tab> a, const DtStep *found) {
     if (!found->go) return;
     a.t0 = found->t0;
