@@ -539,9 +539,36 @@ static int32_t step_stretch(mc_ctx *ctx, int lanes, const StretchSteps &st, doub
     return launch_stretch<P32, float4>(ctx, ctx->p32, lanes, st, dt);
 }
 
-// One step of an adaptive run on the device.
+// The step that was found on the device.
 template <class P, class Tab>
-static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d) {
+static int32_t launch_found(mc_ctx *ctx, const StepArgs<P, Tab> &a) {
+    Timer t(ctx, MC_K_STEP);
+    const unsigned nb = (unsigned)((ctx->n_slots + kStepBlock - 1) / kStepBlock);
+    if (ctx->ions.size() == 1) k_step_found<P, Tab, true><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
+    else k_step_found<P, Tab, false><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
+    LAUNCHCHK();
+    return MC_OK;
+}
+
+// One step of a short adaptive run (k_dt_single).
+template <class P, class Tab>
+static int32_t short_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d, const DtRecord &rec) {
+    unsigned long long *const lines = ctx->dt_rep + 3 * kHotLen;
+    StepArgs<P, Tab> a{};
+    if (ctx->n_slots > 0) {
+        a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
+        a.c0 = rec.c;
+        k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, lines, kDtLines, d.in);
+        LAUNCHCHK();
+    }
+    k_dt_single<<<1, 64, 0, ctx->stream>>>(d, rec, lines, ctx->dt_found);
+    LAUNCHCHK();
+    return ctx->n_slots > 0 ? launch_found<P, Tab>(ctx, a) : MC_OK;
+}
+
+// One step of an adaptive run on the device (last: no launch reads its limits).
+template <class P, class Tab>
+static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d, bool last) {
     if (ctx->n_slots == 0) {  // time alone
         k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
         LAUNCHCHK();
@@ -552,15 +579,8 @@ static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtA
         if (ctx->n_slots > kAdaptivePacks32) {
             k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
             LAUNCHCHK();
-            {
-                Timer t(ctx, MC_K_STEP);
-                const unsigned nb = (unsigned)((ctx->n_slots + kStepBlock - 1) / kStepBlock);
-                if (ctx->ions.size() == 1)
-                    k_step_found<P, Tab, true><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
-                else
-                    k_step_found<P, Tab, false><<<nb, kStepBlock, 0, ctx->stream>>>(a, ctx->dt_found);
-            }
-            LAUNCHCHK();
+            const int32_t rc = launch_found<P, Tab>(ctx, a);
+            if (rc || last) return rc;
             k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, d.next, kDtLines, d.out);
             LAUNCHCHK();
             return MC_OK;
@@ -1333,14 +1353,6 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         }
         k = std::min(k, ctx->pace.steps_for(ctx->t_next_pic - tol - t0, op.dt));
     }
-    // the record and the limits the first step starts from
-    DtRecord rec{t0, ctx->c_next, 0.0, 0ull, 0};
-    k_dt_begin<<<3, kHotRep, 0, ctx->stream>>>(ctx->dt_rep, ctx->dt_rec, rec);
-    LAUNCHCHK();
-    if (!ctx->fp32()) rc = seed_limits<P64, double4>(ctx, ctx->p64);
-    else if (ctx->bf16()) rc = seed_limits<P32, bf16x4>(ctx, ctx->p32);
-    else rc = seed_limits<P32, float4>(ctx, ctx->p32);
-    if (rc) return rc;
     DtArgs d{};
     d.dt_max = op.dt;
     d.rf_cap = op.v_rf != 0.0 && op.f_rf > 0.0 ? 0.05 / op.f_rf : inf;
@@ -1352,8 +1364,24 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     d.w2 = 2.0 * kPi * op.f_rf;
     d.phase = op.phase_rf;
     const int64_t step0 = ctx->step;
+    DtRecord rec{t0, ctx->c_next, 0.0, 0ull, 0};
+    const bool brief = k <= kAdaptiveShort;
+    if (!brief) {
+        // the record and the limits the first step starts from
+        k_dt_begin<<<3, kHotRep, 0, ctx->stream>>>(ctx->dt_rep, ctx->dt_rec, rec);
+        LAUNCHCHK();
+        if (!ctx->fp32()) rc = seed_limits<P64, double4>(ctx, ctx->p64);
+        else if (ctx->bf16()) rc = seed_limits<P32, bf16x4>(ctx, ctx->p32);
+        else rc = seed_limits<P32, float4>(ctx, ctx->p32);
+        if (rc) return rc;
+    }
+    const auto one_step = [&](auto *policy, auto *table, const auto &packs, bool last) {
+        using P = std::remove_pointer_t<decltype(policy)>;
+        using Tab = std::remove_pointer_t<decltype(table)>;
+        return brief ? short_adaptive<P, Tab>(ctx, packs, d, rec) : launch_adaptive<P, Tab>(ctx, packs, d, last);
+    };
     for (int64_t j = 0; j < k && !rc; ++j) {
-        d.in = ctx->dt_rec + (j & 1);
+        d.in = brief && j == 0 ? nullptr : ctx->dt_rec + (j & 1);
         d.out = ctx->dt_rec + ((j + 1) & 1);
         d.limits = ctx->dt_rep + (j % 3) * kHotLen;
         d.next = ctx->dt_rep + ((j + 1) % 3) * kHotLen;
@@ -1361,9 +1389,9 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         d.step = ctx->step;
         if (j > 0) rc = sample_if_due(ctx, d.in, d.t_pause);
         if (rc) break;
-        if (!ctx->fp32()) rc = launch_adaptive<P64, double4>(ctx, ctx->p64, d);
-        else if (ctx->bf16()) rc = launch_adaptive<P32, bf16x4>(ctx, ctx->p32, d);
-        else rc = launch_adaptive<P32, float4>(ctx, ctx->p32, d);
+        if (!ctx->fp32()) rc = one_step((P64 *)nullptr, (double4 *)nullptr, ctx->p64, j + 1 == k);
+        else if (ctx->bf16()) rc = one_step((P32 *)nullptr, (bf16x4 *)nullptr, ctx->p32, j + 1 == k);
+        else rc = one_step((P32 *)nullptr, (float4 *)nullptr, ctx->p32, j + 1 == k);
         ctx->step++;  // (the step that sample_if_due and the launches go by)
     }
     ctx->step = step0;

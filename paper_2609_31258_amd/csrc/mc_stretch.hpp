@@ -264,39 +264,49 @@ __device__ __forceinline__ double from_lane(double v, int l) {
                             __builtin_amdgcn_readlane(__double2loint(v), l));
 }
 
-__device__ __forceinline__ DtStep dt_step(const DtArgs &d) {
+// The step from record r whose limits' smallest is mn over the lanes (lang: some
+// pack takes the Langevin branch), with the record after it.  A whole wavefront.
+__device__ __forceinline__ DtStep dt_of(const DtArgs &d, const DtRecord &r, unsigned long long mn, bool lang,
+                                        DtRecord &o) {
 #pragma clang fp contract(off)
+    const int lane = threadIdx.x & 63;
+    o = r;
+    DtStep s{r.t, 0.0, r.c, 0.0, 0.0, false};
+#pragma unroll
+    for (int o2 = 32; o2 > 0; o2 >>= 1) {
+        const unsigned long long other = __shfl_xor(mn, o2, 64);
+        mn = other < mn ? other : mn;
+    }
+    double dt = fmin(d.dt_max, __longlong_as_double((long long)mn));
+    dt = fmin(dt, d.rf_cap);
+    if (lang) dt = fmin(dt, d.lv_cap);
+    dt = fmin(dt, d.t_pic - r.t);
+    if (dt > d.collapse) {
+        s.go = true;
+        s.dt = from_lane(dt, 0);
+        const double t1 = r.t + dt;
+        // both RF coefficients by one cosine: every wavefront pays for it
+        const double c = d.v_rf * cos(d.w2 * (lane & 1 ? t1 : r.t + 0.5 * dt) + d.phase);
+        s.ch = from_lane(c, 0);
+        s.c1 = from_lane(c, 1);
+        o.t = t1;
+        o.c = s.c1;
+        o.dt = dt;
+        ++o.steps;
+    } else {
+        o.halted = (unsigned long long)d.step + 1ull;
+    }
+    return s;
+}
+
+__device__ __forceinline__ DtStep dt_step(const DtArgs &d) {
     const int lane = threadIdx.x & 63;
     const DtRecord r = *d.in;
     DtRecord o = r;
     DtStep s{r.t, 0.0, r.c, 0.0, 0.0, false};
     if (!r.halted && r.t < d.t_pause) {
-        unsigned long long mn = d.limits[(int64_t)lane * kHotStride];
         const bool lang = __ballot(d.limits[(int64_t)lane * kHotStride + 1] != 0ull) != 0ull;
-#pragma unroll
-        for (int o2 = 32; o2 > 0; o2 >>= 1) {
-            const unsigned long long other = __shfl_xor(mn, o2, 64);
-            mn = other < mn ? other : mn;
-        }
-        double dt = fmin(d.dt_max, __longlong_as_double((long long)mn));
-        dt = fmin(dt, d.rf_cap);
-        if (lang) dt = fmin(dt, d.lv_cap);
-        dt = fmin(dt, d.t_pic - r.t);
-        if (dt > d.collapse) {
-            s.go = true;
-            s.dt = from_lane(dt, 0);
-            const double t1 = r.t + dt;
-            // both RF coefficients by one cosine: every wavefront pays for it
-            const double c = d.v_rf * cos(d.w2 * (lane & 1 ? t1 : r.t + 0.5 * dt) + d.phase);
-            s.ch = from_lane(c, 0);
-            s.c1 = from_lane(c, 1);
-            o.t = t1;
-            o.c = s.c1;
-            o.dt = dt;
-            ++o.steps;
-        } else {
-            o.halted = (unsigned long long)d.step + 1ull;
-        }
+        s = dt_of(d, r, d.limits[(int64_t)lane * kHotStride], lang, o);
     }
     if (blockIdx.x == 0) {
         if (lane == 0) *d.out = o;
@@ -581,6 +591,31 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_adaptive(S
 // against 54.8.  (Three launches with a pass of their own for the reduction
 // took 4e5 packs 35 to 38 us, one launch 28.)
 constexpr int64_t kAdaptivePacks32 = 800'000;
+
+// Batches of one step or two take each by the same three launches in the other
+// order: the packs' limits, the step from them and the record (d.in, or null for
+// the first step, whose record r the host holds; the lines are left cleared),
+// the step's kernel.  They are too short for the limits that every launch leaves
+// and the last one leaves to none: 2e5 FP32 packs took 51 us a call of one step
+// that way and 1.4e4 FP64 packs 44, so 46 and 41.
+constexpr int64_t kAdaptiveShort = 2;
+static __global__ __launch_bounds__(64) void k_dt_single(DtArgs d, DtRecord r, unsigned long long *lines,
+                                                         DtStep *found) {
+    const int lane = threadIdx.x & 63;
+    if (d.in) r = *d.in;
+    unsigned long long *line = lines + (int64_t)lane * kHotStride;
+    const unsigned long long mn = line[0];
+    const bool lang = __ballot(line[1] != 0ull) != 0ull;
+    line[0] = kInfBits;
+    line[1] = 0ull;
+    DtRecord o = r;
+    DtStep s{r.t, 0.0, r.c, 0.0, 0.0, false};
+    if (!r.halted && r.t < d.t_pause) s = dt_of(d, r, mn, lang, o);
+    if (lane == 0) {
+        *found = s;
+        *d.out = o;
+    }
+}
 
 static __global__ __launch_bounds__(64) void k_dt_find(DtArgs d, DtStep *found) {
     const DtStep s = dt_step(d);
