@@ -622,10 +622,10 @@ static __global__ __launch_bounds__(64) void k_dt_find(DtArgs d, DtStep *found) 
     if (threadIdx.x == 0) *found = s;
 }
 
+// (Not held to five wavefronts as k_step is: with that the kernel of several
+// species took 1e6 packs 41.8 us, without 38.7.)
 template <class P, class Tab, bool kOneSpecies>
-__global__ __launch_bounds__(256)
-__attribute__((amdgpu_waves_per_eu(step_waves<P, Tab>(), (step_waves_max<P, Tab, kOneSpecies>())))) void
-k_step_found(StepArgs<P, Tab> a, const DtStep *found) {
+__global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_found(StepArgs<P, Tab> a, const DtStep *found) {
     if (!found->go) return;
     a.t0 = found->t0;
     a.dt = found->dt;

@@ -76,3 +76,14 @@ def test_large_one_species_steps_of_one_call_equal_calls_of_one_step():
     assert one[0][1] > 0.0 and one[0][2] == 40
     for a, b in zip(one, many):
         assert a.shape == b.shape and a.tobytes() == b.tobytes()
+
+
+@pytest.mark.parametrize("n,precision,tables,species", [(0, 0, False, 1), (1000, 0, False, 3), (1000, 1, False, 1),
+                                                        (255, 1, True, 3)])
+def test_short_batches_equal_calls_of_one_step(n, precision, tables, species):
+    """Calls of two steps take both by the launches of a single one, calls of three do not."""
+    _say("adaptive short batches:", n, "packs, precision", precision, "species", species)
+    one = _run(n, precision, tables, species, 1)
+    for per_call in (2, 3):
+        for a, b in zip(one, _run(n, precision, tables, species, per_call)):
+            assert a.shape == b.shape and a.tobytes() == b.tobytes()
