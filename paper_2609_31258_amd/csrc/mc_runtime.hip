@@ -85,7 +85,7 @@ struct mc_ctx {
     // adaptive step (Eq. 1)
     unsigned long long *dt_rep = nullptr, *dt_out = nullptr;
     DtRecord *dt_rec = nullptr;  // two records of an adaptive run on the device (k_stretch_adaptive)
-    DtStep *dt_found = nullptr;  // the step found (k_dt_find)
+    DtStep *dt_found = nullptr;  // the step found (k_dt_single)
     double c_next = 0.0;         // RF coefficient at t, as the device found it
     bool c_next_valid = false;
     StepPace pace;
@@ -550,9 +550,9 @@ static int32_t launch_found(mc_ctx *ctx, const StepArgs<P, Tab> &a) {
     return MC_OK;
 }
 
-// One step of a short adaptive run (k_dt_single).
+// One adaptive step in three launches (k_dt_single).
 template <class P, class Tab>
-static int32_t short_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d, const DtRecord &rec) {
+static int32_t three_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d, const DtRecord &rec) {
     unsigned long long *const lines = ctx->dt_rep + 3 * kHotLen;
     StepArgs<P, Tab> a{};
     if (ctx->n_slots > 0) {
@@ -566,26 +566,10 @@ static int32_t short_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtAr
     return ctx->n_slots > 0 ? launch_found<P, Tab>(ctx, a) : MC_OK;
 }
 
-// One step of an adaptive run on the device (last: no launch reads its limits).
+// One adaptive step in one launch.
 template <class P, class Tab>
-static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d, bool last) {
-    if (ctx->n_slots == 0) {  // time alone
-        k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
-        LAUNCHCHK();
-        return MC_OK;
-    }
+static int32_t launch_adaptive(mc_ctx *ctx, PackPtrs<typename P::T> p, const DtArgs &d) {
     const StepArgs<P, Tab> a = step_args<P, Tab>(ctx, p, 0.0, ctx->op.dt);
-    if constexpr (P::kTwo) {
-        if (ctx->n_slots > kAdaptivePacks32) {
-            k_dt_find<<<1, 64, 0, ctx->stream>>>(d, ctx->dt_found);
-            LAUNCHCHK();
-            const int32_t rc = launch_found<P, Tab>(ctx, a);
-            if (rc || last) return rc;
-            k_dt_limits<P, Tab><<<grid_for(ctx->n_slots), kBlock, 0, ctx->stream>>>(a, d.next, kDtLines, d.out);
-            LAUNCHCHK();
-            return MC_OK;
-        }
-    }
     Timer t(ctx, MC_K_STEP);
     if constexpr (P::kTwo) {
         const unsigned nb = grid_for(ctx->n_slots);
@@ -1365,8 +1349,10 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
     d.phase = op.phase_rf;
     const int64_t step0 = ctx->step;
     DtRecord rec{t0, ctx->c_next, 0.0, 0ull, 0};
-    const bool brief = k <= kAdaptiveShort;
-    if (!brief) {
+    // (without packs the time alone is advanced)
+    const bool three = k <= kAdaptiveShort || ctx->n_slots == 0 ||
+                       (ctx->fp32() && ctx->n_slots > kAdaptivePacks32);
+    if (!three) {
         // the record and the limits the first step starts from
         k_dt_begin<<<3, kHotRep, 0, ctx->stream>>>(ctx->dt_rep, ctx->dt_rec, rec);
         LAUNCHCHK();
@@ -1375,13 +1361,13 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         else rc = seed_limits<P32, float4>(ctx, ctx->p32);
         if (rc) return rc;
     }
-    const auto one_step = [&](auto *policy, auto *table, const auto &packs, bool last) {
+    const auto one_step = [&](auto *policy, auto *table, const auto &packs) {
         using P = std::remove_pointer_t<decltype(policy)>;
         using Tab = std::remove_pointer_t<decltype(table)>;
-        return brief ? short_adaptive<P, Tab>(ctx, packs, d, rec) : launch_adaptive<P, Tab>(ctx, packs, d, last);
+        return three ? three_adaptive<P, Tab>(ctx, packs, d, rec) : launch_adaptive<P, Tab>(ctx, packs, d);
     };
     for (int64_t j = 0; j < k && !rc; ++j) {
-        d.in = brief && j == 0 ? nullptr : ctx->dt_rec + (j & 1);
+        d.in = three && j == 0 ? nullptr : ctx->dt_rec + (j & 1);
         d.out = ctx->dt_rec + ((j + 1) & 1);
         d.limits = ctx->dt_rep + (j % 3) * kHotLen;
         d.next = ctx->dt_rep + ((j + 1) % 3) * kHotLen;
@@ -1389,9 +1375,9 @@ static int32_t adaptive_batch(mc_ctx *ctx, int64_t max_steps, int64_t *done) {
         d.step = ctx->step;
         if (j > 0) rc = sample_if_due(ctx, d.in, d.t_pause);
         if (rc) break;
-        if (!ctx->fp32()) rc = one_step((P64 *)nullptr, (double4 *)nullptr, ctx->p64, j + 1 == k);
-        else if (ctx->bf16()) rc = one_step((P32 *)nullptr, (bf16x4 *)nullptr, ctx->p32, j + 1 == k);
-        else rc = one_step((P32 *)nullptr, (float4 *)nullptr, ctx->p32, j + 1 == k);
+        if (!ctx->fp32()) rc = one_step((P64 *)nullptr, (double4 *)nullptr, ctx->p64);
+        else if (ctx->bf16()) rc = one_step((P32 *)nullptr, (bf16x4 *)nullptr, ctx->p32);
+        else rc = one_step((P32 *)nullptr, (float4 *)nullptr, ctx->p32);
         ctx->step++;  // (the step that sample_if_due and the launches go by)
     }
     ctx->step = step0;

@@ -583,22 +583,22 @@ __global__ __launch_bounds__(256, (step_waves<P, Tab>())) void k_step_adaptive(S
     block_limits(a, s, a.c1, d.next, kDtLines);
 }
 
-// Above kAdaptivePacks32 packs the FP32 form takes its adaptive step in three
-// launches: a wavefront finds the step, k_step's code takes it, k_dt_limits
-// follows.  There the look for the step at the start of every block, in each
-// round of blocks, costs more than the launches: 1e6 packs spread over 0.3 mm
-// 51.5 us a step so against 54.0 in one launch, on the Langevin branch 53.7
-// against 54.8.  (Three launches with a pass of their own for the reduction
-// took 4e5 packs 35 to 38 us, one launch 28.)
+// Other adaptive steps take three launches: the packs' limits, the step from
+// them and from the record (d.in, or null for a batch's first step, whose record
+// r the host holds; the lines are left cleared), the step's kernel.
+//
+// Batches of up to kAdaptiveShort steps, which are too short for the limits that
+// every launch leaves and the last one leaves to none: 2e5 FP32 packs took 51 us
+// a call of one step that way and 1.4e4 FP64 packs 44, so 46 and 41.
+//
+// The FP32 form above kAdaptivePacks32 packs, where the look for the step at the
+// start of every block, in each round of blocks, costs more than the launches:
+// 1e6 packs spread over 0.3 mm 51.5 us a step so against 54.0 in one launch, on
+// the Langevin branch 53.7 against 54.8.  (Three launches with a pass of their
+// own for the reduction took 4e5 packs 35 to 38 us, one launch 28.)
+constexpr int64_t kAdaptiveShort = 2;
 constexpr int64_t kAdaptivePacks32 = 800'000;
 
-// Batches of one step or two take each by the same three launches in the other
-// order: the packs' limits, the step from them and the record (d.in, or null for
-// the first step, whose record r the host holds; the lines are left cleared),
-// the step's kernel.  They are too short for the limits that every launch leaves
-// and the last one leaves to none: 2e5 FP32 packs took 51 us a call of one step
-// that way and 1.4e4 FP64 packs 44, so 46 and 41.
-constexpr int64_t kAdaptiveShort = 2;
 static __global__ __launch_bounds__(64) void k_dt_single(DtArgs d, DtRecord r, unsigned long long *lines,
                                                          DtStep *found) {
     const int lane = threadIdx.x & 63;
@@ -615,11 +615,6 @@ static __global__ __launch_bounds__(64) void k_dt_single(DtArgs d, DtRecord r, u
         *found = s;
         *d.out = o;
     }
-}
-
-static __global__ __launch_bounds__(64) void k_dt_find(DtArgs d, DtStep *found) {
-    const DtStep s = dt_step(d);
-    if (threadIdx.x == 0) *found = s;
 }
 
 // (Not held to five wavefronts as k_step is: with that the kernel of several
