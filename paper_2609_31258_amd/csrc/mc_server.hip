@@ -33,7 +33,9 @@ using namespace mc;
 namespace {
 
 constexpr int kBlk = 256;
-constexpr int kRing = 4;
+// Descriptor slots: co-steps of one step each, which take 20 us, wait for one
+// another with four (3 % slower); with many queries a slot is large.
+constexpr int kRing = 8, kRingLarge = 4, kRingLargeQueries = 256;
 constexpr int64_t kAggMax = 1024;
 
 inline unsigned blocks_for(int64_t n) { return (unsigned)((n + kBlk - 1) / kBlk); }
@@ -106,7 +108,7 @@ struct mc_server {
     hipEvent_t ring_ev[kRing] = {};
     bool ring_used[kRing] = {};
     size_t ring_slot = 0;
-    int ring_pos = 0;
+    int ring_pos = 0, ring_len = kRing;
     std::mutex mu;
     std::condition_variable cv, cv_done;
     std::deque<Query *> pending;
@@ -517,20 +519,25 @@ static int32_t adaptive_steps(mc_server *S, std::vector<Query *> &act) {
     return MC_OK;
 }
 
-// A query's part of a co-step: its arguments over the steps from its step on
-// that the co-step takes, as many as `most`, ending before its next
-// space-charge update or snapshot; the packs each of them emits (on a copy of
-// its source).
-template <class P, class Tab>
-static void plan_query(mc_server *S, const Query &Q, int64_t most, StretchArgs<P, Tab> &sd,
-                       EmitStretchArgs<P, Tab> &ed, Src &src) {
+// The steps a query may take in one launch from its step on, ending before its
+// next space-charge update or snapshot.
+static int64_t steps_ahead(const Query &Q) {
     const mc_operating &op = Q.q.op;
-    int64_t k = std::min<int64_t>(most, op.adaptive ? 1 : kStretchMax);
+    int64_t k = std::min<int64_t>(Q.left, op.adaptive ? 1 : kStretchMax);
     const auto until = [&](int32_t every) {
         if (every > 0) k = std::min<int64_t>(k, every - Q.step % every);
     };
     if (op.sc_on) until(op.sc_every);
     if (op.sample_stride > 0 && Q.q.sample_capacity > 0) until(op.sample_every);
+    return k;
+}
+
+// A query's part of a co-step: its arguments over the k steps from its step on;
+// the packs each of them emits (on a copy of its source).
+template <class P, class Tab>
+static void plan_query(mc_server *S, const Query &Q, int64_t k, StretchArgs<P, Tab> &sd,
+                       EmitStretchArgs<P, Tab> &ed, Src &src) {
+    const mc_operating &op = Q.q.op;
     src = Q.src;
     StretchSteps &st = sd.st;
     EmitSteps &em = ed.st;
@@ -572,14 +579,17 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     const int32_t maxres = S->opt.max_resident;
     // ring slot: wait until the GPU has consumed its previous contents
     const int slot = S->ring_pos;
-    S->ring_pos = (S->ring_pos + 1) % kRing;
+    S->ring_pos = (S->ring_pos + 1) % S->ring_len;
     if (S->ring_used[slot]) SCHK(hipEventSynchronize(S->ring_ev[slot]));
     char *h = S->h_ring + slot * S->ring_slot;
     char *d = S->d_ring + slot * S->ring_slot;
     const size_t pre = (size_t)Pool::round_up(2 * (maxres + 1) * sizeof(int32_t));
     int32_t *pe = (int32_t *)h, *ps = pe + (maxres + 1);
-    Emit *ed = (Emit *)(h + pre);
-    Steps *sd = (Steps *)(h + pre + maxres * sizeof(Emit));
+    // the queries' steps, then their emission, in one copy (each copy is 3 us of
+    // a co-step)
+    Steps *sd = (Steps *)(h + pre);
+    const size_t emit_at = pre + act.size() * sizeof(Steps);
+    Emit *ed = (Emit *)(h + emit_at);
     int ne = 0, ns = 0, be = 0, bs = 0;
     int32_t rc0 = adaptive_steps<P, Tab>(S, act);
     if (rc0) return rc0;
@@ -596,22 +606,26 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     std::stable_sort(act.begin(), act.end(),
                      [](const Query *a, const Query *b) { return cost_of(*a) > cost_of(*b); });
     // the lanes that all queries' packs together leave to each
-    int64_t total = 0;
+    int64_t total = 0, longest = 0;
     bool langevin = true;  // (nearly) no pack of any query collides explicitly
+    double candidates = 0.0;
     for (const Query *Q : act) {
         if (Q->fail_code) continue;
         total += std::min<int64_t>(Q->q.source.n_total,
                                    Q->n_slots + (Q->src.in.kind == 1 ? Q->src.in.packs_per_step : 0));
         langevin = langevin && takes_only_langevin(Q->q.op, Q->most_cand);
+        longest = std::max(longest, steps_ahead(*Q));
+        if (!Q->q.op.adaptive && !Q->q.op.langevin_on) candidates = std::max(candidates, Q->most_cand);
     }
-    const int lanes = query_lanes(S->fp32(), langevin, total);
+    int lanes = query_lanes(S->fp32(), langevin, total);
+    if (longest < 2 && !lanes_pay_in_one_step(S->fp32(), lanes, candidates)) lanes = 0;
     for (Query *Qp : act) {
         Query &Q = *Qp;
         if (Q.fail_code) continue;
         Src src;
         Steps &sa = sd[ns];
         Emit &ea = ed[ne];
-        plan_query<P, Tab>(S, Q, lanes ? Q.left : 1, sa, ea, src);
+        plan_query<P, Tab>(S, Q, lanes ? steps_ahead(Q) : 1, sa, ea, src);
         const int32_t k = sa.st.n;
         const int64_t emitted = ea.st.first[k], n_end = sa.st.n_slots[k - 1];
         if (emitted > 0) {
@@ -656,16 +670,15 @@ static int32_t co_step(mc_server *S, std::vector<Query *> &act) {
     }
     pe[ne] = be;
     ps[ns] = bs;
-    SCHK(hipMemcpyAsync(d, h, pre + ne * sizeof(Emit), hipMemcpyHostToDevice, S->stream));
-    const size_t at = pre + maxres * sizeof(Emit);
-    if (ns > 0) SCHK(hipMemcpyAsync(d + at, h + at, ns * sizeof(Steps), hipMemcpyHostToDevice, S->stream));
+    SCHK(hipMemcpyAsync(d, h, ne > 0 ? emit_at + ne * sizeof(Emit) : pre + ns * sizeof(Steps), hipMemcpyHostToDevice,
+                        S->stream));
     const int32_t *dpe = (const int32_t *)d, *dps = dpe + (maxres + 1);
     if (ne > 0) {
-        k_emit_stretch_multi<P, Tab><<<be, kBlk, 0, S->stream>>>((const Emit *)(d + pre), dpe, ne);
+        k_emit_stretch_multi<P, Tab><<<be, kBlk, 0, S->stream>>>((const Emit *)(d + emit_at), dpe, ne);
         SCHK(hipGetLastError());
     }
     if (ns > 0) {
-        const Steps *dsd = (const Steps *)(d + at);
+        const Steps *dsd = (const Steps *)(d + pre);
         switch (lanes) {
         case 0: k_step_multi<P, Tab><<<bs, kStepBlk, 0, S->stream>>>(dsd, dps, ns); break;
         case 1: launch_multi<P, Tab, 1>(S, bs, dsd, dps, ns); break;
@@ -1025,14 +1038,15 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
                                      : sizeof(EmitStretchArgs<P64, double4>);
     const size_t step_sz = S->fp32() ? (S->bf16() ? sizeof(StretchArgs<P32, bf16x4>) : sizeof(StretchArgs<P32, float4>))
                                      : sizeof(StretchArgs<P64, double4>);
+    S->ring_len = o->max_resident > kRingLargeQueries ? kRingLarge : kRing;
     S->ring_slot = (size_t)Pool::round_up((int64_t)(Pool::round_up(2 * (o->max_resident + 1) * sizeof(int32_t)) +
                                                     o->max_resident * (emit_sz + step_sz)));
-    if (hipHostMalloc((void **)&S->h_ring, kRing * S->ring_slot, hipHostMallocDefault) != hipSuccess)
+    if (hipHostMalloc((void **)&S->h_ring, S->ring_len * S->ring_slot, hipHostMallocDefault) != hipSuccess)
         return bail(sfail(S, MC_ENOMEM, "pinned descriptor ring"));
     if (hipHostMalloc((void **)&S->h_dt, 2 * (size_t)o->max_resident * sizeof(unsigned long long),
                       hipHostMallocDefault) != hipSuccess)
         return bail(sfail(S, MC_ENOMEM, "pinned step-limit buffer"));
-    if (salloc(S, (void **)&S->d_ring, kRing * S->ring_slot)) return bail(MC_ENOMEM);
+    if (salloc(S, (void **)&S->d_ring, S->ring_len * S->ring_slot)) return bail(MC_ENOMEM);
     for (int k = 0; k < kRing; ++k) SC2(hipEventCreateWithFlags(&S->ring_ev[k], hipEventDisableTiming));
     // the query pool
     if (salloc(S, (void **)&S->pool_base, (size_t)o->hbm_budget)) return bail(MC_ENOMEM);
