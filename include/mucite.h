@@ -279,6 +279,8 @@ enum { MC_K_EMIT = 0, MC_K_STEP = 1, MC_K_DEPOSIT = 2, MC_K_POISSON = 3, MC_K_FI
        MC_NKERNEL = 7 };
 typedef struct mc_timing {
     double ms[MC_NKERNEL];
+    /* MC_K_STEP and MC_K_EMIT count steps (those that emitted), of which a launch
+     * takes up to 32; the others launches */
     int64_t launches[MC_NKERNEL];
     int64_t pack_steps;      /* sum over step launches of the slots scanned */
 } mc_timing;
@@ -366,7 +368,8 @@ int32_t mc_inject(mc_ctx *ctx, int32_t src_id, int64_t n);
  * Asynchronous with a fixed step.  With the adaptive step (Eq. 1) each
  * step's length is found on the device by the step kernels themselves; the
  * call reads the record of where the run stands back once per stretch of steps
- * before a space-charge update, and at its end (while a source still emits, whose Eq. 5 counts need each length on the host, once per step).
+ * before a space-charge update, and at its end (while a source still emits,
+ * whose Eq. 5 counts need each length on the host, once per step).
  * Errors: MC_ESTATE, MC_ENOMEM (capacity), MC_ENUMERIC (adaptive step
  * collapsed; the step counter and time stay at the collapsed step),
  * MC_EDEVICE. */

@@ -17,7 +17,8 @@ using namespace mc;
 
 namespace {
 
-// Nodes of the largest grid the asynchronous entry point takes.
+// Nodes of the largest grid the asynchronous entry point takes: a limit of its
+// interface, which callers test for (no memory of its own sets it any more).
 constexpr int64_t kNoAllocMaxNodes = 1ll << 20;
 
 int32_t check_args(const mc_cic_packs *packs, const mc_grid *grid, const int64_t *q_out) {

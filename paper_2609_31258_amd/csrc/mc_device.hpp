@@ -82,7 +82,7 @@ struct P64 {
     using T = double;
     static constexpr bool kTwo = false;
     // every thread of the block calls this before the first table read
-    // (ln_fast, log1p_, sc2pi_fast, cos2pi_fast)
+    // (log1p_ and the functions of random words)
     static __device__ __forceinline__ void prepare_tables(const StepTables *src) {
         static_assert(sizeof(StepTables) % sizeof(double2) == 0, "tables move in 16-byte pieces");
         const double2 *from = reinterpret_cast<const double2 *>(src);
@@ -95,8 +95,6 @@ struct P64 {
     static __device__ __forceinline__ double u01(uint32_t w) { return ((double)w + 0.5) * 0x1p-32; }
     // every call site passes x in (0, 1] (uniform variates and their products)
     static __device__ __forceinline__ double ln(double x) { return ln_pos(x); }
-    // the same from the block's table (step kernels, after prepare_ln)
-    static __device__ __forceinline__ double ln_fast(double x) { return ln_tab(x, g_tables.ln); }
     // x >= 0 and zero or normal at every call site: the hardware reciprocal
     // square root estimate (within 2^-23) refined by sqrt_seeded
     static __device__ __forceinline__ double sqrt_(double x) { return sqrt_seeded(x, __builtin_amdgcn_rsq(x)); }
@@ -106,19 +104,14 @@ struct P64 {
     static __device__ __forceinline__ double rcp(double x) { return recip_seeded(x, __builtin_amdgcn_rcp(x)); }
     static __device__ __forceinline__ double exp_(double x) { return exp(x); }
     // every call site passes a positive ratio (the Einstein-model inverse,
-    // called in the step kernels only, after prepare_ln)
+    // called in the step kernels only, after prepare_tables)
     static __device__ __forceinline__ double log1p_(double x) { return ln1p_tab(x, g_tables.ln); }
     // sin(2 pi u), cos(2 pi u) of uniform variates u in (0, 1): a quarter-turn
     // reduction and two short series instead of the library's general reduction
     static __device__ __forceinline__ void sc2pi(double u, double *s, double *c) { sincos_turn(u, s, c); }
-    static __device__ __forceinline__ double cos2pi(double u) { return cos_turn(u); }
-    // the same from the block's turn table (step kernels, after prepare_tables)
-    static __device__ __forceinline__ void sc2pi_fast(double u, double *s, double *c) {
-        sincos_turn_tab(u, g_tables.turn, s, c);
-    }
-    static __device__ __forceinline__ double cos2pi_fast(double u) { return cos_turn_tab(u, g_tables.turn); }
-    // of the uniform variates of random words (step kernels): ln u, ln(u v),
-    // 2 u - 1, sine and cosine of u turns; the root of a positive x
+    // of the uniform variates of random words (step kernels, after
+    // prepare_tables): ln u, ln(u v), 2 u - 1, sine and cosine of u turns; the
+    // root of a positive x
     static __device__ __forceinline__ double ln_word(uint32_t w) { return mc::ln_word(w, g_tables.ln); }
     static __device__ __forceinline__ double ln_words(uint32_t w, uint32_t v) { return mc::ln_words(w, v, g_tables.ln); }
     static __device__ __forceinline__ double sym_word(uint32_t w) { return mc::sym_word(w); }
@@ -140,7 +133,6 @@ struct P32 {
     }
     static __device__ __forceinline__ void prepare_tables(const StepTables *) {}
     static __device__ __forceinline__ float ln(float x) { return __builtin_amdgcn_logf(x) * 0.693147180559945f; }
-    static __device__ __forceinline__ float ln_fast(float x) { return ln(x); }
     static __device__ __forceinline__ float sqrt_(float x) { return __builtin_amdgcn_sqrtf(x); }
     static __device__ __forceinline__ float div(float a, float b) { return a * __builtin_amdgcn_rcpf(b); }
     static __device__ __forceinline__ float rcp(float x) { return __builtin_amdgcn_rcpf(x); }
@@ -150,14 +142,11 @@ struct P32 {
         *s = __builtin_amdgcn_sinf(u);
         *c = __builtin_amdgcn_cosf(u);
     }
-    static __device__ __forceinline__ float cos2pi(float u) { return __builtin_amdgcn_cosf(u); }
-    static __device__ __forceinline__ void sc2pi_fast(float u, float *s, float *c) { sc2pi(u, s, c); }
-    static __device__ __forceinline__ float cos2pi_fast(float u) { return cos2pi(u); }
     static __device__ __forceinline__ float ln_word(uint32_t w) { return ln(u01(w)); }
     static __device__ __forceinline__ float ln_words(uint32_t w, uint32_t v) { return ln(u01(w) * u01(v)); }
     static __device__ __forceinline__ float sym_word(uint32_t w) { return 2.0f * u01(w) - 1.0f; }
     static __device__ __forceinline__ void sc2pi_word(uint32_t w, float *s, float *c) { sc2pi(u01(w), s, c); }
-    static __device__ __forceinline__ float cos2pi_word(uint32_t w) { return cos2pi(u01(w)); }
+    static __device__ __forceinline__ float cos2pi_word(uint32_t w) { return __builtin_amdgcn_cosf(u01(w)); }
     static __device__ __forceinline__ float sqrt_pos(float x) { return sqrt_(x); }
 };
 

@@ -5,8 +5,8 @@
 // of the caller's arrays: the FP32 form's pairs of floats are joined and split
 // on the way, and one launch and one wait stand for a copy call per array.  A
 // call of a pageable copy costs 16 us whatever its size; 13 of them made up a
-// read of 1e4 packs (211 us, NN us so; its write 202 -> NN us), eight small
-// ones a read of the tallies (192 -> NN us).
+// read of 1e4 packs (207 us, 88 us so; its write 195 -> 76 us), eight small
+// ones a read of the tallies (188 -> 85 us).
 #pragma once
 #include "mc_kernels.hpp"
 #include "mc_pool.hpp"
@@ -19,7 +19,9 @@ constexpr size_t kStageHalf = 2u << 20;
 struct PinnedPiece {
     static char *make() {
         void *p = nullptr;
-        return hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocPortable | hipHostMallocCoherent) == hipSuccess ? static_cast<char *>(p) : nullptr;
+        // (coherent: the halves are read after an event, without a wait for the stream)
+        const hipError_t e = hipHostMalloc(&p, 2 * kStageHalf, hipHostMallocPortable | hipHostMallocCoherent);
+        return e == hipSuccess ? static_cast<char *>(p) : nullptr;
     }
     static void free(char *p) { (void)hipHostFree(p); }
 };

@@ -1173,9 +1173,6 @@ __global__ __launch_bounds__(kDepositThreads) void k_deposit(DepositArgs<typenam
     }
 }
 
-// E = -grad(phi) on nodes: central differences, one-sided at the outer
-// edges, E_r = 0 on the axis.  clear (nullable): a charge grid zeroed on
-// the way, for the next deposit that adds into it.
 // E = -grad Phi at node n (central differences, one-sided at the ends, zero
 // radial field on the axis).
 __device__ __forceinline__ double2 sc_field_at(const double *phi, int64_t n, int32_t nr, int32_t nz, double dr,
@@ -1192,10 +1189,9 @@ __device__ __forceinline__ double2 sc_field_at(const double *phi, int64_t n, int
 }
 
 static __global__ __launch_bounds__(256) void k_bake(const double *phi, double2 *e, int32_t nr, int32_t nz, double dr,
-                                                     double dz, unsigned long long *clear) {
+                                                     double dz) {
     const int64_t n = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (n >= (int64_t)nr * nz) return;
-    if (clear) clear[n] = 0ull;
     e[n] = sc_field_at(phi, n, nr, nz, dr, dz);
 }
 

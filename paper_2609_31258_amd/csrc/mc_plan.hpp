@@ -81,7 +81,8 @@ inline double densest_explicit(const GasRows &gas, double dz, const mc_operating
     double most = 0.0;
     for (int32_t j = 0; j < nz; ++j) {
         const double c = per * gas.densest[(size_t)j];
-        const bool inside = !window || (std::max(j - 1, 0) * dz >= op.lv_z_lo && std::min(j + 1, nz - 1) * dz < op.lv_z_hi);
+        const bool inside = !window || (std::max(j - 1, 0) * dz >= op.lv_z_lo &&
+                                        std::min(j + 1, nz - 1) * dz < op.lv_z_hi);
         most = std::max(most, op.langevin_on && inside ? std::min(c, op.lv_switch) : c);
     }
     return most;

@@ -1107,7 +1107,7 @@ int32_t mc_load_fields(mc_ctx *ctx, const mc_grid *g, const mc_field_tables *t) 
     for (int k = 0; k < 3; ++k) {
         if (!phis[k]) continue;
         HIPCHK(hipMemcpyAsync(tmp, phis[k], nn * sizeof(double), hipMemcpyHostToDevice, ctx->stream));
-        k_bake<<<grid_for(nn), kBlock, 0, ctx->stream>>>(tmp, outs[k], g->nr, g->nz, g->dr, g->dz, nullptr);
+        k_bake<<<grid_for(nn), kBlock, 0, ctx->stream>>>(tmp, outs[k], g->nr, g->nz, g->dr, g->dz);
         LAUNCHCHK();
         HIPCHK(hipStreamSynchronize(ctx->stream));
     }

@@ -966,7 +966,7 @@ int32_t mc_server_create(const mc_server_options *o, const mc_grid *g, const mc_
     for (int k = 0; k < 3; ++k) {
         if (!phis[k]) continue;
         SC2(hipMemcpyAsync(tmp, phis[k], nn * sizeof(double), hipMemcpyHostToDevice, S->stream));
-        k_bake<<<blocks_for(nn), kBlk, 0, S->stream>>>(tmp, outs[k], g->nr, g->nz, g->dr, g->dz, nullptr);
+        k_bake<<<blocks_for(nn), kBlk, 0, S->stream>>>(tmp, outs[k], g->nr, g->nz, g->dr, g->dz);
         SC2(hipStreamSynchronize(S->stream));
     }
     const double *gas[4] = {t->gas_ur, t->gas_uz, t->gas_p, t->gas_t};
