@@ -503,7 +503,9 @@ def run_large(steps: int, fill: bool, n_packs: int = 16_000_000, sort_every: int
             "steps": steps, "sort_every": sort_every, "value": ps / r["wall"], "unit": "pack-steps/s",
             "ms_per_step": r["wall"] * 1e3 / steps, "active": r["active"], "classes": r["classes"],
             "collisions_per_s": r["coll"] / r["wall"], "candidates_per_pack_step": r["cand"] / max(ps, 1),
-            "kernel_ms": r["timing"]["ms"], "roofline": roofline(r, "fp32", alpha),
+            "kernel_ms": r["timing"]["ms"],
+            # (the counters of traffic and issue are of the 256 x 1024 workload's launches)
+            "roofline": {**roofline(r, "fp32", alpha), "traffic": None, "issue": None},
             "cpu_slice": {"value": n_cpu * cpu_steps / wall_o, "unit": "pack-steps/s", "cores": num_threads(),
                           "kind": "oracle", "sample": f"{n_cpu} packs of the same snapshot, {cpu_steps} steps, "
                                                       f"no space-charge update, {wall_o:.1f} s",
