@@ -701,8 +701,8 @@ __device__ __forceinline__ void flush_counts(const TallyPtrs &t, const StepCount
 // Waves per SIMD the step kernel is compiled for (its register budget):
 // the FP64 form holds its loop state in register pairs and runs three waves
 // in 143 registers (three measured 3 % faster than two and 2 % faster than
-// four, which spill); the FP32 form fits five.  No register is spilled to
-// memory.
+// four, which spill); the FP32 form fits five.  No vector register is spilled;
+// a few scalars are kept in lanes of vector registers.
 template <class P, class Tab>
 constexpr int step_waves() {
     return P::kTwo ? 5 : 3;
