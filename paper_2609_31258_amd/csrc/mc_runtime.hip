@@ -656,14 +656,24 @@ static int32_t seed_limits(mc_ctx *ctx, PackPtrs<typename P::T> p) {
     return MC_OK;
 }
 
+// What adaptive steps keep on the device, taken as one piece: a refusal leaves
+// nothing behind that a later call would take for the whole.
+struct AdaptiveMemory {
+    unsigned long long lines[4 * kHotLen];  // three sets for k_stretch_adaptive, one for a step that the host sizes
+    unsigned long long out[2];
+    DtRecord rec[2];
+    DtStep found;
+};
+
 static int32_t adaptive_buffers(mc_ctx *ctx) {
     if (ctx->dt_rep) return MC_OK;
-    // three sets of lines for k_stretch_adaptive, one for a step that the host sizes
-    int32_t rc = dalloc_t(ctx, &ctx->dt_rep, 4 * (size_t)kHotLen);
-    if (!rc) rc = dalloc_t(ctx, &ctx->dt_out, 2);
-    if (!rc) rc = dalloc_t(ctx, &ctx->dt_rec, 2);
-    if (!rc) rc = dalloc_t(ctx, &ctx->dt_found, 1);
+    AdaptiveMemory *mem = nullptr;
+    const int32_t rc = dalloc_t(ctx, &mem, 1);
     if (rc) return rc;
+    ctx->dt_rep = mem->lines;
+    ctx->dt_out = mem->out;
+    ctx->dt_rec = mem->rec;
+    ctx->dt_found = &mem->found;
     k_dt_reset<<<4, kHotRep, 0, ctx->stream>>>(ctx->dt_rep);
     LAUNCHCHK();
     return MC_OK;

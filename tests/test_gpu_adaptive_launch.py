@@ -87,3 +87,33 @@ def test_short_batches_equal_calls_of_one_step(n, precision, tables, species):
     for per_call in (2, 3):
         for a, b in zip(one, _run(n, precision, tables, species, per_call)):
             assert a.shape == b.shape and a.tobytes() == b.tobytes()
+
+
+def test_a_refused_adaptive_step_is_refused_again():
+    """A budget that holds the limit lines (four sets of 128 lines of 128 bytes) but not the records beside them
+    refuses the adaptive step each time it is asked for, and the context goes on with fixed steps: as a context that
+    was never refused, bit for bit."""
+    from paper_2609_31258_amd import mucite
+    _say("adaptive step refused by the budget")
+    n = 300
+    f, ion = synth.uniform_fields(20, 40, 5e-5), synth.config_c1(10)[1][0]
+    op = synth.Operating(dt=1e-9, z_det=f.grid.L, r_det=f.grid.R)
+    snap = synth.pack_snapshot(n, f, seed=4, z_lo=0.2 * f.grid.L, z_hi=0.8 * f.grid.L, r_hi=0.5 * f.grid.R)
+    out, budget = [], 0  # (a grid this small takes less to load than the tallies and the lines do afterwards)
+    for refused in (False, True):
+        with mucite.Sim(seed=3, pack_capacity=n, precision=0, hbm_budget=budget) as g:
+            op.adaptive = int(refused)
+            g.setup(f, [ion], [], op)
+            g.write_packs(snap)
+            budget = g.info()["device_bytes"] + 4 * 128 * 128
+            for _ in range(2 if refused else 0):
+                with pytest.raises(mucite.MucateError) as err:
+                    g.step(5)
+                assert err.value.code == mucite.MC_EBUDGET
+                assert g.info()["step"] == 0
+            op.adaptive = 0
+            g.set_operating(op)
+            g.step(5)
+            out.append(g.read_packs())
+    for k in out[0]:
+        assert np.array_equal(out[0][k], out[1][k]), k
