@@ -1224,20 +1224,12 @@ int32_t mc_set_operating(mc_ctx *ctx, const mc_operating *op) {
     const bool first = !ctx->has_op;
     if (!first && op->n_exit_bins != ctx->op.n_exit_bins)
         return fail(ctx, MC_ESTATE, "the number of exit bins is fixed by the first operating point");
-    ctx->op = *op;
-    ctx->c_next_valid = false;  // RF and step settings may have changed
-    ctx->has_op = true;
-    for (size_t k = 0; k < ctx->ions.size(); ++k) ctx_alpha(ctx, k);
-    find_most_cand(ctx);
-    ctx->lv_share.forget(false);
-    int32_t rc = upload_species(ctx);
-    if (rc) return rc;
     const int64_t nn = (int64_t)ctx->nr * ctx->nz;
     if (first) {
         const int64_t base = TC_N + op->n_exit_bins + nn + MC_HIST_KE + MC_HIST_TEFF + MC_HIST_R;
         ctx->tal_len = hot_offset(base) + kHotLen;
-        rc = dalloc_t(ctx, &ctx->tal, ctx->tal_len);
-        if (rc) return rc;
+        const int32_t rc = dalloc_t(ctx, &ctx->tal, ctx->tal_len);
+        if (rc) return rc;  // (the context stays without an operating point)
         HIPCHK(hipMemsetAsync(ctx->tal, 0, ctx->tal_len * sizeof(unsigned long long), ctx->stream));
         unsigned long long *p = ctx->tal;
         ctx->tp.cnt = p;
@@ -1253,6 +1245,14 @@ int32_t mc_set_operating(mc_ctx *ctx, const mc_operating *op) {
         ctx->tp.hist_r = p;
         ctx->tp.hot = ctx->tal + hot_offset(base);
     }
+    ctx->op = *op;
+    ctx->c_next_valid = false;  // RF and step settings may have changed
+    ctx->has_op = true;
+    for (size_t k = 0; k < ctx->ions.size(); ++k) ctx_alpha(ctx, k);
+    find_most_cand(ctx);
+    ctx->lv_share.forget(false);
+    int32_t rc = upload_species(ctx);
+    if (rc) return rc;
     const double reach = op->d_hit + 0.5 * std::min(ctx->dr, ctx->dz);
     const int32_t wi = (int32_t)std::ceil(reach / ctx->dr), wj = (int32_t)std::ceil(reach / ctx->dz);
     k_hit<<<grid_for(nn), kBlock, 0, ctx->stream>>>(ctx->mask, ctx->hit, ctx->nr, ctx->nz, ctx->dr, ctx->dz, reach, wi,

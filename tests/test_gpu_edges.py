@@ -227,3 +227,27 @@ def test_a_load_after_a_refused_one_solves_with_its_own_tables():
     assert np.abs(out[1][0]).max() > 0.0
     for a, b in zip(*out):
         assert np.array_equal(a, b)
+
+
+def test_a_refused_operating_point_leaves_the_context_without_one():
+    """A budget that the fields fit but the tallies do not refuses the operating point each time, and steps, which
+    have nowhere to count, are refused as before any operating point."""
+    from paper_2609_31258_amd import mucite
+    _say("operating point refused by the budget")
+    f, ion = synth.uniform_fields(20, 40, 5e-5), synth.config_c1(10)[1][0]
+    op = synth.Operating(dt=1e-9, z_det=f.grid.L, r_det=f.grid.R, n_exit_bins=20_000)
+    probe = mucite.Sim(seed=1, pack_capacity=500)
+    probe.load_fields(f)
+    budget = probe.info()["device_bytes"] + 8 * op.n_exit_bins  # (short of the other tallies)
+    probe.close()
+    s = mucite.Sim(seed=1, pack_capacity=500, hbm_budget=budget)
+    s.load_fields(f)
+    s.define_ion(ion)
+    for _ in range(2):
+        with pytest.raises(mucite.MucateError) as err:
+            s.set_operating(op)
+        assert err.value.code == mucite.MC_EBUDGET
+        with pytest.raises(mucite.MucateError) as err:
+            s.step(1)
+        assert err.value.code == mucite.MC_ESTATE
+    s.close()
